@@ -7,18 +7,22 @@
 //    holds at least k rows); the columns are processed in panels of width
 //    kPanel;
 //  * per panel, every leaf factors its active rows of the panel with
-//    Householder reflectors in LDS, forms the compact-WY factor T
+//    Householder reflectors held in registers, forms the compact-WY factor T
 //    (H_0...H_(w-1) = I - V T V^T) and updates its trailing columns with
 //    C <- C - V T^T (V^T C), three small GEMMs on the FP64 matrix cores;
 //  * the w x w triangles the leaves leave in their top rows are combined
-//    four at a time up a reduction tree (depth log4 of the leaf count);
+//    eight at a time up a reduction tree (depth log8 of the leaf count);
 //    combining stacked upper triangles gives reflectors [e_j; v] with v
 //    upper triangular in each absorbed triangle, stored in its place, and
 //    their own WY factor updates the trailing columns of the node's rows;
-//  * Q = prod_p L_p T_p [I; 0] is then formed by applying the tree and leaf
-//    WY factors (C <- C - V T (V^T C)) in reverse order to [I_k; 0], on the
-//    columns that can be non-trivial, and each column c is multiplied by
-//    sign(R_cc) so that R has a non-negative diagonal.
+//  * a factorisation reads only the panel and a trailing update of the level
+//    below writes only the trailing columns, so the two share one launch;
+//  * the caller's block is read by panel 0 only; the factors live in a working
+//    copy, and Q = prod_p L_p T_p [S; 0], S = diag(sign R_cc) (so that R has
+//    a non-negative diagonal), is formed in the caller's block by applying
+//    the tree and leaf WY factors (C <- C - V T (V^T C)) in reverse order on
+//    the columns that can be non-trivial; rows of [S; 0] that no factor has
+//    touched yet are taken as known, not read.
 // Reflectors follow the LAPACK dlarfg convention: beta = -sign(alpha) * norm,
 // tau = (beta - alpha) / beta, and tau = 0 (H = I) when the part below the
 // diagonal is exactly zero, so rank-deficient blocks never divide by zero.
@@ -30,267 +34,334 @@ namespace {
 
 constexpr int kPanel = 32;
 constexpr int kLeafRows = 192;   // three rows per lane of one wavefront
-constexpr int kLR = kLeafRows + 1;   // odd row length: fragment reads hit distinct banks
 constexpr int kT = kPanel + 1;   // padded row length of the small LDS matrices
 
 struct QrPlan {
   int N, k, nb, P, depth;
 };
 
-__host__ __device__ inline int leaf_start(int i, int N, int nb) {
-  return (int)(((long)i * N) / nb);
-}
-
-__device__ __forceinline__ double wave_sum(double x) { return wave_sum64(x); }
-
-// C(M x N) = sum_k A(m, k) B(k, n) for operands in LDS, on the FP64 matrix
-// cores (v_mfma_f64_16x16x4: operand lane l -> (row l%16, k l/16), result
-// element r -> (row l/16 + 4r, column l%16)).  16x16 blocks are dealt to the
-// four wavefronts; `store(m, n, value)` receives every result element once.
-// The operands of kMmStage k-steps are read into registers before their
-// products issue, so that one LDS latency covers kMmStage products, and the
-// products rotate over four accumulators.  Indices outside the operands are
-// clamped to element (0, 0) for the read and their values replaced by zero,
-// so every LDS read stays inside the caller's arrays.
-constexpr int kMmStage = 8;
-template <typename FA, typename FB, typename FS>
-__device__ __forceinline__ void lds_mm(int M, int N, int K, FA A, FB B, FS store, int wave,
-                                       int lane) {
-  const int bm = (M + 15) >> 4, bn = (N + 15) >> 4;
-  for (int blk = wave; blk < bm * bn; blk += 4) {
-    const int i0 = (blk / bn) << 4, j0 = (blk % bn) << 4;
-    const int ar = i0 + (lane & 15), bc = j0 + (lane & 15);
-    const bool ain = ar < M, bin = bc < N;
-    const int arc = ain ? ar : 0, bcc = bin ? bc : 0;
-    v4d acc[4] = {{0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}};
-    for (int k0 = 0; k0 < K; k0 += 4 * kMmStage) {
-      double a[kMmStage], b[kMmStage];
-#pragma unroll
-      for (int u = 0; u < kMmStage; ++u) {
-        const int ka = k0 + 4 * u + (lane >> 4);
-        const bool kin = ka < K;
-        const int kc = kin ? ka : 0;
-        const double av = A(arc, kc), bv = B(kc, bcc);
-        a[u] = (ain && kin) ? av : 0.0;
-        b[u] = (bin && kin) ? bv : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < kMmStage; ++u)
-        acc[u & 3] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u], acc[u & 3], 0, 0, 0);
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = i0 + (lane >> 4) + 4 * r, col = j0 + (lane & 15);
-      if (row < M && col < N) store(row, col, (acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r]));
-    }
-  }
-}
-
-// Global -> LDS copy with kInFlight independent loads per thread before the
-// LDS stores: one workgroup per CU leaves nothing else to hide the latency.
-constexpr int kInFlight = 8;
-template <typename FL, typename FS>
-__device__ __forceinline__ void g2l(int count, int tid, FL load, FS store) {
-  for (int base = tid; base < count; base += 256 * kInFlight) {
-    double t[kInFlight];
-#pragma unroll
-    for (int u = 0; u < kInFlight; ++u) {
-      const int i = base + u * 256;
-      t[u] = i < count ? load(i) : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < kInFlight; ++u) {
-      const int i = base + u * 256;
-      if (i < count) store(i, t[u]);
-    }
-  }
-}
-
 struct QrArgs {
-  double* A[kMaxProb];   // matrices being factored (in place)
-  double* E[kMaxProb];   // explicit Q being formed
-  double* O[kMaxProb];   // destination of Q
-  double* tau;           // [count][P][nb][kPanel] leaf taus
+  double* W[kMaxProb];   // the caller's blocks: read by panel 0, then Q
+  double* A[kMaxProb];   // working copies holding V and R
   double* Tl;            // [count][P][nb][kPanel*kPanel] leaf WY factors
   double* Tn;            // [count][P][nb][kPanel*kPanel] tree WY factors (by right child)
-  double* sgn;           // [count][k] signs of the diagonal of R
   int count, N, k, nb, P;
+  int rows, extra;       // leaves hold `rows` rows, the first `extra` one more
 };
+
+// First row of leaf i (no division: the kernels start with this).
+__device__ __forceinline__ int leaf_start(const QrArgs& q, int i) {
+  return i * q.rows + min(i, q.extra);
+}
 
 __device__ __forceinline__ long slot(int mat, int p, int leaf, int nb, int P) {
   return ((long)mat * P + p) * nb + leaf;
 }
 
-// T (w x w, upper) of H_0...H_(w-1) = I - V T V^T from the Gram matrix
-// G = V^T V (strict upper part) and the taus, forward columnwise:
-// T_jj = tau_j, T[i, j] = -tau_j sum_{l=i}^{j-1} T[i, l] G[l, j] for i < j.
-// Row i depends only on itself, so lane i builds row i in registers.
-__device__ __forceinline__ void build_T(double (*T)[kT], double (*G)[kT], const double* tau,
-                                        int w, int lane) {
-  double t[kPanel];
-#pragma unroll
-  for (int j = 0; j < kPanel; ++j) {
-    double acc = 0.0;
-#pragma unroll
-    for (int l = 0; l < j; ++l) acc += t[l] * G[l][j];   // t[l] = 0 for l < lane
-    const double tj = j < w ? tau[j] : 0.0;
-    t[j] = lane < j ? -tj * acc : (lane == j ? tj : 0.0);
-  }
-  if (lane < kPanel) {
-#pragma unroll
-    for (int j = 0; j < kPanel; ++j) T[lane][j] = t[j];
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Householder factorisation of one panel by the four wavefronts of a
-// workgroup, each holding 64 rows of the panel in registers: x[c] is column
-// c of the lane's row.  The pivot of column j is row j, held by lane j of
-// wavefront 0; on(j) says whether the lane's row carries reflector j (lies
-// below the pivot).  Rows and columns outside the panel are held as zeros,
-// so they take part in every sum without changing it.  Per column every
-// wavefront reduces its share of the squared norm and wavefront 0 publishes
-// the pivot; after a barrier all wavefronts form the same reflector (dlarfg
-// convention); one transpose-reduction per wavefront (wave_xsum32) of the
-// products v_j^T x_s, a barrier, and the four shares summed in a fixed
-// order give every wavefront the same v_j^T x_s for the later columns s > j
-// (applied at once from scalar registers) and v_s^T v_j for the earlier
-// ones (the Gram column of the WY factor T, written by wavefront 0).  The
-// shared sums are double-buffered by column parity, so two barriers per
-// column order all reads and writes.
+// workgroup.  The panel sits in registers, a column per lane: lane c of a
+// 16-lane row holds the panel columns c and c + 16 of the rows g + 16 r,
+// r < R, where g = 0..15 numbers the 16-lane rows of the workgroup.  A step
+// needs column j in every lane of its row, which is one DPP broadcast per
+// register (row_newbcast), then 2 R multiply-adds give the row's share of
+// x_j^T x_s for the lane's two columns s: the squared norm of the column
+// (s = j) and the products of all others come from the same sums, so a step
+// has one exchange between the wavefronts (through LDS, double-buffered by
+// the parity of j) and one barrier.  With S_s the sum below the pivot and
+// a_s the pivot row, the reflector (dlarfg: beta = -sign(a_j) |(a_j, x_j)|,
+// v = x_j / (a_j - beta)) gives v^T x_s = a_s + S_s / (a_j - beta), and for
+// the earlier columns the Gram column of the WY factor T.  Reflectors stay
+// unscaled in their registers (each lane keeps the scale of its columns);
+// the pivot row goes to Rs as it becomes a row of R and is zeroed from
+// column j on, so that no later sum needs a mask.  Every wavefront forms the
+// same reflector from the same sums in the same order, and writes the same
+// values to the same places where only one would have to: a step without
+// branches is faster than one with less to store.
+//
+// Bound by latency: 32 dependent steps.  Measured on 8 blocks of
+// 5184 x 160, one row per lane with a 63-add transpose-reduction of the 32
+// products per step, a second reduction for the norm and a second barrier
+// took 51.7 us per launch of leaves (44.0 us of tree nodes); this form takes
+// 28.3 us, of which the 32 steps are 17 us (1290 cycles each).
 // ---------------------------------------------------------------------------
 
-// 1/x to full double precision from the hardware estimate (two Newton
-// steps); x is never zero where it is used.
+// 1/x and 1/sqrt(x) to full double precision from the hardware estimates (two
+// Newton steps), for arguments away from the ends of the exponent range.
 __device__ __forceinline__ double fast_rcp(double x) {
   double r = __builtin_amdgcn_rcp(x);
   r = fma(r, fma(-x, r, 1.0), r);
   return fma(r, fma(-x, r, 1.0), r);
 }
+__device__ __forceinline__ double fast_rsq(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = fma(y, fma(-0.5 * x * y, y, 0.5), y);
+  return fma(y, fma(-0.5 * x * y, y, 0.5), y);
+}
 
-struct PanelShare {
-  double ss[2][4];          // squared norms below the pivot, per wavefront
-  double alpha[2];          // pivot value
-  double dot[2][4][kPanel]; // v_j^T x_s per wavefront
+// Lane L of each 16-lane row, in every lane of the row.
+template <int L>
+__device__ __forceinline__ double row_bcast(double x) {
+  return __longlong_as_double(
+      __builtin_amdgcn_update_dpp(0LL, __double_as_longlong(x), 0x150 + L, 0xf, 0xf, true));
+}
+
+constexpr int kGL = kPanel + 2;   // row length of Gt: 16-byte aligned rows
+
+struct PanelLds {
+  double part[2][4][kPanel];     // [buffer][wavefront][chunk a | chunk b]: x_j^T x_s below the pivot
+  double alpha[2][16][kPanel];   // [buffer][16-lane row][chunk a | chunk b]: register row 0
+  double Rs[kPanel][kT];         // R
+  double Gt[kPanel][kGL];        // Gt[j][s] = v_s^T v_j for s < j, Gt[j][j] = tau_j
+  double T[kPanel][kT];
 };
 
-// Squared norm below the pivot of column j (this wavefront's share) and the
-// pivot value, published for the step that factors column j.
-template <int J, typename On>
-__device__ __forceinline__ void publish_norm(const double (&x)[kPanel], int lane, int wave,
-                                             const On& on, PanelShare& sh) {
-  constexpr int b = J & 1;
-  const double ssw = wave_sum64(on(J) ? x[J] * x[J] : 0.0);
-  if (lane == 0) sh.ss[b][wave] = ssw;
-  if (wave == 0 && lane == J) sh.alpha[b] = x[J];
-}
+// The pass over the columns works on a pair of column chunks: `a` holds the
+// 16 pivots of this half of the panel, `b` the other 16 columns; register 0
+// of each holds the pivot rows (the halves trade places between the passes).
+template <int R>
+struct PanelRegs {
+  double a[R], b[R];       // unscaled panel entries
+  double sa, sb;           // scales of the lane's reflectors
+};
 
-// Step J of the panel factorisation (J is a template parameter so that every
-// register of the panel is addressed statically); columns J >= w are absent.
-// Column J + 1 is updated first and its norm published before the other
-// columns are updated, so that its reduction overlaps their updates.
-template <int J, typename On>
-__device__ __forceinline__ void panel_step(double (&x)[kPanel], int w, int lane, int wave,
-                                           const On& on, double* tau_out, double (*G)[kT],
-                                           PanelShare& sh) {
-  if (J < w) {
-    constexpr int b = J & 1;
-    const bool bj = on(J);
-    const bool piv = wave == 0 && lane == J;
-    __syncthreads();
-    const double ss = (sh.ss[b][0] + sh.ss[b][1]) + (sh.ss[b][2] + sh.ss[b][3]);
-    const double alpha = sh.alpha[b];
-    // dlarfg: beta = -sign(alpha) |(alpha, x)|, tau = (beta - alpha) / beta,
-    // v = x / (alpha - beta); H = I (tau = 0) when x is exactly zero
-    const bool live = ss > 0.0;
-    const double nrm = sqrt(alpha * alpha + ss);
-    const double beta = live ? (alpha >= 0.0 ? -nrm : nrm) : alpha;
-    const double tau = live ? (beta - alpha) * fast_rcp(beta) : 0.0;
-    const double scal = live ? fast_rcp(alpha - beta) : 0.0;
-    const double vj = bj ? x[J] * scal : (piv ? 1.0 : 0.0);
-    x[J] = bj ? vj : (piv ? beta : x[J]);
-    if (wave == 0 && lane == 0) tau_out[J] = tau;
-    const double part = wave_xsum32([&](int s) { return s == J ? 0.0 : vj * x[s]; }, lane);
-    const int col = lane >> 1;
-    if (!(lane & 1)) sh.dot[b][wave][col] = part;
-    __syncthreads();
-    const double tot =
-        (sh.dot[b][0][col] + sh.dot[b][1][col]) + (sh.dot[b][2][col] + sh.dot[b][3][col]);
-    if (wave == 0 && !(lane & 1) && col < J) G[col][J] = tot;
-    const double f = tau * tot;
-    if constexpr (J + 1 < kPanel) {
-      x[J + 1] -= readlane_f64(f, 2 * (J + 1)) * vj;
-      publish_norm<J + 1>(x, lane, wave, on, sh);
+// Column j = j0 + JL; j0 = 0 or 16, chunk a starts at column j0, chunk b at
+// 16 - j0.
+template <int JL, int R>
+__device__ __forceinline__ void panel_step(PanelRegs<R>& x, int j0, int w, int lane, int wave,
+                                           PanelLds& sh) {
+  const int j = j0 + JL;
+  if (j < w) {
+    constexpr int buf = JL & 1;
+    const int c = lane & 15, row = (lane >> 4) + 4 * wave;
+    const bool piv = row == JL;   // this 16-lane row holds the pivot row
+    const bool upper = lane >= 32;
+    sh.alpha[buf][row][c] = x.a[0];
+    sh.alpha[buf][row][16 + c] = x.b[0];
+    double v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = row_bcast<JL>(x.a[r]);
+    v[0] = piv ? 0.0 : v[0];
+    double p0 = 0.0, p1 = 0.0, q0 = 0.0, q1 = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; r += 2) {
+      p0 = fma(v[r], x.a[r], p0);
+      q0 = fma(v[r], x.b[r], q0);
+      p1 = fma(v[r + 1], x.a[r + 1], p1);
+      q1 = fma(v[r + 1], x.b[r + 1], q1);
     }
+    double p = p0 + p1, q = q0 + q1;
+    swap_halves32(p, q);   // lanes < 32 sum chunk a, the others chunk b
+    p += q;
+    q = p;
+    swap_halves16(p, q);
+    p += q;
+    sh.part[buf][wave][(upper ? 16 : 0) + c] = p;
+    __syncthreads();
+    const double aa = sh.alpha[buf][JL][c], ab = sh.alpha[buf][JL][16 + c];
+    const double Sa = (sh.part[buf][0][c] + sh.part[buf][1][c]) +
+                      (sh.part[buf][2][c] + sh.part[buf][3][c]);
+    const double Sb = (sh.part[buf][0][16 + c] + sh.part[buf][1][16 + c]) +
+                      (sh.part[buf][2][16 + c] + sh.part[buf][3][16 + c]);
+    const double ss = row_bcast<JL>(Sa), al = row_bcast<JL>(aa);
+    // tau = (beta - alpha) / beta; H = I (tau = 0) when the part below the
+    // pivot is exactly zero
+    const double q2 = fma(al, al, ss);
+    const double y = fast_rsq(q2);
+    double nrm = q2 * y;
+    nrm = fma(0.5 * y, fma(-nrm, nrm, q2), nrm);
+    double tau = fma(fabs(al), y, 1.0), inv = fast_rcp(fabs(al) + nrm);
+    // the estimates hold away from the ends of the exponent range (the
+    // condition is the same in every lane)
+    if (__builtin_expect(!__all(q2 > 1e-280 && q2 < 1e280), 0)) {
+      nrm = sqrt(q2);
+      tau = 1.0 + fabs(al) / nrm;
+      inv = 1.0 / (fabs(al) + nrm);
+    }
+    const bool live = !(ss == 0.0);
+    const double beta = live ? -copysign(nrm, al) : al;
+    const double scal = live ? copysign(inv, al) : 0.0;
+    tau = live ? tau : 0.0;
+    const double da = fma(scal, Sa, aa), db = fma(scal, Sb, ab);
+    const double fa = c > JL ? tau * da : 0.0, fb = j0 == 0 ? tau * db : 0.0;
+    const double ga = -fa * scal, gb = -fb * scal;
 #pragma unroll
-    for (int s = J + 2; s < kPanel; ++s) x[s] -= readlane_f64(f, 2 * s) * vj;
+    for (int r = 0; r < R; ++r) {
+      x.a[r] = fma(ga, v[r], x.a[r]);
+      x.b[r] = fma(gb, v[r], x.b[r]);
+    }
+    x.a[0] = piv && c >= JL ? 0.0 : x.a[0];
+    x.b[0] = piv && j0 == 0 ? 0.0 : x.b[0];
+    // row j of Gt (columns below j count) and of R (columns from j on count)
+    const int col = (upper ? 16 - j0 : j0) + c;
+    const double gram = upper ? x.sb * db : (c == JL ? tau : x.sa * da);
+    const double rrow = upper ? ab - fb : (c == JL ? beta : aa - fa);
+    sh.Gt[j][col] = gram;
+    sh.Rs[j][col] = rrow;
+    x.sa = c == JL ? scal : x.sa;
   }
-  if constexpr (J + 1 < kPanel) panel_step<J + 1>(x, w, lane, wave, on, tau_out, G, sh);
 }
 
-// The whole panel; afterwards wavefront 0 forms T from the Gram columns.
-template <typename On>
-__device__ __forceinline__ void block_panel_qr(double (&x)[kPanel], int w, int lane, int wave,
-                                               On on, double* tau_s, double (*G)[kT],
-                                               double (*T)[kT], PanelShare& sh) {
-  publish_norm<0>(x, lane, wave, on, sh);
-  panel_step<0>(x, w, lane, wave, on, tau_s, G, sh);
-  if (wave == 0) build_T(T, G, tau_s, w, lane);
+template <int R>
+__device__ __forceinline__ void swap_chunks(PanelRegs<R>& x) {
+  auto sw = [](double& p, double& q) {
+    const double t = p;
+    p = q;
+    q = t;
+  };
+  sw(x.a[0], x.a[1]);
+  sw(x.b[0], x.b[1]);
+#pragma unroll
+  for (int r = 0; r < R; ++r) sw(x.a[r], x.b[r]);
+  sw(x.sa, x.sb);
 }
 
-// ---------------------------------------------------------------------------
-// leaf factorisation of panel p (the trailing columns: qr_leaf_wy)
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void qr_leaf_factor(QrArgs q, int p) {
-  __shared__ double T[kPanel][kT], G[kPanel][kT];
-  __shared__ double tau_s[kPanel];
-  __shared__ PanelShare sh;
-  const int leaf = blockIdx.x, mat = blockIdx.y;
+// T (upper) of H_0...H_(w-1) = I - V T V^T from Gt.  The 8 x 8 diagonal
+// blocks are built columnwise, T_jj = tau_j, T[i, j] = -tau_j sum_{l=i}^{j-1}
+// T[i, l] G[l, j], one block per wavefront, a row per lane; two blocks side
+// by side then merge with T_12 = -T_11 (G_12 T_22), to 16 x 16 and to
+// 32 x 32.  (One wavefront building all 32 columns, a chain of 496
+// multiply-adds fed from LDS, took 11000 cycles of a panel's 63000.)
+__device__ __forceinline__ void build_T(PanelLds& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int N = q.N, k = q.k, nb = q.nb;
-  const int c0 = p * kPanel, w = min(kPanel, k - c0);
-  const int s = leaf_start(leaf, N, nb), e = leaf_start(leaf + 1, N, nb);
-  const int a0 = (leaf == 0) ? c0 : s;
-  const int m = e - a0;
-  double* A = q.A[mat];
-  // row (lane + 64 wave) of the leaf's active rows; rows at or beyond m are
-  // held as zeros
-  const int row = lane + 64 * wave;
-  double x[kPanel];
+  double (*Y)[kT] = sh.Rs;   // R has been stored
   {
-    const double* src = A + (long)(a0 + (row < m ? row : 0)) * k + c0;
+    const int b = 8 * wave;
+    double t[8];
 #pragma unroll
-    for (int c = 0; c < kPanel; ++c) x[c] = (row < m && c < w) ? src[c] : 0.0;
-  }
-  block_panel_qr(x, w, lane, wave, [&](int j) { return row > j; }, tau_s, G, T, sh);
-  if (row < m) {
-    double* dst = A + (long)(a0 + row) * k + c0;
+    for (int j = 0; j < 8; ++j) {
+      double acc[2] = {0.0, 0.0};
 #pragma unroll
-    for (int c = 0; c < kPanel; ++c)
-      if (c < w) dst[c] = x[c];
+      for (int l = 0; l < j; ++l) acc[l & 1] = fma(t[l], sh.Gt[b + j][b + l], acc[l & 1]);
+      const double tj = sh.Gt[b + j][b + j];
+      t[j] = lane < j ? -tj * (acc[0] + acc[1]) : (lane == j ? tj : 0.0);   // t[l] = 0 for l < lane
+    }
+    if (lane < 8) {
+#pragma unroll
+      for (int j = 0; j < kPanel; ++j) sh.T[b + lane][j] = 0.0;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) sh.T[b + lane][b + j] = t[j];
+    }
   }
   __syncthreads();
+  // merges at width h: thread (i, c) forms one element
+  auto merge = [&](int h, int i, int c, int o, bool on) {
+    double y = 0.0;
+    if (on) {
+      for (int l = 0; l < h; ++l) y = fma(sh.Gt[o + h + l][o + i], sh.T[o + h + l][o + h + c], y);
+      Y[o + i][c] = y;
+    }
+    __syncthreads();
+    if (on) {
+      double z = 0.0;
+      for (int l = 0; l < h; ++l) z = fma(sh.T[o + i][o + l], Y[o + l][c], z);
+      sh.T[o + i][o + h + c] = -z;
+    }
+    __syncthreads();
+  };
+  merge(8, lane >> 3, lane & 7, 16 * wave, wave < 2);
+  merge(16, tid >> 4, tid & 15, 0, true);
+}
+
+// Loads the panel through ld(g, r, column), factors it, returns V and R
+// through st(g, r, column, V entry, R entry) (row g + 16 r; the R entry is
+// meaningful for r < 2) and forms T.
+template <int R, typename LD, typename ST>
+__device__ __forceinline__ void panel_qr(int w, int lane, int wave, PanelLds& sh, LD ld, ST st) {
+  static_assert(R >= 2 && R % 2 == 0, "register rows");
+  PanelRegs<R> x;
+  const int g = (lane >> 4) + 4 * wave, c = lane & 15;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    x.a[r] = ld(g, r, c);
+    x.b[r] = ld(g, r, c + 16);
+  }
+  x.sa = x.sb = 0.0;
+  // rows of Gt and Rs at or beyond w are never written
+  for (int i = threadIdx.x; i < kPanel * kPanel; i += 256) {
+    sh.Gt[i >> 5][i & 31] = 0.0;
+    sh.Rs[i >> 5][i & 31] = 0.0;
+  }
+  __syncthreads();
+  // two passes over one copy of the code (the instruction cache holds it)
+#pragma unroll 1
+  for (int j0 = 0; j0 < kPanel; j0 += 16) {
+    panel_step<0>(x, j0, w, lane, wave, sh);
+    panel_step<1>(x, j0, w, lane, wave, sh);
+    panel_step<2>(x, j0, w, lane, wave, sh);
+    panel_step<3>(x, j0, w, lane, wave, sh);
+    panel_step<4>(x, j0, w, lane, wave, sh);
+    panel_step<5>(x, j0, w, lane, wave, sh);
+    panel_step<6>(x, j0, w, lane, wave, sh);
+    panel_step<7>(x, j0, w, lane, wave, sh);
+    panel_step<8>(x, j0, w, lane, wave, sh);
+    panel_step<9>(x, j0, w, lane, wave, sh);
+    panel_step<10>(x, j0, w, lane, wave, sh);
+    panel_step<11>(x, j0, w, lane, wave, sh);
+    panel_step<12>(x, j0, w, lane, wave, sh);
+    panel_step<13>(x, j0, w, lane, wave, sh);
+    panel_step<14>(x, j0, w, lane, wave, sh);
+    panel_step<15>(x, j0, w, lane, wave, sh);
+    swap_chunks(x);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    st(g, r, c, x.sa * x.a[r], r < 2 ? sh.Rs[g + 16 * r][c] : 0.0);
+    st(g, r, c + 16, x.sb * x.b[r], r < 2 ? sh.Rs[g + 16 * r][c + 16] : 0.0);
+  }
+  build_T(sh);
+}
+
+// ---------------------------------------------------------------------------
+// leaf factorisation of panel p (the trailing columns: leaf_wy)
+// ---------------------------------------------------------------------------
+template <int R>
+__device__ __forceinline__ void leaf_factor(const QrArgs& q, int p, int leaf, int mat,
+                                            PanelLds& sh) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int k = q.k, nb = q.nb;
+  const int c0 = p * kPanel, w = min(kPanel, k - c0);
+  const int s = leaf_start(q, leaf), e = leaf_start(q, leaf + 1);
+  const int a0 = (leaf == 0) ? c0 : s;
+  const int m = e - a0;
+  const double* src = (p == 0 ? q.W[mat] : q.A[mat]) + (long)a0 * k + c0;
+  double* dst = q.A[mat] + (long)a0 * k + c0;
+  // rows at or beyond m and columns at or beyond w are held as zeros
+  panel_qr<R>(
+      w, lane, wave, sh,
+      [&](int g, int r, int c) {
+        return g + 16 * r < m && c < w ? (src + (long)(16 * r) * k)[g * k + c] : 0.0;
+      },
+      [&](int g, int r, int c, double v, double rv) {
+        const int row = g + 16 * r;
+        if (row < m && c < w) (dst + (long)(16 * r) * k)[g * k + c] = c >= row ? rv : v;
+      });
   const long sl = slot(mat, p, leaf, nb, q.P);
-  if (tid < w) q.tau[sl * kPanel + tid] = tau_s[tid];
   for (int idx = tid; idx < kPanel * kPanel; idx += 256)
-    q.Tl[sl * kPanel * kPanel + idx] = T[idx / kPanel][idx % kPanel];
+    q.Tl[sl * kPanel * kPanel + idx] = sh.T[idx / kPanel][idx % kPanel];
+}
+
+// R register rows hold leaves of up to 16 R rows.
+template <int R>
+__global__ __launch_bounds__(256) void qr_leaf_factor(QrArgs q, int p) {
+  __shared__ PanelLds sh;
+  leaf_factor<R>(q, p, blockIdx.x, blockIdx.y, sh);
 }
 
 // Top row of the w x w triangle a leaf holds during panel p.
-__device__ __forceinline__ int top_row(int leaf, int c0, int N, int nb) {
-  return leaf == 0 ? c0 : leaf_start(leaf, N, nb);
+__device__ __forceinline__ int top_row(const QrArgs& q, int leaf, int c0) {
+  return leaf == 0 ? c0 : leaf_start(q, leaf);
 }
 
 // ---------------------------------------------------------------------------
 // Reduction tree: a node at stride s combines the triangles of the leaves
 // a, a + s, ..., a + (kArity - 1) s (those below nb), a = node * s * kArity;
-// the first child keeps R, the others receive the reflector parts.  Lane l
-// of wavefront v holds row (l & 31) of child 2 v + (l >> 5).  The node's WY
-// factor is stored in the slot of child 1, s (kArity i + 1), which no other
-// node at any stride shares (its odd part times a power of kArity).
+// the first child keeps R, the others receive the reflector parts.  The
+// node's WY factor is stored in the slot of child 1, s (kArity i + 1), which
+// no other node at any stride shares (its odd part times a power of kArity).
 // ---------------------------------------------------------------------------
 constexpr int kArity = 8;
-static_assert(kArity == 2 * 4, "two children per wavefront, four wavefronts");
 constexpr int kTrailN = 32;   // columns per workgroup in the block-reflector kernels
 static_assert(kTrailN == kPanel, "the leaf and tree block-reflector chunks share one launch width");
 
@@ -300,92 +371,99 @@ __device__ __forceinline__ int node_children(int a, int s, int nb) {
 
 // The workgroup factors the stacked triangles [R_0; R_1; ...]; the
 // reflectors are [e_j; v_j] with v_j in the upper triangles of the children
-// after the first (the node's trailing columns: qr_tree_wy).
-__global__ __launch_bounds__(256) void qr_tree_factor(QrArgs q, int p, int s) {
-  __shared__ double T[kPanel][kT], G[kPanel][kT];
-  __shared__ double tau_s[kPanel];
-  __shared__ PanelShare sh;
-  const int a = blockIdx.x * s * kArity;
-  const int mat = blockIdx.y;
-  const int N = q.N, k = q.k, nb = q.nb;
-  if (a + s >= nb) return;
-  const int nch = node_children(a, s, nb);
+// after the first (the node's trailing columns: tree_wy).  Register row r
+// holds rows g + 16 (r mod 2) of child r / 2.  The rows of child 0 below the
+// pivot are zero in the pivot column, so the panel code needs no mask for
+// them.
+template <int R>
+__device__ __forceinline__ void tree_factor(const QrArgs& q, int p, int s, int a, int nch, int mat,
+                                            PanelLds& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int k = q.k, nb = q.nb;
   const int c0 = p * kPanel, w = min(kPanel, k - c0);
   double* A = q.A[mat];
-  const int rr = lane & 31, h = 2 * wave + (lane >> 5);
-  const bool live = h < nch;
-  const long rowoff = live ? (long)(top_row(a + h * s, c0, N, nb) + rr) * k + c0 : 0;
-  double x[kPanel];
-#pragma unroll
-  for (int c = 0; c < kPanel; ++c) x[c] = (live && rr <= c && c < w) ? A[rowoff + c] : 0.0;
-  // the reflectors live in the children after the first; their rows below
-  // the triangles and absent children are held as zeros
-  block_panel_qr(x, w, lane, wave, [&](int) { return h > 0; }, tau_s, G, T, sh);
-  if (live) {
-#pragma unroll
-    for (int c = 0; c < kPanel; ++c)
-      if (rr <= c && c < w) A[rowoff + c] = x[c];
-  }
-  __syncthreads();
+  auto base = [&](int r) {   // register row r of the stack (the same in every lane)
+    return A + (long)(top_row(q, a + (r >> 1) * s, c0) + 16 * (r & 1)) * k + c0;
+  };
+  auto in = [&](int g, int r, int c) {
+    return (r >> 1) < nch && g + 16 * (r & 1) <= c && c < w;
+  };
+  panel_qr<R>(
+      w, lane, wave, sh,
+      [&](int g, int r, int c) { return in(g, r, c) ? base(r)[g * k + c] : 0.0; },
+      [&](int g, int r, int c, double v, double rv) {
+        if (in(g, r, c)) base(r)[g * k + c] = r < 2 ? rv : v;
+      });
   const long sl = slot(mat, p, a + s, nb, q.P);
   for (int idx = tid; idx < kPanel * kPanel; idx += 256)
-    q.Tn[sl * kPanel * kPanel + idx] = T[idx / kPanel][idx % kPanel];
+    q.Tn[sl * kPanel * kPanel + idx] = sh.T[idx / kPanel][idx % kPanel];
+}
+
+__device__ __forceinline__ void tree_factor_node(const QrArgs& q, int p, int s, int node, int mat,
+                                                 PanelLds& sh) {
+  const int a = node * s * kArity;
+  if (a + s >= q.nb) return;
+  const int nch = node_children(a, s, q.nb);
+  if (nch <= 2)
+    tree_factor<4>(q, p, s, a, nch, mat, sh);
+  else if (nch <= 4)
+    tree_factor<8>(q, p, s, a, nch, mat, sh);
+  else
+    tree_factor<2 * kArity>(q, p, s, a, nch, mat, sh);
 }
 
 // ---------------------------------------------------------------------------
-// Block reflectors applied to 32-column chunks, one chunk per workgroup
-// (blockIdx.z), so that the chunks of a leaf or node run side by side.
+// Block reflectors applied to 32-column chunks, one chunk per workgroup, so
+// that the chunks of a leaf or node run side by side.
 // FORM = false: the trailing update of the factorisation, A <- H^T A on the
-// columns [c0 + w, k) (H = I - V T V^T, so H^T uses T^T); FORM = true: the
-// Q formation, E <- H E on the columns [c0, k).
+// columns [c0 + w, k) (H = I - V T V^T, so H^T uses T^T; panel 0 takes the
+// columns from the caller's block); FORM = true: the Q formation, E <- H E
+// on the columns [c0, k) of the caller's block, E = [S; 0] at first.  Of E
+// in panel p, chunk 0 (its own columns) holds what this panel's earlier
+// factors have written and [S; 0] elsewhere, and the later chunks what the
+// later panels have written, which is everything but the rows
+// c0 .. c0 + w - 1 (zero until the first factor of this panel reaches them).
 // ---------------------------------------------------------------------------
+struct WyLds {
+  double Wp[4][kPanel][kT];
+  double T[kPanel][kT], W2[kPanel][kT];
+};
 
-// Node rows: W1 = C_0 + sum_h V_h^T C_h; W2 = op(T) W1; C_0 -= W2;
-// C_h -= V_h W2.  The children are stacked with V_0 = I, so that the node is
-// one product of the leaf kernel's form over kArity x 32 rows: wavefront w
-// owns children 2w and 2w + 1 (64 rows) and reads their rows of V and C
-// straight into the MFMA operand layout; rows r >= w of a child are zero.
-template <bool FORM>
-__global__ __launch_bounds__(256, 2) void qr_tree_wy(QrArgs q, int p, int s) {
-  constexpr int RW = kArity * kPanel / 4;   // rows per wavefront (two children)
-  constexpr int KS = RW / 4;
-  constexpr int RB = RW / 16;
-  static_assert(kPanel == 32 && kTrailN == kPanel && kArity == 8, "fragment shapes");
-  __shared__ double Wp[4][kPanel][kT];
-  __shared__ double T[kPanel][kT], W2[kPanel][kT];
-  __shared__ int tops[kArity];
-  const int a = blockIdx.x * s * kArity;
-  const int mat = blockIdx.y;
-  const int N = q.N, k = q.k, nb = q.nb;
-  if (a + s >= nb) return;
-  const int nch = node_children(a, s, nb);
+// S_cc from the diagonal of R.
+__device__ __forceinline__ double diag_sign(const double* A, int k, int c) {
+  return A[(long)c * k + c] < 0.0 ? -1.0 : 1.0;
+}
+
+// One chunk: C <- C - V op(T) (V^T C) for 4 RW rows, of which this wavefront
+// owns rows RW wave .. RW (wave + 1) - 1.  vval / cval(row, column) give the
+// operands (zeros outside), put(row, column, value) stores the result.  The
+// operands are read from global memory straight into the operand layout of
+// v_mfma_f64_16x16x4 (lane l: row l/16 of a 4-row k-step, column l%16 of a
+// 16-column block); the wavefronts' partial products V_w^T C_w meet in LDS,
+// every wavefront forms one 16 x 16 block of W2 = op(T) W1 from their sum,
+// and each then updates its own rows.  The second reading of V and C (in the
+// layouts of the update) and T are requested before the barriers that
+// separate the products, so one memory latency covers them; the update's
+// products accumulate onto C itself.  `ksteps` k-steps of this wavefront have
+// a C that is not known to be zero.  TREE: the rows are 32-row triangles
+// stacked, whose rows 16 .. 31 are zero in columns 0 .. 15 (those products
+// are left out).  50 KB of LDS lets three workgroups share a CU.
+//
+// Bound by latency (a chain of two memory round trips, 3 x 8 to 3 x 64
+// dependent f64 MFMAs and three barriers): on 8 blocks of 5184 x 160 a launch
+// forming Q took 20.2 us (nodes) and 38.6 us (leaves) with the second reading
+// issued where it was used and the zeros multiplied, 15.7 and 25.7 us in this
+// form.
+template <bool FORM, bool TREE, int RW, typename VF, typename CF, typename PF>
+__device__ __forceinline__ void wy_apply(const double* Tg, int rows, int ksteps, VF vval, CF cval,
+                                         PF put, WyLds& sh) {
+  constexpr int KS = RW / 4, RB = RW / 16;
+  static_assert(kPanel == 32 && kTrailN == kPanel && RW % 16 == 0, "fragment shapes");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c0 = p * kPanel, w = min(kPanel, k - c0);
-  const int cb = (FORM ? c0 : c0 + w) + blockIdx.z * kTrailN;
-  if (cb >= k) return;
-  const int nc = min(kTrailN, k - cb);
-  if (tid < kArity) tops[tid] = tid < nch ? top_row(a + tid * s, c0, N, nb) : 0;
-  const double* A = q.A[mat];
-  double* M = FORM ? q.E[mat] : q.A[mat];
-  const long sl = slot(mat, p, a + s, nb, q.P);
-  for (int idx = tid; idx < kPanel * kPanel; idx += 256) {
-    const int i = idx / kPanel, l = idx % kPanel;
-    T[i][l] = (i < w && l < w) ? q.Tn[sl * kPanel * kPanel + idx] : 0.0;
-  }
-  __syncthreads();
-  // stacked row u = 32 h + r of child h
-  auto vval = [&](int u, int c) -> double {
-    const int h = u >> 5, r = u & 31;
-    if (h >= nch || r >= w || c >= w) return 0.0;
-    if (h == 0) return r == c ? 1.0 : 0.0;
-    return r <= c ? A[(long)(tops[h] + r) * k + c0 + c] : 0.0;
-  };
-  auto cval = [&](int u, int c) -> double {
-    const int h = u >> 5, r = u & 31;
-    return (h < nch && r < w && c < nc) ? M[(long)(tops[h] + r) * k + cb + c] : 0.0;
-  };
   const int r0 = RW * wave, li = lane & 15, lk = lane >> 4;
+  double tg[kPanel * kPanel / 256];
+#pragma unroll
+  for (int i = 0; i < kPanel * kPanel / 256; ++i) tg[i] = Tg[tid + 256 * i];
   {
     double vf[KS][2], cf[KS][2];
 #pragma unroll
@@ -393,134 +471,45 @@ __global__ __launch_bounds__(256, 2) void qr_tree_wy(QrArgs q, int p, int s) {
       const int rr = r0 + 4 * t + lk;
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        vf[t][i] = vval(rr, 16 * i + li);
-        cf[t][i] = cval(rr, 16 * i + li);
+        vf[t][i] = t < ksteps && !(TREE && i == 0 && (t & 4)) ? vval(rr, 16 * i + li) : 0.0;
+        cf[t][i] = t < ksteps ? cval(rr, 16 * i + li) : 0.0;
       }
     }
+#pragma unroll
+    for (int i = 0; i < kPanel * kPanel / 256; ++i)
+      sh.T[(tid >> 5) + 8 * i][tid & 31] = tg[i];
     v4d acc[2][2] = {{{0, 0, 0, 0}, {0, 0, 0, 0}}, {{0, 0, 0, 0}, {0, 0, 0, 0}}};
 #pragma unroll
     for (int t = 0; t < KS; ++t)
+      if (t < ksteps) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(vf[t][i], cf[t][j], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < 2; ++j)
+            if (!(TREE && i == 0 && (t & 4)))
+              acc[i][j] =
+                  __builtin_amdgcn_mfma_f64_16x16x4f64(vf[t][i], cf[t][j], acc[i][j], 0, 0, 0);
+      }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) Wp[wave][16 * i + lk + 4 * r][16 * j + li] = acc[i][j][r];
+        for (int r = 0; r < 4; ++r) sh.Wp[wave][16 * i + lk + 4 * r][16 * j + li] = acc[i][j][r];
   }
-  __syncthreads();
-  {
-    const int bi = wave >> 1, bj = wave & 1;
-    v4d a2 = {0, 0, 0, 0};
-#pragma unroll
-    for (int t = 0; t < kPanel / 4; ++t) {
-      const int l = 4 * t + lk, i = 16 * bi + li, c = 16 * bj + li;
-      const double tv = FORM ? T[i][l] : T[l][i];
-      const double w1 = (Wp[0][l][c] + Wp[1][l][c]) + (Wp[2][l][c] + Wp[3][l][c]);
-      a2 = __builtin_amdgcn_mfma_f64_16x16x4f64(tv, w1, a2, 0, 0, 0);
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) W2[16 * bi + lk + 4 * r][16 * bj + li] = a2[r];
-  }
-  __syncthreads();
+  // the update's operands
+  double v2[RB][kPanel / 4];
+  v4d u[RB][2];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int rr0 = r0 + 16 * rb;
-    if ((rr0 >> 5) >= nch) break;
-    v4d u[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
 #pragma unroll
-    for (int t = 0; t < kPanel / 4; ++t) {
-      const double av = vval(rr0 + li, 4 * t + lk);
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        u[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, W2[4 * t + lk][16 * j + li], u[j], 0, 0, 0);
-    }
+    for (int t = 0; t < kPanel / 4; ++t)
+      v2[rb][t] = !(TREE && (rb & 1) && t < 4) ? vval(rr0 + li, 4 * t + lk) : 0.0;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int uu = rr0 + lk + 4 * r, col = 16 * j + li;
-        const int h = uu >> 5, rw = uu & 31;
-        if (h < nch && rw < w && col < nc) {
-          double* pc = M + (long)(tops[h] + rw) * k + cb + col;
-          *pc = *pc - u[j][r];
-        }
-      }
-  }
-}
-
-// Leaf rows: C -= V op(T) (V^T C), V unit lower-trapezoidal (implicit ones,
-// zeros above).  Wavefront w owns rows 48 w .. 48 w + 47 of the leaf and
-// reads its rows of V and C from global memory straight into the operand
-// layout of v_mfma_f64_16x16x4 (lane l: row l/16 of a 4-row k-step, column
-// l%16 of a 16-column block), so neither block is staged in LDS: the
-// wavefronts' partial products V_w^T C_w meet in LDS, every wavefront forms
-// one 16 x 16 block of W2 = op(T) W1 from their sum, and each then updates
-// its own rows, C_w -= V_w W2.  About 50 KB of LDS lets several workgroups
-// share a CU.
-template <bool FORM>
-__global__ __launch_bounds__(256, 2) void qr_leaf_wy(QrArgs q, int p) {
-  constexpr int RW = kLeafRows / 4;   // rows per wavefront
-  constexpr int KS = RW / 4;          // k-steps over a wavefront's rows
-  constexpr int RB = RW / 16;         // 16-row blocks of a wavefront's rows
-  static_assert(kPanel == 32 && kTrailN == kPanel && RW % 16 == 0, "fragment shapes");
-  __shared__ double Wp[4][kPanel][kT];
-  __shared__ double T[kPanel][kT], W2[kPanel][kT];
-  const int leaf = blockIdx.x, mat = blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int N = q.N, k = q.k, nb = q.nb;
-  const int c0 = p * kPanel, w = min(kPanel, k - c0);
-  const int cb = (FORM ? c0 : c0 + w) + blockIdx.z * kPanel;
-  if (cb >= k) return;
-  const int nc = min(kPanel, k - cb);
-  const int s = leaf_start(leaf, N, nb), e = leaf_start(leaf + 1, N, nb);
-  const int a0 = (leaf == 0) ? c0 : s;
-  const int m = e - a0;
-  const double* A = q.A[mat];
-  double* M = FORM ? q.E[mat] : q.A[mat];
-  const long sl = slot(mat, p, leaf, nb, q.P);
-  auto vval = [&](int r, int c) -> double {
-    if (r >= m || c >= w) return 0.0;
-    return r > c ? A[(long)(a0 + r) * k + c0 + c] : (r == c ? 1.0 : 0.0);
-  };
-  auto cval = [&](int r, int c) -> double {
-    return (r < m && c < nc) ? M[(long)(a0 + r) * k + cb + c] : 0.0;
-  };
-  // T (w x w; entries outside it are never read)
-  for (int idx = tid; idx < kPanel * kPanel; idx += 256) {
-    const int i = idx / kPanel, l = idx % kPanel;
-    T[i][l] = (i < w && l < w) ? q.Tl[sl * kPanel * kPanel + idx] : 0.0;
-  }
-  const int r0 = RW * wave, li = lane & 15, lk = lane >> 4;
-  {
-    double vf[KS][2], cf[KS][2];
-#pragma unroll
-    for (int t = 0; t < KS; ++t) {
-      const int rr = r0 + 4 * t + lk;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        vf[t][i] = vval(rr, 16 * i + li);
-        cf[t][i] = cval(rr, 16 * i + li);
-      }
-    }
-    v4d acc[2][2] = {{{0, 0, 0, 0}, {0, 0, 0, 0}}, {{0, 0, 0, 0}, {0, 0, 0, 0}}};
-#pragma unroll
-    for (int t = 0; t < KS; ++t)
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(vf[t][i], cf[t][j], acc[i][j], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) Wp[wave][16 * i + lk + 4 * r][16 * j + li] = acc[i][j][r];
+      for (int r = 0; r < 4; ++r) u[rb][j][r] = cval(rr0 + lk + 4 * r, 16 * j + li);
   }
   __syncthreads();
   {
@@ -530,72 +519,171 @@ __global__ __launch_bounds__(256, 2) void qr_leaf_wy(QrArgs q, int p) {
 #pragma unroll
     for (int t = 0; t < kPanel / 4; ++t) {
       const int l = 4 * t + lk, i = 16 * bi + li, c = 16 * bj + li;
-      const double tv = FORM ? T[i][l] : T[l][i];
-      const double w1 = (Wp[0][l][c] + Wp[1][l][c]) + (Wp[2][l][c] + Wp[3][l][c]);
+      const double tv = FORM ? sh.T[i][l] : sh.T[l][i];
+      const double w1 = (sh.Wp[0][l][c] + sh.Wp[1][l][c]) + (sh.Wp[2][l][c] + sh.Wp[3][l][c]);
       a2 = __builtin_amdgcn_mfma_f64_16x16x4f64(tv, w1, a2, 0, 0, 0);
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) W2[16 * bi + lk + 4 * r][16 * bj + li] = a2[r];
+    for (int r = 0; r < 4; ++r) sh.W2[16 * bi + lk + 4 * r][16 * bj + li] = a2[r];
   }
   __syncthreads();
+  double w2[kPanel / 4][2];
+#pragma unroll
+  for (int t = 0; t < kPanel / 4; ++t)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) w2[t][j] = sh.W2[4 * t + lk][16 * j + li];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int rr0 = r0 + 16 * rb;
-    if (rr0 >= m) break;
-    v4d u[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+    if (rr0 < rows) {
 #pragma unroll
-    for (int t = 0; t < kPanel / 4; ++t) {
-      const double av = vval(rr0 + li, 4 * t + lk);
+      for (int t = 0; t < kPanel / 4; ++t)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          if (!(TREE && (rb & 1) && t < 4))
+            u[rb][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-v2[rb][t], w2[t][j], u[rb][j], 0, 0, 0);
 #pragma unroll
       for (int j = 0; j < 2; ++j)
-        u[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, W2[4 * t + lk][16 * j + li], u[j], 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) put(rr0 + lk + 4 * r, 16 * j + li, u[rb][j][r]);
     }
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = rr0 + lk + 4 * r, col = 16 * j + li;
-        if (row < m && col < nc) {
-          double* pc = M + (long)(a0 + row) * k + cb + col;
-          *pc = *pc - u[j][r];
-        }
-      }
   }
 }
 
-// ---------------------------------------------------------------------------
-// Q formation
-// ---------------------------------------------------------------------------
-__global__ void qr_init_e(QrArgs q) {
-  const int mat = blockIdx.y;
-  const long total = (long)q.N * q.k;
-  double* E = q.E[mat];
-  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < total;
-       i += (long)gridDim.x * blockDim.x) {
-    const long r = i / q.k, c = i % q.k;
-    E[i] = (r == c) ? 1.0 : 0.0;
-  }
-}
-
-// sgn[mat][c] = sign(R_cc) (R_cc read from the factored block).  A separate
-// pass, because the destination of Q may be the factored block itself.
-__global__ void qr_diag_sign(QrArgs q) {
-  const int mat = blockIdx.y;
+// Node rows, with V_0 = I: row 32 h + r of the stack is row r of child h, and
+// wavefront w owns children 2w and 2w + 1; rows r >= w of a child are zero.
+template <bool FORM>
+__device__ __forceinline__ void tree_wy(const QrArgs& q, int p, int s, int node, int mat, int chunk,
+                                        bool top, WyLds& sh) {
+  constexpr int RW = kArity * kPanel / 4;
+  static_assert(RW == 2 * kPanel, "two children per wavefront");
+  const int a = node * s * kArity;
+  const int k = q.k, nb = q.nb;
+  if (a + s >= nb) return;
+  const int nch = node_children(a, s, nb);
+  const int c0 = p * kPanel, w = min(kPanel, k - c0);
+  const int cb = (FORM ? c0 : c0 + w) + chunk * kTrailN;
+  if (cb >= k) return;
+  const int nc = min(kTrailN, k - cb);
   const double* A = q.A[mat];
-  for (int c = threadIdx.x; c < q.k; c += blockDim.x)
-    q.sgn[(long)mat * q.k + c] = A[(long)c * q.k + c] < 0.0 ? -1.0 : 1.0;
+  double* M = FORM ? q.W[mat] : q.A[mat];
+  const int wave = threadIdx.x >> 6;
+  // the wavefront's two children
+  const long t0 = (long)top_row(q, a + 2 * wave * s, c0) * k;
+  const long t1 = (long)top_row(q, a + (2 * wave + 1) * s, c0) * k;
+  auto vval = [&](int u, int c) -> double {
+    const int h = u >> 5, r = u & 31;
+    if (h >= nch || r >= w || c >= w) return 0.0;
+    if (h == 0) return r == c ? 1.0 : 0.0;
+    return r <= c ? A[(h & 1 ? t1 : t0) + r * k + c0 + c] : 0.0;
+  };
+  auto cval = [&](int u, int c) -> double {
+    const int h = u >> 5, r = u & 31;
+    if (h >= nch || r >= w || c >= nc) return 0.0;
+    if (FORM) {
+      // child 0 was a child of the level above, except at the top (leaf 0);
+      // the other children's rows are first reached here
+      if (h == 0 && top) return chunk == 0 && r == c ? diag_sign(A, k, c0 + c) : 0.0;
+      if (h > 0 && chunk == 0) return 0.0;
+    }
+    return M[(h & 1 ? t1 : t0) + r * k + cb + c];
+  };
+  auto put = [&](int u, int c, double v) {
+    const int h = u >> 5, r = u & 31;
+    if (h < nch && r < w && c < nc) M[(h & 1 ? t1 : t0) + r * k + cb + c] = v;
+  };
+  const int ksteps = FORM && chunk == 0 ? (wave == 0 ? kPanel / 4 : 0)
+                                        : kPanel / 4 * max(0, min(2, nch - 2 * wave));
+  wy_apply<FORM, true, RW>(q.Tn + slot(mat, p, a + s, nb, q.P) * kPanel * kPanel, kPanel * nch,
+                           ksteps, vval, cval, put, sh);
 }
 
-// Q_out[:, c] = sgn[c] * E[:, c]
-__global__ void qr_sign_copy(QrArgs q) {
-  const int mat = blockIdx.y;
-  const long total = (long)q.N * q.k;
-  const double* E = q.E[mat];
-  const double* sg = q.sgn + (long)mat * q.k;
-  double* O = q.O[mat];
-  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < total;
-       i += (long)gridDim.x * blockDim.x)
-    O[i] = sg[i % q.k] * E[i];
+// Leaf rows: V is unit lower-trapezoidal (implicit ones, zeros above).
+template <bool FORM>
+__device__ __forceinline__ void leaf_wy(const QrArgs& q, int p, int leaf, int mat, int chunk,
+                                        WyLds& sh) {
+  constexpr int RW = kLeafRows / 4;
+  const int k = q.k, nb = q.nb;
+  const int c0 = p * kPanel, w = min(kPanel, k - c0);
+  const int cb = (FORM ? c0 : c0 + w) + chunk * kPanel;
+  if (cb >= k) return;
+  const int nc = min(kPanel, k - cb);
+  const int s = leaf_start(q, leaf), e = leaf_start(q, leaf + 1);
+  const int a0 = (leaf == 0) ? c0 : s;
+  const int m = e - a0;
+  const double* A = q.A[mat];
+  const double* V = A + (long)a0 * k + c0;
+  const double* Cin = (FORM || p == 0 ? q.W[mat] : q.A[mat]) + (long)a0 * k + cb;
+  double* C = (FORM ? q.W[mat] : q.A[mat]) + (long)a0 * k + cb;
+  auto vval = [&](int r, int c) -> double {
+    if (r >= m || c >= w) return 0.0;
+    return r > c ? V[r * k + c] : (r == c ? 1.0 : 0.0);
+  };
+  auto cval = [&](int r, int c) -> double {
+    if (r >= m || c >= nc) return 0.0;
+    if (FORM) {
+      // the tree has written the top rows; without one they are those of
+      // [S; 0].  The rows below are first reached here in chunk 0
+      if (nb == 1 && r < w) return chunk == 0 && r == c ? diag_sign(A, k, c0 + c) : 0.0;
+      if (chunk == 0 && r >= w) return 0.0;
+    }
+    return Cin[r * k + c];
+  };
+  auto put = [&](int r, int c, double v) {
+    if (r < m && c < nc) C[r * k + c] = v;
+  };
+  const int r0 = RW * (threadIdx.x >> 6);
+  const int live = FORM && chunk == 0 ? w : m;   // rows of C that may be non-zero
+  wy_apply<FORM, false, RW>(q.Tl + slot(mat, p, leaf, nb, q.P) * kPanel * kPanel, m,
+                            max(0, min(RW / 4, (live - r0 + 3) >> 2)), vval, cval, put, sh);
+}
+
+// ---------------------------------------------------------------------------
+// launches
+// ---------------------------------------------------------------------------
+union StageLds {
+  PanelLds panel;
+  WyLds wy;
+};
+
+// After the leaf factors of panel p: the first tree level's factors (`next`
+// nodes per matrix; the first blocks, since the next launch waits for their
+// 32 serial steps) beside the leaves' trailing columns.
+__global__ __launch_bounds__(256, 2) void qr_leaf_trail(QrArgs q, int p, int trail, int next) {
+  __shared__ StageLds sh;
+  int x = blockIdx.x;
+  if (x < next * q.count) {
+    tree_factor_node(q, p, 1, x % next, x / next, sh.panel);
+    return;
+  }
+  x -= next * q.count;
+  const int per = q.nb * trail;
+  leaf_wy<false>(q, p, x % per / trail, x / per, x % trail, sh.wy);
+}
+
+// After the tree factors at stride s: the next level's factors beside those
+// nodes' trailing columns.
+__global__ __launch_bounds__(256, 2) void qr_tree_trail(QrArgs q, int p, int s, int nodes,
+                                                        int trail, int next) {
+  __shared__ StageLds sh;
+  int x = blockIdx.x;
+  if (x < next * q.count) {
+    tree_factor_node(q, p, s * kArity, x % next, x / next, sh.panel);
+    return;
+  }
+  x -= next * q.count;
+  const int per = nodes * trail;
+  tree_wy<false>(q, p, s, x % per / trail, x / per, x % trail, false, sh.wy);
+}
+
+__global__ __launch_bounds__(256, 2) void qr_tree_form(QrArgs q, int p, int s, int top) {
+  __shared__ WyLds sh;
+  tree_wy<true>(q, p, s, blockIdx.x, blockIdx.y, blockIdx.z, top != 0, sh);
+}
+
+__global__ __launch_bounds__(256, 2) void qr_leaf_form(QrArgs q, int p) {
+  __shared__ WyLds sh;
+  leaf_wy<true>(q, p, blockIdx.x, blockIdx.y, blockIdx.z, sh);
 }
 
 QrPlan make_plan(int N, int k) {
@@ -626,8 +714,7 @@ bool qr_plan_ok(int N, int k) {
 size_t qr_workspace_bytes(int count, int N, int k) {
   const QrPlan pl = make_plan(N, k);
   const size_t slots = (size_t)count * pl.P * pl.nb;
-  const size_t n = slots * kPanel + 2 * slots * kPanel * kPanel + (size_t)count * N * k +
-                   (size_t)count * k;
+  const size_t n = 2 * slots * kPanel * kPanel + (size_t)count * N * k;
   return n * sizeof(double);
 }
 
@@ -649,46 +736,47 @@ int launch_qr(int count, double* const* W, int N, int k, void* ws, hipStream_t s
   q.nb = pl.nb;
   q.P = pl.P;
   const size_t slots = (size_t)count * pl.P * pl.nb;
-  double* base = (double*)ws;
-  q.tau = base;
-  q.Tl = q.tau + slots * kPanel;
+  q.Tl = (double*)ws;
   q.Tn = q.Tl + slots * kPanel * kPanel;
-  double* e = q.Tn + slots * kPanel * kPanel;
+  double* work = q.Tn + slots * kPanel * kPanel;
   for (int i = 0; i < count; ++i) {
-    q.A[i] = W[i];
-    q.E[i] = e + (size_t)i * N * k;
-    q.O[i] = W[i];
+    q.W[i] = W[i];
+    q.A[i] = work + (size_t)i * N * k;
   }
-  q.sgn = e + (size_t)count * N * k;
+  q.rows = N / pl.nb;
+  q.extra = N % pl.nb;
+  const int leaf_rows = q.rows + (q.extra > 0);
+  auto nodes_at = [&](int st) { return (pl.nb + st * kArity - 1) / (st * kArity); };
 
-  // factorisation: per panel the leaves, then the tree levels; each factor
-  // launch is followed by the update of the trailing columns it leaves
   for (int p = 0; p < pl.P; ++p) {
     const int c0 = p * kPanel, w = std::min(kPanel, k - c0);
     const int trail = (k - c0 - w + kTrailN - 1) / kTrailN;
-    qr_leaf_factor<<<dim3(pl.nb, count), 256, 0, s>>>(q, p);
-    if (trail) qr_leaf_wy<false><<<dim3(pl.nb, count, trail), 256, 0, s>>>(q, p);
+    const dim3 leaves(pl.nb, count);
+    if (leaf_rows <= 64)
+      qr_leaf_factor<4><<<leaves, 256, 0, s>>>(q, p);
+    else if (leaf_rows <= 128)
+      qr_leaf_factor<8><<<leaves, 256, 0, s>>>(q, p);
+    else
+      qr_leaf_factor<12><<<leaves, 256, 0, s>>>(q, p);
+    int next = pl.depth > 0 ? nodes_at(1) : 0;   // nodes of the next level to factor
+    if (pl.nb * trail + next)
+      qr_leaf_trail<<<count * (pl.nb * trail + next), 256, 0, s>>>(q, p, trail, next);
     for (int L = 0, st = 1; L < pl.depth; ++L, st *= kArity) {
-      const int nodes = (pl.nb + st * kArity - 1) / (st * kArity);
-      qr_tree_factor<<<dim3(nodes, count), 256, 0, s>>>(q, p, st);
-      if (trail) qr_tree_wy<false><<<dim3(nodes, count, trail), 256, 0, s>>>(q, p, st);
+      const int nodes = next;
+      next = L + 1 < pl.depth ? nodes_at(st * kArity) : 0;
+      if (nodes * trail + next)
+        qr_tree_trail<<<count * (nodes * trail + next), 256, 0, s>>>(q, p, st, nodes, trail, next);
     }
   }
-  const long total = (long)N * k;
-  const int blocks = (int)std::min<long>(1024, (total + 255) / 256);
-  qr_init_e<<<dim3(blocks, count), 256, 0, s>>>(q);
   for (int p = pl.P - 1; p >= 0; --p) {
     const int chunks = (k - p * kPanel + kTrailN - 1) / kTrailN;
     for (int L = pl.depth - 1; L >= 0; --L) {
       int st = 1;
       for (int i = 0; i < L; ++i) st *= kArity;
-      const int nodes = (pl.nb + st * kArity - 1) / (st * kArity);
-      qr_tree_wy<true><<<dim3(nodes, count, chunks), 256, 0, s>>>(q, p, st);
+      qr_tree_form<<<dim3(nodes_at(st), count, chunks), 256, 0, s>>>(q, p, st, L == pl.depth - 1);
     }
-    qr_leaf_wy<true><<<dim3(pl.nb, count, chunks), 256, 0, s>>>(q, p);
+    qr_leaf_form<<<dim3(pl.nb, count, chunks), 256, 0, s>>>(q, p);
   }
-  qr_diag_sign<<<dim3(1, count), 256, 0, s>>>(q);
-  qr_sign_copy<<<dim3(blocks, count), 256, 0, s>>>(q);
   CTM_HIP_TRY(hipGetLastError());
   return 0;
 }
