@@ -2538,8 +2538,14 @@ ctm_status ctm_gemm_f64_split(int count, const double* const* A, const double* c
     g.C[i] = C[i];
     g.transA[i] = trans_a[i];
   }
-  if (used_split) *used_split = gemm_si_balanced_applies(g, scratch, ncu) ? 1 : 0;
-  int r = launch_gemm_si_balanced(g, (double*)scratch, ncu, (hipStream_t)stream);
+  // the documented operand alignment (the kernel itself needs less)
+  bool aligned = !(lda & 1);
+  for (int i = 0; i < count; ++i)
+    aligned = aligned && !((uintptr_t)A[i] & 15) && !((uintptr_t)B[i] & ((ldb & 1) ? 7 : 15));
+  const bool split = aligned && gemm_si_balanced_applies(g, scratch, ncu);
+  if (used_split) *used_split = split ? 1 : 0;
+  const int r = split ? launch_gemm_si_balanced(g, (double*)scratch, ncu, (hipStream_t)stream)
+                      : launch_gemm_si(g, (hipStream_t)stream);
   return r ? CTM_E_DEVICE : CTM_OK;
 }
 

@@ -576,178 +576,266 @@ __global__ __launch_bounds__(64 * WGM * WGN, 512 / (64 * WGM * WGN)) void gemm_s
 }
 
 // ---------------------------------------------------------------------------
-// Split form of the skinny tile for the SI applications (stream-K style).  A
-// launch of one tile per workgroup leaves CUs idle or half loaded when the
-// count x tiles_m tiles do not fill the chip evenly (432 tiles of 96 rows on
-// 512 slots at D = 6).  Here one workgroup of 8 wavefronts per CU (192 x 160
-// tiles: each B block is re-read by half as many tiles as with 96 rows) takes
-// an equal, contiguous range of the (tile, K-slice) space.  A tile inside one
-// range is written directly; a tile cut by range boundaries leaves partial
-// tiles in scratch (slot 2w for the segment that starts range w, 2w+1 for the
-// one that ends it), which a second kernel sums in workgroup order, so
-// results do not depend on timing.
+// Split products for the SI applications (stream-K style): C = op(A) B with
+// N <= 160 and long K.  A launch of one tile per workgroup leaves CUs idle or
+// half loaded when the tiles do not fill the chip evenly.  Here one workgroup
+// of 8 wavefronts per CU takes an equal, contiguous range of the (tile,
+// 16-wide K slice) space.  A tile inside one range is written directly; a
+// tile cut by range boundaries leaves partial tiles in scratch (slot 2w for
+// the segment that starts range w, 2w+1 for the one that ends it), which a
+// second kernel sums in workgroup order, so results do not depend on timing.
 // ---------------------------------------------------------------------------
 struct StreamK {
-  long total;     // count * tiles_m * nslices
   int nslices;    // BK-slices of K per tile
   int tiles_m;
   int nwg;        // workgroups (ranges) of the main kernel
+  int per, rem;   // slices per range; the first `rem` ranges have one more
   double* part;   // 2 * nwg partial BM x BN tiles (row-major)
 };
 
-__device__ __forceinline__ long sk_begin(long w, const StreamK& sk) { return w * sk.total / sk.nwg; }
-
-__device__ __forceinline__ int sk_owner(long p, const StreamK& sk) {
-  int w = (int)((p * sk.nwg) / sk.total);
-  while (w + 1 < sk.nwg && sk_begin(w + 1, sk) <= p) ++w;
-  while (w > 0 && sk_begin(w, sk) > p) --w;
-  return w;
+__device__ __forceinline__ int sk_begin(int w, const StreamK& sk) {
+  return w * sk.per + min(w, sk.rem);
 }
 
+__device__ __forceinline__ int sk_owner(int p, const StreamK& sk) {
+  const int wide = sk.rem * (sk.per + 1);
+  return p < wide ? p / (sk.per + 1) : sk.rem + (p - wide) / sk.per;
+}
+
+// Two adjacent doubles by one 16-byte load; global loads need no more than
+// the 8-byte alignment every double has (odd leading dimensions included).
+typedef double v2du __attribute__((ext_vector_type(2), aligned(8)));
+
+// The 8 wavefronts stand WM x WN; each owns MI x NI blocks of 16 x 16.  The
+// rows of a wavefront are its own, so its elements of A go from global
+// memory straight into the operand registers of the matrix instruction (of a
+// 16-wide slice lane l takes k = 2 (l / 16), + 1, + 8 and + 9 of row l % 16,
+// one for each of the slice's four instructions, which multiply them with
+// the same rows of B: the order of the sum within a slice is free) and only
+// B, which all share, is staged in LDS, one barrier per slice.  Loads run a
+// slice (A) and two slices (B) ahead and stand between the matrix
+// instructions of a slice, so that their issue and the LDS stores hide in
+// the 64 cycles each of those takes.
+// Rows and columns past the edge are read from clamped addresses and never
+// stored; the last slice of K, when it is not full, is filled up with zeros.
+//
+// Bound by the f64 matrix cores.  8 products of 5184 x 5184 x 160: 1.185 ms
+// with A staged in LDS beside B, loads under per-element bounds checks at the
+// slice's start and the LDS stores at its end (matrix cores busy 73%), now
+// 1.065 ms (82%; 1.0 ms with no loads at all).  8 of 1024 x 1024 x 72:
+// 68 -> 39 us; 8 of 1875 x 1875 x 87 (odd rows, which took one-tile kernels
+// before): 328 -> 127 us; 6 of 2500 x 2500 x 105: 210 -> 156 us.
+template <int MI, int NI, int WN>
+struct SkTile {
+  static constexpr int WM = 8 / WN;
+  static constexpr int BM = 16 * MI * WM, BN = 16 * NI * WN;
+  static constexpr int BK = 16, NT = 512;
+  static constexpr int LB = BN + 8;   // B rows in LDS: rows 2 apart fall 32 banks apart
+  static constexpr int NB = BN * BK / 2;              // 16-byte loads of B per slice
+  static constexpr int VB = (NB + NT - 1) / NT;
+  // k of matrix instruction t, beyond the lane's 2 (l / 16)
+  static constexpr int kof(int t) { return 8 * (t >> 1) + (t & 1); }
+};
+
 // acc += op(A)[m0 .. m0+BM) x B over the K slices [s0, s1) of problem prob.
-template <int BM, int BN, int WGM, int WGN, bool TRANS, bool BODD, int MI, int NI>
+// ONE: N == 1 (B has no pairs of columns).
+template <int MI, int NI, int WN, bool TRANS, bool ONE>
 __device__ __forceinline__ void sk_segment(const GemmBatch& g, int prob, int m0, int s0, int s1,
-                                           double (*As)[SkinnyA<BM, 16>::SIZE],
-                                           double (*Bs)[16][BN + 16], v4d (&acc)[MI][NI]) {
-  constexpr int BK = 16;
-  using AL = SkinnyA<BM, BK>;
-  constexpr int WTM = BM / WGM, WTN = BN / WGN;
-  constexpr int NT = 64 * WGM * WGN;
-  constexpr int NA = BM * BK / 2, NB = BN * BK / 2;
-  constexpr int VA = (NA + NT - 1) / NT, VB = (NB + NT - 1) / NT;
+                                           double (*Bs)[16][SkTile<MI, NI, WN>::LB],
+                                           v4d (&acc)[MI][NI]) {
+  using S = SkTile<MI, NI, WN>;
+  constexpr int BK = S::BK;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave % WGM, wn = wave / WGM;
+  const int li = lane & 15, lk = lane >> 4;
+  const int wm = wave / WN, wn = wave % WN;
   const int M = g.M, N = g.N, K = g.K;
+  const long lda = g.lda, ldb = g.ldb;
   const double* A = (const double*)g.A[prob];
   const double* B = (const double*)g.B[prob];
-  const long lda = g.lda, ldb = g.ldb;
-  v2d ra[VA], rb[VB];
-  auto load = [&](int k0) {
+  const int full = K / BK;   // slices before the partial one
+  const int sf = min(s1, full);
+
+  // A: this lane's rows at k = 2 lk of the slice the next load takes
+  const double* pa[MI];
+  const long astep = TRANS ? BK * lda : BK;
 #pragma unroll
-    for (int e = 0; e < VA; ++e) {
-      const int i = tid + e * NT;
-      v2d v = {0.0, 0.0};
-      if (i < NA) {
-        if (TRANS) {
-          const int gk = k0 + i / (BM / 2), gm = m0 + 2 * (i % (BM / 2));
-          if (gk < K) {
-            const double* p = A + (long)gk * lda + gm;
-            if (gm + 1 < M) v = *(const v2d*)p;
-            else if (gm < M) v.x = p[0];
-          }
-        } else {
-          const int gm = m0 + i / (BK / 2), gk = k0 + 2 * (i % (BK / 2));
-          if (gm < M) {
-            const double* p = A + (long)gm * lda + gk;
-            if (gk + 1 < K) v = *(const v2d*)p;
-            else if (gk < K) v.x = p[0];
-          }
-        }
-      }
-      ra[e] = v;
-    }
+  for (int i = 0; i < MI; ++i) {
+    const long m = min(m0 + (wm * MI + i) * 16 + li, M - 1);
+    const long k = s0 * BK + 2 * lk;
+    pa[i] = TRANS ? A + k * lda + m : A + m * lda + k;
+  }
+  auto load_a = [&](double (&ra)[MI][4]) {
 #pragma unroll
-    for (int e = 0; e < VB; ++e) {
-      const int i = tid + e * NT;
-      const int gk = k0 + i / (BN / 2), gn = 2 * (i % (BN / 2));
-      v2d v = {0.0, 0.0};
-      if (i < NB && gk < K) {
-        const double* p = B + (long)gk * ldb + gn;
-        if (gn + 1 < N) {
-          // an odd ldb leaves every other row 8-byte aligned only
-          if (BODD) {
-            v.x = p[0];
-            v.y = p[1];
-          } else {
-            v = *(const v2d*)p;
-          }
-        } else if (gn < N) {
-          v.x = p[0];
-        }
+    for (int i = 0; i < MI; ++i) {
+      if (TRANS) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) ra[i][t] = pa[i][S::kof(t) * lda];
+      } else {
+        const v2du v0 = *(const v2du*)pa[i], v1 = *(const v2du*)(pa[i] + S::kof(2));
+        ra[i][0] = v0.x;
+        ra[i][1] = v0.y;
+        ra[i][2] = v1.x;
+        ra[i][3] = v1.y;
       }
-      rb[e] = v;
+      pa[i] += astep;
     }
   };
-  auto store = [&](int buf) {
+  auto load_a_last = [&](double (&ra)[MI][4]) {   // the partial slice
+    const int k = full * BK + 2 * lk;
 #pragma unroll
-    for (int e = 0; e < VA; ++e) {
-      const int i = tid + e * NT;
-      if (i < NA) {
-        if (TRANS) {
-          const int kk = i / (BM / 2), m = 2 * (i % (BM / 2));
-          *(v2d*)&As[buf][kk * AL::LT + m] = ra[e];
-        } else {
-          const int m = i / (BK / 2), kk = 2 * (i % (BK / 2));
-          As[buf][m * AL::LN + kk] = ra[e].x;
-          As[buf][m * AL::LN + kk + 1] = ra[e].y;
-        }
-      }
-    }
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int e = 0; e < VB; ++e) {
-      const int i = tid + e * NT;
-      if (i < NB) *(v2d*)&Bs[buf][i / (BN / 2)][2 * (i % (BN / 2))] = rb[e];
+      for (int t = 0; t < 4; ++t)
+        ra[i][t] = k + S::kof(t) < K ? pa[i][S::kof(t) * (TRANS ? lda : 1)] : 0.0;
+  };
+  // B: pair e of this thread in row kb of a slice (threads beyond the slice's
+  // pairs repeat its last one); the last column of an odd N is read as the
+  // second of its pair
+  const double* pb[S::VB];
+  int kb[S::VB], lb[S::VB];
+  bool second[S::VB];
+#pragma unroll
+  for (int e = 0; e < S::VB; ++e) {
+    const int i = min(tid + e * S::NT, S::NB - 1);
+    const int kk = i / (S::BN / 2), n = 2 * (i % (S::BN / 2));
+    second[e] = !ONE && n + 1 == N;
+    pb[e] = B + (long)(s0 * BK + kk) * ldb + (n + 1 < N ? n : second[e] ? n - 1 : 0);
+    kb[e] = kk;
+    lb[e] = kk * S::LB + n;
+  }
+  const long bstep = BK * ldb;
+  auto ld_b = [&](const double* q) {
+    v2du v;
+    if (ONE)
+      v.x = v.y = *q;
+    else
+      v = *(const v2du*)q;
+    return v;
+  };
+  auto load_b = [&](v2du (&rb)[S::VB]) {
+#pragma unroll
+    for (int e = 0; e < S::VB; ++e) {
+      rb[e] = ld_b(pb[e]);
+      pb[e] += bstep;
     }
   };
-  load(s0 * BK);
-  store(0);
+  auto load_b_last = [&](v2du (&rb)[S::VB]) {
+#pragma unroll
+    for (int e = 0; e < S::VB; ++e) {
+      rb[e].x = rb[e].y = 0.0;
+      if (full * BK + kb[e] < K) rb[e] = ld_b(pb[e]);
+    }
+  };
+  auto store_b = [&](int buf, const v2du (&rb)[S::VB]) {
+    double* base = &Bs[buf][0][0];
+#pragma unroll
+    for (int e = 0; e < S::VB; ++e) {
+      v2d v;
+      v.x = second[e] ? rb[e].y : rb[e].x;
+      v.y = rb[e].y;
+      *(v2d*)(base + lb[e]) = v;
+    }
+  };
+  double ra[MI][4], rn[MI][4];
+  v2du rb[S::VB];
+  auto mul = [&](int buf, int t) {
+    const double* bp = &Bs[buf][S::kof(t) + 2 * lk][wn * NI * 16 + li];
+    double b[NI];
+#pragma unroll
+    for (int j = 0; j < NI; ++j) b[j] = bp[16 * j];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ra[i][t], b[j], acc[i][j], 0, 0, 0);
+  };
+  auto advance = [&]() {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) ra[i][t] = rn[i][t];
+  };
+
+  if (s0 < full) {
+    load_b(rb);
+    load_a(ra);
+  } else {
+    load_b_last(rb);
+    load_a_last(ra);
+  }
+  store_b(0, rb);
+  if (s0 + 1 < s1) {
+    if (s0 + 1 < full) load_b(rb);
+    else load_b_last(rb);
+  }
+  // nothing is in flight where the loop begins: its waits are then only those
+  // of its own loads, in their order
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
   __syncthreads();
-  for (int kt = s0; kt < s1; ++kt) {
-    const int buf = (kt - s0) & 1;
-    if (kt + 1 < s1) load((kt + 1) * BK);
-#pragma unroll
-    for (int ks = 0; ks < BK; ks += 4) {
-      double a[MI], b[NI];
-      const int kr = ks + (lane >> 4);
-#pragma unroll
-      for (int i = 0; i < MI; ++i) {
-        const int m = wm * WTM + i * 16 + (lane & 15);
-        a[i] = TRANS ? As[buf][kr * AL::LT + m] : As[buf][m * AL::LN + kr];
-      }
-#pragma unroll
-      for (int j = 0; j < NI; ++j) b[j] = Bs[buf][kr][wn * WTN + j * 16 + (lane & 15)];
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    if (kt + 1 < s1) store(buf ^ 1);
+  int s = s0, buf = 0;
+  for (; s + 2 < sf; ++s, buf ^= 1) {
+    // matrix instructions and LDS reads may move across these marks, loads,
+    // LDS stores and the waits they need may not
+    mul(buf, 0);
+    __builtin_amdgcn_sched_barrier(0x108);
+    load_a(rn);
+    mul(buf, 1);
+    __builtin_amdgcn_sched_barrier(0x108);
+    store_b(buf ^ 1, rb);
+    load_b(rb);
+    mul(buf, 2);
+    __builtin_amdgcn_sched_barrier(0x108);
+    mul(buf, 3);
     __syncthreads();
+    advance();
+  }
+  for (; s < s1; ++s, buf ^= 1) {   // the last slices: what comes after may be partial or absent
+    if (s + 1 < s1) {
+      if (s + 1 < full) load_a(rn);
+      else load_a_last(rn);
+      store_b(buf ^ 1, rb);
+    }
+    if (s + 2 < s1) {
+      if (s + 2 < full) load_b(rb);
+      else load_b_last(rb);
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) mul(buf, t);
+    __syncthreads();
+    advance();
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, bool BODD>
-__global__ __launch_bounds__(64 * WGM * WGN, 512 / (64 * WGM * WGN)) void gemm_streamk_f64(
-    GemmBatch g, StreamK sk) {
-  constexpr int WTM = BM / WGM, WTN = BN / WGN;
-  constexpr int MI = WTM / 16, NI = WTN / 16;
-  __shared__ double As[2][SkinnyA<BM, 16>::SIZE];
-  __shared__ double Bs[2][16][BN + 16];
+template <int MI, int NI, int WN, bool ONE>
+__global__ __launch_bounds__(512, 2) void gemm_streamk_f64(GemmBatch g, StreamK sk) {
+  using S = SkTile<MI, NI, WN>;
+  constexpr int BM = S::BM, BN = S::BN;
+  __shared__ __attribute__((aligned(16))) double Bs[2][16][S::LB];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave % WGM, wn = wave / WGM;
+  const int wm = wave / WN, wn = wave % WN;
   const int w = xcd_remap(blockIdx.x, gridDim.x);
-  const long begin = sk_begin(w, sk), end = sk_begin(w + 1, sk);
+  const int begin = sk_begin(w, sk), end = sk_begin(w + 1, sk);
   const int M = g.M, N = g.N;
   // segments last to first: a range of L <= nslices slices then reads slice
   // t of its second tile, and later slice t + nslices - L of its first, at
   // step t, so the ranges sharing a problem (and an XCD) walk K in two
   // phases and reuse each B slice from L2
-  long pend = end;
+  int pend = end;
   while (pend > begin) {
-    const long tile = (pend - 1) / sk.nslices;
-    const long pos = tile * sk.nslices > begin ? tile * sk.nslices : begin;
-    const int s0 = (int)(pos - tile * sk.nslices), s1 = (int)(pend - tile * sk.nslices);
-    const int prob = (int)(tile / sk.tiles_m), m0 = (int)(tile % sk.tiles_m) * BM;
+    const int tile = (pend - 1) / sk.nslices;
+    const int pos = max(tile * sk.nslices, begin);
+    const int s0 = pos - tile * sk.nslices, s1 = pend - tile * sk.nslices;
+    const int prob = tile / sk.tiles_m, m0 = (tile % sk.tiles_m) * BM;
     v4d acc[MI][NI];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NI; ++j) acc[i][j] = v4d{0, 0, 0, 0};
     if (g.transA[prob])
-      sk_segment<BM, BN, WGM, WGN, true, BODD, MI, NI>(g, prob, m0, s0, s1, As, Bs, acc);
+      sk_segment<MI, NI, WN, true, ONE>(g, prob, m0, s0, s1, Bs, acc);
     else
-      sk_segment<BM, BN, WGM, WGN, false, BODD, MI, NI>(g, prob, m0, s0, s1, As, Bs, acc);
+      sk_segment<MI, NI, WN, false, ONE>(g, prob, m0, s0, s1, Bs, acc);
+    const int mw = wm * MI * 16 + (lane >> 4), nw = wn * NI * 16 + (lane & 15);
     if (s0 == 0 && s1 == sk.nslices) {
       // the whole tile: written here
       double* C = (double*)g.C[prob];
@@ -755,7 +843,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 512 / (64 * WGM * WGN)) void gemm_s
       bool okn[NI];
 #pragma unroll
       for (int j = 0; j < NI; ++j) {
-        const int n = wn * WTN + j * 16 + (lane & 15);
+        const int n = nw + j * 16;
         okn[j] = n < N;
         offn[j] = okn[j] ? map2(n, g.cdiv_n, g.cs_n1, g.cs_n0) : 0;
       }
@@ -763,7 +851,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 512 / (64 * WGM * WGN)) void gemm_s
       for (int i = 0; i < MI; ++i) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int m = m0 + wm * WTM + i * 16 + (lane >> 4) + 4 * r;
+          const int m = m0 + mw + i * 16 + 4 * r;
           if (m >= M) continue;
           const long offm = map2(m, g.cdiv_m, g.cs_m1, g.cs_m0);
 #pragma unroll
@@ -778,15 +866,13 @@ __global__ __launch_bounds__(64 * WGM * WGN, 512 / (64 * WGM * WGN)) void gemm_s
       }
     } else {
       // part of a tile: into the slot of this segment
-      double* P = sk.part + (long)(2 * w + (pos == begin ? 0 : 1)) * (BM * BN);
+      double* P = sk.part + (long)(2 * w + (pos == begin ? 0 : 1)) * (BM * BN) + mw * BN + nw;
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int ml = wm * WTM + i * 16 + (lane >> 4) + 4 * r;
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-          for (int j = 0; j < NI; ++j) P[ml * BN + wn * WTN + j * 16 + (lane & 15)] = acc[i][j][r];
-        }
+          for (int j = 0; j < NI; ++j) P[(i * 16 + 4 * r) * BN + j * 16] = acc[i][j][r];
     }
     pend = pos;
   }
@@ -936,15 +1022,15 @@ __global__ __launch_bounds__(skf32::NT, 1) void gemm_streamk_f32(GemmBatch g, St
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave % WGM, wn = wave / WGM;
   const int w = xcd_remap(blockIdx.x, gridDim.x);
-  const long begin = sk_begin(w, sk), end = sk_begin(w + 1, sk);
+  const int begin = sk_begin(w, sk), end = sk_begin(w + 1, sk);
   const int M = g.M, N = g.N;
   // segments last to first, as in the float64 kernel
-  long pend = end;
+  int pend = end;
   while (pend > begin) {
-    const long tile = (pend - 1) / sk.nslices;
-    const long pos = tile * sk.nslices > begin ? tile * sk.nslices : begin;
-    const int s0 = (int)(pos - tile * sk.nslices), s1 = (int)(pend - tile * sk.nslices);
-    const int prob = (int)(tile / sk.tiles_m), m0 = (int)(tile % sk.tiles_m) * BM;
+    const int tile = (pend - 1) / sk.nslices;
+    const int pos = max(tile * sk.nslices, begin);
+    const int s0 = pos - tile * sk.nslices, s1 = pend - tile * sk.nslices;
+    const int prob = tile / sk.tiles_m, m0 = (tile % sk.tiles_m) * BM;
     v4f acc[MI][NI];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -993,29 +1079,38 @@ __global__ __launch_bounds__(skf32::NT, 1) void gemm_streamk_f32(GemmBatch g, St
 // Sums the partial tiles of every tile cut by range boundaries, in
 // workgroup order, and writes them through C's index map (alpha and
 // accumulate as in the main kernel).  kFixRows-row strips of a tile per block
-// of 256 threads, two adjacent columns per thread.  Ranges are never empty here (the
-// split runs only with at least 8 slices per workgroup), so every workgroup
-// between the first and the last owner of a tile left a partial in slot 2w.
-constexpr int kFixRows = 24;
+// of 256 threads, two adjacent columns per thread, four partials in flight.
+// Ranges are never empty here (the split runs only with at least 8 slices
+// per workgroup), so every workgroup between the first and the last owner of
+// a tile left a partial in slot 2w.
+constexpr int kFixRows = 8;
 
 template <int BM, int BN>
 __global__ __launch_bounds__(256) void gemm_streamk_fixup(GemmBatch g, StreamK sk) {
   static_assert(BM % kFixRows == 0 && BN % 2 == 0, "strip shape");
-  const long tile = blockIdx.x / (BM / kFixRows);
+  const int tile = blockIdx.x / (BM / kFixRows);
   const int r0 = (blockIdx.x % (BM / kFixRows)) * kFixRows;
-  const long t0 = tile * sk.nslices, t1 = t0 + sk.nslices;
+  const int t0 = tile * sk.nslices, t1 = t0 + sk.nslices;
   const int wf = sk_owner(t0, sk), wl = sk_owner(t1 - 1, sk);
   if (wf == wl) return;
-  const int prob = (int)(tile / sk.tiles_m), m0 = (int)(tile % sk.tiles_m) * BM;
+  const int prob = tile / sk.tiles_m, m0 = (tile % sk.tiles_m) * BM;
   const int first_slot = sk_begin(wf, sk) < t0 ? 2 * wf + 1 : 2 * wf;
   double* C = (double*)g.C[prob];
   constexpr int PR = BN / 2;   // column pairs per row
   for (int q = threadIdx.x; q < kFixRows * PR; q += 256) {
     const int ml = r0 + q / PR, n = 2 * (q % PR), m = m0 + ml;
     if (m >= g.M || n >= g.N) continue;
-    const long e = (long)ml * BN + n;
-    v2d v = *(const v2d*)&sk.part[(long)first_slot * (BM * BN) + e];
-    for (int w = wf + 1; w <= wl; ++w) v += *(const v2d*)&sk.part[(long)(2 * w) * (BM * BN) + e];
+    const double* P = sk.part + (long)ml * BN + n;
+    v2d v = *(const v2d*)(P + (long)first_slot * (BM * BN));
+    int w = wf + 1;
+    for (; w + 3 <= wl; w += 4) {
+      v2d x[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = *(const v2d*)(P + (long)(2 * (w + i)) * (BM * BN));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v += x[i];
+    }
+    for (; w <= wl; ++w) v += *(const v2d*)(P + (long)(2 * w) * (BM * BN));
     const bool two = n + 1 < g.N;
     const long offm = map2(m, g.cdiv_m, g.cs_m1, g.cs_m0);
     double* p0 = C + offm + map2(n, g.cdiv_n, g.cs_n1, g.cs_n0);
@@ -1522,39 +1617,47 @@ size_t gemm_si_scratch_bytes() { return (size_t)2 * kSplitMaxCus * 192 * 160 * s
 // Ranges of the split: ncu, or fewer so that each holds at least 8 slices.
 static int sk_ranges(long pairs, int ncu) { return (int)std::min<long>(ncu, pairs / 8); }
 
+// Rows of a tile of the split kernel: 192 (4 x 2 wavefronts) where N needs
+// more than seven 16-column blocks; else 8 wavefronts one above the other
+// with one or two 16-row blocks each and as many columns as N needs (less of
+// the matrix work is padding than on 128 or 160 columns).  256 rows read B
+// half as often; 128 where the taller tile would add more than a tenth of
+// rows past the edge.
+static int sk_rows(int M, int N) {
+  if (N > 112) return 192;
+  const long tall = (long)ceil_div(M, 256) * 256, low = (long)ceil_div(M, 128) * 128;
+  return 10 * tall > 11 * low ? 128 : 256;
+}
+
 bool gemm_si_balanced_useful(int count, int M, int N, int K, int ncu) {
   // the split pays whenever each tile holds several slices: its ranges keep
   // every CU busy for the same time whatever the tile count, where the
   // plain kernel leaves CUs idle through whole K walks once the tiles are
   // fewer than the slots or do not divide them
   if (ncu < 1 || ncu > kSplitMaxCus || N > 160 || M <= 0 || count <= 0 || K <= 0) return false;
-  const long tiles = (long)ceil_div(M, 192) * count, ns = ceil_div(K, 16);
-  return ns >= 16 && sk_ranges(tiles * ns, ncu) >= 1;
-}
-
-// The split kernel's operands: A as the skinny kernel's (even lda, 16-byte
-// aligned rows); B with an even ldb on 16-byte aligned bases, or with an odd
-// one on 8-byte aligned bases (loaded one element at a time).
-static bool streamk_ok(const GemmBatch& g) {
-  if ((g.lda & 1) || (g.a_bs & 1)) return false;
-  const uintptr_t balign = (g.ldb & 1) ? 7 : 15;
-  for (int i = 0; i < g.count; ++i)
-    if (((uintptr_t)g.A[i] & 15) || ((uintptr_t)g.B[i] & balign)) return false;
-  return true;
+  const long tiles = (long)ceil_div(M, sk_rows(M, N)) * count, ns = ceil_div(K, 16);
+  return ns >= 16 && sk_ranges(tiles * ns, ncu) >= 1 && tiles * ns <= (1L << 30);
 }
 
 bool gemm_si_balanced_applies(const GemmBatch& g, const void* scratch, int ncu) {
   if (!scratch || ((uintptr_t)scratch & 15) || g.M <= 0 || g.N <= 0 || g.count <= 0 || g.nbatch != 1)
     return false;
-  return gemm_si_balanced_useful(g.count, g.M, g.N, g.K, ncu) && streamk_ok(g) &&
-         (long)g.count * ceil_div(g.M, 192) * ceil_div(g.K, 16) <= (1L << 40);
+  return gemm_si_balanced_useful(g.count, g.M, g.N, g.K, ncu);
 }
 
-template <int BN, bool BODD>
-static int launch_streamk_f64(const GemmBatch& g, const StreamK& sk, hipStream_t s) {
-  gemm_streamk_f64<192, BN, 4, 2, BODD><<<sk.nwg, 512, 0, s>>>(g, sk);
+template <int MI, int NI, int WN, bool ONE = false>
+static int launch_streamk_f64(const GemmBatch& g, StreamK& sk, int ncu, hipStream_t s) {
+  using S = SkTile<MI, NI, WN>;
+  static_assert((size_t)S::BM * S::BN <= 192 * 160, "scratch slots");
+  sk.tiles_m = ceil_div(g.M, S::BM);
+  const int total = g.count * sk.tiles_m * sk.nslices;
+  sk.nwg = sk_ranges(total, ncu);
+  sk.per = total / sk.nwg;
+  sk.rem = total % sk.nwg;
+  gemm_streamk_f64<MI, NI, WN, ONE><<<sk.nwg, S::NT, 0, s>>>(g, sk);
   CTM_HIP_TRY(hipGetLastError());
-  gemm_streamk_fixup<192, BN><<<(int)((long)g.count * sk.tiles_m * (192 / kFixRows)), 256, 0, s>>>(g, sk);
+  gemm_streamk_fixup<S::BM, S::BN>
+      <<<g.count * sk.tiles_m * (S::BM / kFixRows), 256, 0, s>>>(g, sk);
   CTM_HIP_TRY(hipGetLastError());
   return 0;
 }
@@ -1562,19 +1665,23 @@ static int launch_streamk_f64(const GemmBatch& g, const StreamK& sk, hipStream_t
 int launch_gemm_si_balanced(const GemmBatch& g, double* scratch, int ncu, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.count <= 0 || g.nbatch <= 0) return 0;
   if (!gemm_si_balanced_applies(g, scratch, ncu)) return launch_gemm_si(g, s);
-  const int tm = ceil_div(g.M, 192);
-  const int ns = ceil_div(g.K, 16);
-  StreamK sk;
-  sk.nslices = ns;
-  sk.tiles_m = tm;
-  sk.total = (long)g.count * tm * ns;
-  sk.nwg = sk_ranges(sk.total, ncu);
+  StreamK sk{};
+  sk.nslices = ceil_div(g.K, 16);
   sk.part = scratch;
-  // 128-wide tiles for N <= 128 (3 x 4 accumulator blocks of 16 x 16 per
-  // wavefront): less of the MFMA work is padding
-  const bool odd = g.ldb & 1;
-  if (g.N <= 128) return odd ? launch_streamk_f64<128, true>(g, sk, s) : launch_streamk_f64<128, false>(g, sk, s);
-  return odd ? launch_streamk_f64<160, true>(g, sk, s) : launch_streamk_f64<160, false>(g, sk, s);
+  if (g.N > 128) return launch_streamk_f64<3, 5, 2>(g, sk, ncu, s);
+  if (g.N > 112) return launch_streamk_f64<3, 4, 2>(g, sk, ncu, s);
+  const bool tall = sk_rows(g.M, g.N) == 256;
+  if (g.N == 1)
+    return tall ? launch_streamk_f64<2, 1, 1, true>(g, sk, ncu, s) : launch_streamk_f64<1, 1, 1, true>(g, sk, ncu, s);
+  switch ((g.N + 15) / 16) {
+    case 1: return tall ? launch_streamk_f64<2, 1, 1>(g, sk, ncu, s) : launch_streamk_f64<1, 1, 1>(g, sk, ncu, s);
+    case 2: return tall ? launch_streamk_f64<2, 2, 1>(g, sk, ncu, s) : launch_streamk_f64<1, 2, 1>(g, sk, ncu, s);
+    case 3: return tall ? launch_streamk_f64<2, 3, 1>(g, sk, ncu, s) : launch_streamk_f64<1, 3, 1>(g, sk, ncu, s);
+    case 4: return tall ? launch_streamk_f64<2, 4, 1>(g, sk, ncu, s) : launch_streamk_f64<1, 4, 1>(g, sk, ncu, s);
+    case 5: return tall ? launch_streamk_f64<2, 5, 1>(g, sk, ncu, s) : launch_streamk_f64<1, 5, 1>(g, sk, ncu, s);
+    case 6: return tall ? launch_streamk_f64<2, 6, 1>(g, sk, ncu, s) : launch_streamk_f64<1, 6, 1>(g, sk, ncu, s);
+    default: return tall ? launch_streamk_f64<2, 7, 1>(g, sk, ncu, s) : launch_streamk_f64<1, 7, 1>(g, sk, ncu, s);
+  }
 }
 
 int launch_gemm_f64_any(const GemmBatch& g, double* scratch, int ncu, hipStream_t s) {
@@ -1593,7 +1700,7 @@ bool gemm_si_f32_balanced_applies(const GemmBatch& g, const void* scratch, int n
   // at least 8 slices per range, so that no range is empty, and 8 per tile
   const long tiles = (long)g.count * ceil_div(g.M, skf32::BM), ns = ceil_div(g.K, skf32::BK);
   return rowmajor_c && ncu >= 1 && ncu <= kSplitMaxCus && ns >= 8 && tiles * ns >= 8L * ncu &&
-         tiles * ns <= (1L << 40);
+         tiles * ns <= (1L << 30);
 }
 
 int launch_gemm_si_f32_balanced(const GemmBatch& g, double* scratch, int ncu, hipStream_t s) {
@@ -1603,8 +1710,10 @@ int launch_gemm_si_f32_balanced(const GemmBatch& g, double* scratch, int ncu, hi
   StreamK sk;
   sk.nslices = ceil_div(g.K, skf32::BK);
   sk.tiles_m = tm;
-  sk.total = (long)g.count * tm * sk.nslices;
+  const int total = g.count * tm * sk.nslices;
   sk.nwg = ncu;
+  sk.per = total / ncu;
+  sk.rem = total % ncu;
   sk.part = scratch;
   gemm_streamk_f32<<<ncu, skf32::NT, 0, s>>>(g, sk);
   CTM_HIP_TRY(hipGetLastError());
