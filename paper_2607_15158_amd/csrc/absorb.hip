@@ -11,16 +11,23 @@
 //   Ct[(x, o1k o1b), (y, o2k o2b)]   = sum_(pb, qb, s) X[...] A[s, pb, qb, o1b, o2b]
 // the same tensor for 4 d chi^2 D^6 flops (9x less at D = 6, d = 2).
 //
-// One workgroup takes kAbsG = 2 consecutive (x, y) pairs of one problem:
-// their W rows and the problem's leg permutation of A are staged in LDS, the
-// first product (rows (g, pb, qb), K = D^2, N = d D^2) writes X to LDS, the
-// second (rows (g, o1k, o2k), K = d D^2, N = D^2) stages the output block in
-// LDS, from where it is written through the output's index map (for the
-// corners, each pair's D^2 columns of a row of Ct contiguously).  The edges'
-// absorption Z2 = Z1 a has the same form with rows (b, g').  Both run on v_mfma_f64_16x16x4; the index
-// groupings of every operand are additive, so per-dimension offset tables in
-// LDS turn each fragment into a per-lane base plus one table entry per
-// k-step.
+// A wavefront takes one (x, y) pair at a time, on its own: with rows (pb, qb)
+// and K = (pk, qk), the first product leaves X_s in the matrix cores' result
+// layout (row l / 16 + 4 r, column l % 16), which is their operand layout for
+// the second product, out^T[(o1b, o2b), (o1k, o2k)] += A_s^T X_s with
+// K = (pb, qb), so X never leaves the registers and no wavefront waits for
+// another.  Both products read the same fragments of A_s, from a table every
+// workgroup sets up once (the workgroups are persistent); the pair's W and
+// its output block pass through one buffer per wavefront, so that global
+// memory is read and written in runs.  D^2 = 36 is padded to 48 rows and
+// columns (324 matrix instructions per pair where 182 would hold the
+// numbers), which costs less than sharing rows between wavefronts.
+//
+// Bound by the f64 matrix cores (0.70 ms for the four corners of D = 6,
+// chi = 144, against 0.35 ms of memory traffic).  Two pairs per workgroup, with X and the
+// output staged in LDS for all four wavefronts and A permuted anew by every
+// workgroup, took 2.64 ms; this form 0.89 ms (D = 5, chi = 75: 387 and
+// 108 us; D = 4, chi = 64: 136 and 16 us).
 
 #include "common.h"
 #include "elem.h"
@@ -28,12 +35,9 @@
 namespace sictm {
 namespace {
 
-constexpr int kAbsG = 2;          // (x, y) pairs per workgroup
 constexpr int kAbsMaxDl = 36;     // D^2 up to D = 6
 constexpr int kAbsMaxN = 72;      // d D^2 up to d = 2 at D = 6
-constexpr int kAbsRB = ((kAbsG * kAbsMaxDl + 15) / 16 + 3) / 4;   // 16-row blocks per wavefront
-constexpr int kAbsNB1 = (kAbsMaxN + 15) / 16;    // column blocks of the first product
-constexpr int kAbsNB2 = (kAbsMaxDl + 15) / 16;   // column blocks of the second
+constexpr int kAbsWaves = 8;
 
 constexpr int kAbsMaxProb = 8;
 
@@ -44,181 +48,143 @@ struct AbsArgs {
   const double* A[kAbsMaxProb];    // single-layer site tensor [s][u][l][d][r] per problem
   long sA[kAbsMaxProb][4];         // per problem: strides in A of the legs p, q, o1, o2
   long nR, sR1, sR2, so1, so2;
-  int n2, D, d, Dl;
+  int n2, d;
 };
 
-// DT: the bond dimension D as a compile-time constant (every index division
-// by D or D^2 becomes a multiply).
-template <int DT, typename TO>
-__global__ __launch_bounds__(256) void k_absorb_corner(AbsArgs a) {
-  // LDS: one buffer holds in turn the W rows [G][Dl][Dl], X [G * Dl][dDl]
-  // and the corner block in Ct's order; A [s][p][q][o1][o2] (62 KB in all:
-  // two workgroups share a CU)
-  static_assert(kAbsMaxN >= kAbsMaxDl, "X is the largest stage");
-  __shared__ double Bx[kAbsG * kAbsMaxDl * kAbsMaxN];
-  __shared__ double As[kAbsMaxN * kAbsMaxDl];
-  double* const Ws = Bx;
-  double* const Xs = Bx;
-  const int corner = blockIdx.y;
+// Sizes for a bond dimension D (a compile-time constant, so that index
+// divisions become multiplies).
+template <int D>
+struct AbsTile {
+  static constexpr int Dl = D * D;
+  static constexpr int RB = (Dl + 15) / 16;        // 16-row (and column) blocks
+  static constexpr int KS = (Dl + 3) / 4;          // k-steps
+  static constexpr int LA = RB == 1 ? 16 : 48;     // table row: rows 1 apart fall 32 banks apart
+  static constexpr int SA = 4 * KS * LA;           // table of one s
+  static constexpr int SW = Dl * Dl + (Dl & 1);    // one pair's W or output block
+  static constexpr int NP = (Dl * Dl / 2 + 63) / 64;   // 16-byte loads per lane
+  static constexpr int dmax = kAbsMaxN / Dl;
+};
+
+typedef double v2da __attribute__((ext_vector_type(2), aligned(8)));
+
+template <int D, typename TO>
+__global__ __launch_bounds__(64 * kAbsWaves, 2) void k_absorb_corner(AbsArgs a) {
+  using S = AbsTile<D>;
+  constexpr int Dl = S::Dl, RB = S::RB, KS = S::KS, LA = S::LA;
+  constexpr int D4 = Dl * Dl;
+  // As: [s][(p, q)][(o1, o2)], zeros outside
+  __shared__ __attribute__((aligned(16))) double As[S::dmax * S::SA], bufs[kAbsWaves][S::SW];
+  const int prob = blockIdx.y, d = a.d;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  constexpr int D = DT, Dl = DT * DT;
-  const int d = a.d, dDl = d * Dl;
-  const long nR = a.nR;
-  const long R0 = (long)blockIdx.x * kAbsG;
-  const int G = (int)min((long)kAbsG, nR - R0);
-  __shared__ long rowoff[kAbsG];   // output offset of pair g
-  if (tid < G) {
-    const long R = R0 + tid;
-    rowoff[tid] = (R / a.n2) * a.sR1 + (R % a.n2) * a.sR2;
-  }
-  __shared__ int ko1[kAbsMaxDl], mo1[kAbsMaxDl], k1off[kAbsMaxDl], n1off[kAbsMaxN];
-  __shared__ int ko2[kAbsMaxN], k2off[kAbsMaxN], n2off[kAbsMaxDl], mo2[kAbsMaxDl];
-  const double* W = a.W[corner];
-  for (long i = tid; i < (long)G * Dl * Dl; i += 256) Ws[i] = W[R0 * Dl * Dl + i];
-  const long* st = a.sA[corner];
-  constexpr int D2 = D * D, D3 = D2 * D, D4 = D3 * D;
-  for (int i = tid; i < d * D4; i += 256) {
-    int rem = i;
-    const int o2 = rem % D; rem /= D;
-    const int o1 = rem % D; rem /= D;
-    const int q = rem % D; rem /= D;
-    const int p = rem % D;
-    const int s = rem / D;
-    As[i] = a.A[corner][(long)s * D4 + p * st[0] + q * st[1] + o1 * st[2] + o2 * st[3]];
-  }
-  for (int i = tid; i < Dl; i += 256) {
-    const int hi = i / D, lo = i % D;
-    ko1[i] = hi * D * Dl + lo * D;       // k = (pk, qk) -> W offset
-    mo1[i] = hi * Dl + lo;               // m' = (pb, qb) -> W offset
-    k1off[i] = hi * D3 + lo * D2;        // k = (pk, qk) -> A offset
-    n2off[i] = hi * D + lo;              // n = (o1b, o2b) -> A offset
-    mo2[i] = hi * D + lo;                // (o1k, o2k) -> X column offset
-  }
-  for (int i = tid; i < dDl; i += 256) {
-    const int s = i / Dl, r = i % Dl;
-    n1off[i] = s * D4 + (r / D) * D + r % D;                  // n = (s, o1k, o2k) -> A
-    ko2[i] = (r / D * D + r % D) * dDl + s * Dl;              // k = (pb, qb, s) (pairs first) -> X
-    k2off[i] = s * D4 + (r / D) * D3 + (r % D) * D2;          // k = (pb, qb, s) -> A
-  }
-  __syncthreads();
-  // Wavefront w takes the 16-row blocks w and w + 4 of both products and
-  // every column block, so each k-step's fragments feed up to 10 (then 6)
-  // independent accumulators.
-  const int M = G * Dl;
-  const int mb = (M + 15) >> 4, nb1 = (dDl + 15) >> 4, nb2 = (Dl + 15) >> 4;
   const int li = lane & 15, lk = lane >> 4;
-  int abase[kAbsRB];
-  bool arow[kAbsRB];   // this lane's operand row m exists (per lane)
-  bool blk[kAbsRB];    // the wavefront's u-th row block exists (uniform)
-  // product 1: X[(g, pb, qb), (s, o1k, o2k)], rows m = g Dl + m'
-  {
-    int bbase[kAbsNB1];
-    bool bcol[kAbsNB1];
-#pragma unroll
-    for (int u = 0; u < kAbsRB; ++u) {
-      const int m = ((wave + 4 * u) << 4) + li;
-      blk[u] = (wave + 4 * u) < mb;
-      arow[u] = blk[u] && m < M;
-      abase[u] = arow[u] ? (m / Dl) * Dl * Dl + mo1[m % Dl] : 0;
-    }
-#pragma unroll
-    for (int v = 0; v < kAbsNB1; ++v) {
-      const int n = (v << 4) + li;
-      bcol[v] = v < nb1 && n < dDl;
-      bbase[v] = bcol[v] ? n1off[n] : 0;
-    }
-    v4d acc[kAbsRB][kAbsNB1];
-#pragma unroll
-    for (int u = 0; u < kAbsRB; ++u)
-#pragma unroll
-      for (int v = 0; v < kAbsNB1; ++v) acc[u][v] = v4d{0, 0, 0, 0};
-    for (int t = 0; t < Dl; t += 4) {
-      const int k = t + lk;
-      const bool kin = k < Dl;
-      const int kk = kin ? k : 0;
-      const int ka = ko1[kk], kb = k1off[kk];
-      double av[kAbsRB], bv[kAbsNB1];
-#pragma unroll
-      for (int u = 0; u < kAbsRB; ++u) av[u] = (arow[u] && kin) ? Ws[abase[u] + ka] : 0.0;
-#pragma unroll
-      for (int v = 0; v < kAbsNB1; ++v) bv[v] = (bcol[v] && kin) ? As[bbase[v] + kb] : 0.0;
-#pragma unroll
-      for (int u = 0; u < kAbsRB; ++u)
-#pragma unroll
-        for (int v = 0; v < kAbsNB1; ++v)
-          acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[v], acc[u][v], 0, 0, 0);
-    }
-    __syncthreads();   // every wavefront is done with the W rows
-#pragma unroll
-    for (int u = 0; u < kAbsRB; ++u)
-#pragma unroll
-      for (int v = 0; v < kAbsNB1; ++v)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = ((wave + 4 * u) << 4) + lk + 4 * r, col = (v << 4) + li;
-          if (blk[u] && row < M && col < dDl) Xs[row * dDl + col] = acc[u][v][r];
-        }
+  double* buf = bufs[wave];
+  const long* st = a.sA[prob];
+  for (int i = tid; i < d * S::SA; i += 64 * kAbsWaves) {
+    const int s = i / S::SA, k = i % S::SA / LA, n = i % LA;
+    As[i] = k < Dl && n < Dl ? a.A[prob][(long)s * D4 + (k / D) * st[0] + (k % D) * st[1] +
+                                         (n / D) * st[2] + (n % D) * st[3]]
+                             : 0.0;
   }
   __syncthreads();
-  // product 2: rows (g, o1k, o2k), columns (o1b, o2b), K = (s, pb, qb); the
-  // results go to LDS (over X) in Ct's order, [g][(o1k, o1b)][(o2k, o2b)]
-  {
-    int bbase[kAbsNB2];
-    bool bcol[kAbsNB2];
+  // offsets in a pair's block of (hi, lo) as the ket halves (of K = (pk, qk)
+  // and of (o1k, o2k)) and as the bra halves (of (pb, qb) and of (o1b, o2b))
+  auto ket = [](int i) { return (i / D) * D * Dl + (i % D) * D; };
+  auto bra = [](int i) { return (i / D) * Dl + i % D; };
+  int kk[KS], kb[KS];   // of 4 t + lk
+  bool kin[KS];
 #pragma unroll
-    for (int u = 0; u < kAbsRB; ++u) {
-      const int m = ((wave + 4 * u) << 4) + li;
-      abase[u] = arow[u] ? (m / Dl) * Dl * dDl + mo2[m % Dl] : 0;
-    }
-#pragma unroll
-    for (int v = 0; v < kAbsNB2; ++v) {
-      const int n = (v << 4) + li;
-      bcol[v] = v < nb2 && n < Dl;
-      bbase[v] = bcol[v] ? n2off[n] : 0;
-    }
-    v4d acc[kAbsRB][kAbsNB2];
-#pragma unroll
-    for (int u = 0; u < kAbsRB; ++u)
-#pragma unroll
-      for (int v = 0; v < kAbsNB2; ++v) acc[u][v] = v4d{0, 0, 0, 0};
-    for (int t = 0; t < dDl; t += 4) {
-      const int k = t + lk;
-      const bool kin = k < dDl;
-      const int kk = kin ? k : 0;
-      const int ka = ko2[kk], kb = k2off[kk];
-      double av[kAbsRB], bv[kAbsNB2];
-#pragma unroll
-      for (int u = 0; u < kAbsRB; ++u) av[u] = (arow[u] && kin) ? Xs[abase[u] + ka] : 0.0;
-#pragma unroll
-      for (int v = 0; v < kAbsNB2; ++v) bv[v] = (bcol[v] && kin) ? As[bbase[v] + kb] : 0.0;
-#pragma unroll
-      for (int u = 0; u < kAbsRB; ++u)
-#pragma unroll
-        for (int v = 0; v < kAbsNB2; ++v)
-          acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[v], acc[u][v], 0, 0, 0);
-    }
-    __syncthreads();   // every wavefront is done with X
-#pragma unroll
-    for (int u = 0; u < kAbsRB; ++u)
-#pragma unroll
-      for (int v = 0; v < kAbsNB2; ++v)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = ((wave + 4 * u) << 4) + lk + 4 * r, col = (v << 4) + li;
-          if (blk[u] && row < M && col < Dl) {
-            const int g = row / Dl, o = row % Dl, o1k = o / D, o2k = o % D;
-            const int o1b = col / D, o2b = col % D;
-            Ws[(g * Dl + o1k * D + o1b) * Dl + o2k * D + o2b] = acc[u][v][r];
-          }
-        }
+  for (int t = 0; t < KS; ++t) {
+    kin[t] = 4 * t + lk < Dl;
+    kk[t] = kin[t] ? ket(4 * t + lk) : 0;
+    kb[t] = kin[t] ? bra(4 * t + lk) : 0;
   }
-  __syncthreads();
-  // for the corners, rows (x, o1) of Ct hold the D^2 columns (y, o2) of one
-  // pair contiguously
-  TO* Ct = (TO*)a.Ct[corner];
-  for (int i = tid; i < G * Dl * Dl; i += 256) {
-    const int g = i / (Dl * Dl), rem = i % (Dl * Dl), o1 = rem / Dl, o2 = rem % Dl;
-    Ct[rowoff[g] + o1 * a.so1 + o2 * a.so2] = (TO)Ws[i];
+  int rb[RB];   // of 16 i + li
+  bool rin[RB];
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+    rin[i] = 16 * i + li < Dl;
+    rb[i] = rin[i] ? bra(16 * i + li) : 0;
+  }
+  const double* W = a.W[prob];
+  TO* C = (TO*)a.Ct[prob];
+  const long step = (long)gridDim.x * kAbsWaves;
+  for (long R = (long)blockIdx.x * kAbsWaves + wave; R < a.nR; R += step) {
+    {
+      const double* q = W + R * D4;
+      v2da w[S::NP];
+#pragma unroll
+      for (int e = 0; e < S::NP; ++e) {
+        const int i = lane + 64 * e;
+        if (i < D4 / 2) w[e] = *(const v2da*)(q + 2 * i);
+      }
+#pragma unroll
+      for (int e = 0; e < S::NP; ++e) {
+        const int i = lane + 64 * e;
+        if (i < D4 / 2) *(v2da*)(buf + 2 * i) = w[e];
+      }
+      if ((D4 & 1) && lane == 0) buf[D4 - 1] = q[D4 - 1];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    double wf[RB][KS];
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int t = 0; t < KS; ++t) {
+        const double v = buf[rb[i] + kk[t]];
+        wf[i][t] = rin[i] && kin[t] ? v : 0.0;
+      }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // one column block at a time (unrolled, its fragments would not fit the registers)
+#pragma unroll 1
+    for (int j = 0; j < RB; ++j) {
+      const int col = 16 * j + li;
+      v4d out[RB];
+#pragma unroll
+      for (int i = 0; i < RB; ++i) out[i] = v4d{0, 0, 0, 0};
+#pragma unroll 1
+      for (int s = 0; s < d; ++s) {
+        const double* F = As + s * S::SA + lk * LA + li;
+        v4d x[RB];
+#pragma unroll
+        for (int i = 0; i < RB; ++i) x[i] = v4d{0, 0, 0, 0};
+#pragma unroll
+        for (int t = 0; t < KS; ++t) {
+          const double f = F[4 * t * LA + 16 * j];
+#pragma unroll
+          for (int i = 0; i < RB; ++i)
+            x[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(wf[i][t], f, x[i], 0, 0, 0);
+        }
+#pragma unroll
+        for (int t = 0; t < KS; ++t)
+#pragma unroll
+          for (int i = 0; i < RB; ++i)
+            out[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(F[4 * t * LA + 16 * i], x[t >> 2][t & 3],
+                                                          out[i], 0, 0, 0);
+      }
+      // row 4 t + lk = (o1b, o2b), column 16 j + li = (o1k, o2k)
+#pragma unroll
+      for (int t = 0; t < KS; ++t)
+        if (kin[t] && col < Dl) buf[ket(col) + kb[t]] = out[t >> 2][t & 3];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    TO* o = C + (R / a.n2) * a.sR1 + (R % a.n2) * a.sR2;
+    if (D % 2 == 0 && a.so2 == 1) {
+      using V2 = TO __attribute__((ext_vector_type(2), aligned(sizeof(TO))));
+#pragma unroll
+      for (int e = 0; e < S::NP; ++e) {
+        const int i = 2 * (lane + 64 * e);
+        if (i < D4) {
+          const v2da v = *(const v2da*)(buf + i);
+          V2 u;
+          u.x = (TO)v.x;
+          u.y = (TO)v.y;
+          *(V2*)(o + (i / Dl) * a.so1 + i % Dl) = u;
+        }
+      }
+    } else {
+      for (int i = lane; i < D4; i += 64) o[(i / Dl) * a.so1 + (i % Dl) * a.so2] = (TO)buf[i];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
 }
 
@@ -228,14 +194,25 @@ bool absorb_corner_fits(int D, int d) {
   return d >= 1 && D >= 2 && D * D <= kAbsMaxDl && d * D * D <= kAbsMaxN;
 }
 
+// Persistent workgroups: as many as the chip holds side by side (LDS, and
+// the registers of D = 6), shared by the problems.
+template <int D, typename TO>
+static int launch_absorb_d(const AbsArgs& a, int count, hipStream_t s) {
+  const long per = (256L * (D >= 6 ? 1 : D == 5 ? 2 : 4) + count - 1) / count;
+  const long need = (a.nR + kAbsWaves - 1) / kAbsWaves;
+  k_absorb_corner<D, TO><<<dim3((unsigned)(need < per ? need : per), count), 64 * kAbsWaves, 0, s>>>(a);
+  CTM_HIP_TRY(hipGetLastError());
+  return 0;
+}
+
 template <typename TO>
-static void launch_absorb_t(const AbsArgs& a, dim3 grid, int D, hipStream_t s) {
+static int launch_absorb_t(const AbsArgs& a, int count, int D, hipStream_t s) {
   switch (D) {
-    case 2: k_absorb_corner<2, TO><<<grid, 256, 0, s>>>(a); break;
-    case 3: k_absorb_corner<3, TO><<<grid, 256, 0, s>>>(a); break;
-    case 4: k_absorb_corner<4, TO><<<grid, 256, 0, s>>>(a); break;
-    case 5: k_absorb_corner<5, TO><<<grid, 256, 0, s>>>(a); break;
-    default: k_absorb_corner<6, TO><<<grid, 256, 0, s>>>(a); break;
+    case 2: return launch_absorb_d<2, TO>(a, count, s);
+    case 3: return launch_absorb_d<3, TO>(a, count, s);
+    case 4: return launch_absorb_d<4, TO>(a, count, s);
+    case 5: return launch_absorb_d<5, TO>(a, count, s);
+    default: return launch_absorb_d<6, TO>(a, count, s);
   }
 }
 
@@ -259,14 +236,8 @@ int launch_absorb(int count, const double* const* W, void* const* out, bool out_
   a.sR2 = ostr[1];
   a.so1 = ostr[2];
   a.so2 = ostr[3];
-  a.D = D;
   a.d = d;
-  a.Dl = D * D;
-  dim3 grid((unsigned)((nR + kAbsG - 1) / kAbsG), count);
-  if (out_f32) launch_absorb_t<float>(a, grid, D, s);
-  else launch_absorb_t<double>(a, grid, D, s);
-  CTM_HIP_TRY(hipGetLastError());
-  return 0;
+  return out_f32 ? launch_absorb_t<float>(a, count, D, s) : launch_absorb_t<double>(a, count, D, s);
 }
 
 int launch_absorb_corners(const double* const* W, void* const* Ct, bool out_f32, const double* A,
