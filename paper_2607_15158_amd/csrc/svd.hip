@@ -12,20 +12,22 @@
 // Jacobi iteration runs on X = R^T, which converges in a few sweeps where A
 // itself needs dozens: R^T = Ut S V'^T gives A = (Q V') S (P Ut)^T.
 //
-// Block-pair parallel ordering: the columns are cut into blocks of kBlk; an
-// outer sweep pairs the blocks in a round-robin tournament, one launch per
-// round, one workgroup per block pair and matrix.  The workgroup loads the
-// 2 kBlk columns of U into LDS and rotates the pairs across the two blocks
-// in kBlk inner steps of kBlk disjoint pairs (in the sweep's first round,
-// where every block is visited once, the pairs within each block first, in
-// kBlk - 1 more steps), so that every column pair meets once per sweep;
-// 16 lanes per pair (rows spread over the lanes, dot products reduced by
-// DPP row sums); the
-// rotations of the visit are accumulated in a 2 kBlk x 2 kBlk matrix W and
-// applied to the right vectors once at the end (V_cols <- V_cols W).
-// A per-matrix flag records
-// whether a sweep rotated anything, and later launches return at once after
-// a sweep without rotations.  Columns that end numerically zero
+// Up to n = 96 (128 for the values alone) one workgroup holds the columns of
+// a matrix in LDS for all sweeps (svd_small).  Above that, block-pair parallel
+// ordering: the columns are cut into an even number of blocks of equal width,
+// at most kBlk; an outer sweep pairs the blocks in a round-robin tournament,
+// one workgroup per block pair and matrix, the rounds separated by grid
+// barriers of one cooperative launch, or by launches inside a stream capture.
+// The workgroup loads the columns of both blocks into LDS and rotates the
+// pairs across the two blocks in as many steps of disjoint pairs as a block
+// has columns (in the sweep's first round, where every block is visited once,
+// the pairs within each block first, by halving), so that every column pair
+// meets once per sweep; 16 lanes per pair (rows spread over the lanes, dot
+// products reduced by DPP row sums); the rotations of the visit are
+// accumulated in a 2 kBlk x 2 kBlk matrix W and applied to the right vectors
+// once at the end (V_cols <- V_cols W).  A per-matrix flag records whether a
+// sweep rotated anything, and the sweeps end after one without rotations.
+// Columns that end numerically zero
 // (rank-deficient input) are replaced by an orthonormal completion so that
 // u stays orthogonal.  Singular values are returned in descending order (ties by
 // index).
@@ -42,7 +44,6 @@ constexpr int kRPL = kSvdMaxN / 64;   // rows per lane in the finalisation
 constexpr int kCompChunk = 32;       // non-zero columns staged per LDS pass of the completion
 constexpr int kBlk = 16;              // columns per block
 constexpr int kMaxSweeps = 24;
-constexpr int kInner = 1;            // inner sweeps per block-pair visit
 constexpr int kLanesPerPair = 16;
 
 __device__ __forceinline__ double wsum(double x) { return wave_sum64(x); }
@@ -56,7 +57,7 @@ struct SvdArgs {
   double* V[kMaxProb];         // ... and right vectors (V')
   double* work;       // [count][2][n][n] column-major working columns
   int* flags;         // [count][kMaxSweeps] "a rotation happened in sweep s"
-  int n, nblk, want_v;
+  int n, nblk, bs, want_v;     // bs: columns of a block (<= kBlk)
   // preconditioning
   const double* Ain[kMaxProb]; // the caller's matrices
   double* Wp[kMaxProb];        // A P, then Q
@@ -166,11 +167,214 @@ __device__ __forceinline__ double fast_rcp(double x) {
   return fma(r, fma(-x, r, 1.0), r);
 }
 
+// The plane rotation that orthogonalises two columns with squared norms al,
+// be and product ga (all divided by the squared norm of the matrix, which
+// keeps their products in range): t, the smaller root of
+// t^2 + 2 zeta t = 1 with zeta = (be - al) / (2 ga), c and s.  False when
+// the pair is orthogonal to working precision (|ga| <= tol sqrt(al be), tol =
+// 1e-15 sqrt(n)) or a column is numerically zero: below 1e-15 of the matrix norm,
+// rotating cannot converge in the relative sense and does not change the
+// result above roundoff; such columns are completed at the end.  `counts`:
+// the rotation is clearly above roundoff (a pair left at |ga| ~ tol sqrt(al
+// be) keeps being rotated but does not prevent the sweeps from stopping).
+// The norms follow the rotation, al - t ga and be + t ga, and are summed anew
+// from the columns every sweep (visit).
+struct SvdScale {
+  double scale, tol2, cut;
+};
+__device__ __forceinline__ SvdScale svd_scale(double fro2, int n) {
+  const double scale = fro2 > 1e-300 ? 1.0 / fro2 : 1e300;
+  return {scale, 1e-30 * n, 1e-30 * (fro2 * scale)};
+}
+__device__ __forceinline__ bool plane_rotation(double al, double be, double ga, const SvdScale& f,
+                                               double& t, double& c, double& s, bool& counts) {
+  const double g2 = ga * ga, thr = f.tol2 * (al * be);
+  counts = g2 > 256.0 * thr;
+  if (!(g2 > thr && al > f.cut && be > f.cut)) return false;
+  const double d = be - al, h2 = fma(d, d, 4.0 * g2);
+  const double h = h2 * fast_rsqrt(h2);
+  t = copysign(2.0 * ga, d * ga) * fast_rcp(fabs(d) + h);
+  c = fast_rsqrt(fma(t, t, 1.0));
+  s = c * t;
+  return true;
+}
+
+// All sweeps of a small matrix in one workgroup, with the columns of U (and
+// of V) in LDS: a sweep is a sequence of halvings, each pairing the columns
+// of the first half of every set with those of the second (h steps for
+// halves of h columns, pair (i, (i + r) mod h) in step r), then the halves
+// with themselves: n - 1 steps and a few more for odd sizes.  16 lanes hold
+// a pair; the column of the first half stays in their registers for the h
+// steps, so that a step moves one column through LDS, sums one product and
+// has one barrier.  (Rotations with c left to a scale per column halve the
+// arithmetic and measured 1 to 5 % slower: the scales lengthen the chain.)
+//
+// Bound by the latency of a step (a 16-lane sum, three reciprocal square
+// roots and reciprocals, one LDS round trip).  Used where
+// U and V (U alone for values only) fit the LDS; above that the block-pair
+// kernels spread the columns over several CUs.  Measured, 4 random matrices with
+// vectors, before (block pairs of 16 columns at every size) and after: n = 20
+// 374 and 176 us, 64 872 and 497, 87 1724 and 1032, 96 1630 and 1108; values
+// only, n = 100: 1732 and 1149.
+template <int RPL, bool WANT_V>
+struct SmallSvd {
+  static constexpr int ROWS = 16 * RPL;
+  // columns 16 rows apart modulo 32 fall 32 banks apart for the two pairs of
+  // a half wavefront; where that does not fit, an odd stride
+  static constexpr int LD = ROWS <= 48 ? 48 : ROWS <= 80 ? 80 : ROWS + 1;
+  double U[ROWS][LD];
+  double V[WANT_V ? ROWS : 1][WANT_V ? LD : 1];
+  double nrm[ROWS];
+};
+
+template <int RPL, bool WANT_V>
+__global__ __launch_bounds__(8 * 16 * RPL) void svd_small(SvdArgs a) {
+  using L = SmallSvd<RPL, WANT_V>;
+  constexpr int NT = 8 * L::ROWS;
+  __shared__ L sh;
+  const int n = a.n, mat = blockIdx.x;
+  const int tid = threadIdx.x, grp = tid >> 4, li = tid & 15;
+  const double* A = a.A[mat];
+  // U[c][r] = A[r][c], V = I; rows from n on hold zeros
+  for (int i = tid; i < n * L::ROWS; i += NT) {
+    const int r = i / n, c = i % n;
+    sh.U[c][r] = r < n ? A[(size_t)r * n + c] : 0.0;
+    if (WANT_V) sh.V[c][r] = r == c ? 1.0 : 0.0;
+  }
+  const SvdScale f = svd_scale(a.fro2[mat], n);
+  __syncthreads();
+  for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
+    for (int c = grp; c < n; c += NT / 16) {
+      double x = 0.0;
+#pragma unroll
+      for (int t = 0; t < RPL; ++t) x = fma(sh.U[c][li + 16 * t], sh.U[c][li + 16 * t], x);
+      x = gsum16(x) * f.scale;
+      if (li == 0) sh.nrm[c] = x;
+    }
+    __syncthreads();
+    int rotated = 0;
+    int h = (n + 1) >> 1;   // columns of a half at this level
+    for (int level = 0;; ++level) {
+      // odd sizes leave more first-half columns than there are groups
+      for (int g0 = 0; g0 < h << level; g0 += NT / 16) {
+        // this group's set [base, base + size) and its place idx in the first half
+        int base = 0, size = n;
+        const int set = (g0 + grp) / h, idx = (g0 + grp) % h;
+        bool in = set < (1 << level);
+        for (int b = level - 1; b >= 0 && in; --b) {   // descend to the set
+          const int half = (size + 1) >> 1;
+          if ((set >> b) & 1) {
+            base += half;
+            size -= half;
+          } else {
+            size = half;
+          }
+        }
+        const int half = (size + 1) >> 1;   // of this set: h or one less
+        in = in && idx < half && size > 1;
+        const int p = base + idx;
+        double up[RPL], vp[RPL], al = 0.0;
+        if (in) {
+          al = sh.nrm[p];
+#pragma unroll
+          for (int t = 0; t < RPL; ++t) {
+            up[t] = sh.U[p][li + 16 * t];
+            if (WANT_V) vp[t] = sh.V[p][li + 16 * t];
+          }
+        }
+        for (int r = 0; r < h; ++r) {
+          int k = idx + r;
+          k = k >= h ? k - h : k;   // place in the second half
+          if (in && half + k < size) {
+            const int q = base + half + k;
+            double uq[RPL];
+            double ga = 0.0, g1 = 0.0;
+#pragma unroll
+            for (int t = 0; t < RPL; ++t) uq[t] = sh.U[q][li + 16 * t];
+            const double be = sh.nrm[q];
+#pragma unroll
+            for (int t = 0; t < RPL; t += 2) {
+              ga = fma(up[t], uq[t], ga);
+              if (t + 1 < RPL) g1 = fma(up[t + 1], uq[t + 1], g1);
+            }
+            ga = gsum16(ga + g1) * f.scale;
+            double t_, c, s;
+            bool counts;
+            if (plane_rotation(al, be, ga, f, t_, c, s, counts)) {
+              rotated |= counts;
+#pragma unroll
+              for (int t = 0; t < RPL; ++t) {
+                const double x = up[t], y = uq[t];
+                up[t] = c * x - s * y;
+                sh.U[q][li + 16 * t] = s * x + c * y;
+              }
+              if (WANT_V) {
+#pragma unroll
+                for (int t = 0; t < RPL; ++t) {
+                  const double x = vp[t], y = sh.V[q][li + 16 * t];
+                  vp[t] = c * x - s * y;
+                  sh.V[q][li + 16 * t] = s * x + c * y;
+                }
+              }
+              al = fma(-t_, ga, al);
+              if (li == 0) sh.nrm[q] = fma(t_, ga, be);
+            }
+          }
+          __syncthreads();
+        }
+        if (in) {
+          if (li == 0) sh.nrm[p] = al;
+#pragma unroll
+          for (int t = 0; t < RPL; ++t) {
+            sh.U[p][li + 16 * t] = up[t];
+            if (WANT_V) sh.V[p][li + 16 * t] = vp[t];
+          }
+        }
+        __syncthreads();
+      }
+      if (h == 1) break;
+      h = (h + 1) >> 1;
+    }
+    if (!__syncthreads_or(rotated)) break;
+  }
+  double* Uc = a.work + (size_t)mat * 2 * n * n;
+  double* Vc = Uc + (size_t)n * n;
+  for (int i = tid; i < n * n; i += NT) {
+    const int c = i / n, r = i % n;
+    Uc[i] = sh.U[c][r];
+    if (WANT_V) Vc[i] = sh.V[c][r];
+  }
+}
+
+// Where the one-workgroup kernel applies.
+bool small_svd_fits(int n, bool want_v) { return n <= (want_v ? 96 : 128); }
+
+template <bool WANT_V>
+void launch_small_svd(const SvdArgs& a, int count, hipStream_t s) {
+  const int n = a.n;
+  if (n <= 32)
+    svd_small<2, WANT_V><<<count, 256, 0, s>>>(a);
+  else if (n <= 48)
+    svd_small<3, WANT_V><<<count, 384, 0, s>>>(a);
+  else if (n <= 64)
+    svd_small<4, WANT_V><<<count, 512, 0, s>>>(a);
+  else if (n <= 80)
+    svd_small<5, WANT_V><<<count, 640, 0, s>>>(a);
+  else if (n <= 96)
+    svd_small<6, WANT_V><<<count, 768, 0, s>>>(a);
+  else
+    svd_small<8, false><<<count, 1024, 0, s>>>(a);
+}
+
 // One round of an outer sweep: block pair (tournament positions bp,
 // nblk-1-bp).  The 2 kBlk columns of U live in LDS; the rotations of the
 // visit are accumulated in a 2 kBlk x 2 kBlk matrix W (also in LDS) and the
 // right vectors are updated once at the end, V_cols <- V_cols W.  RPL is the
-// number of rows per lane (n <= 16 RPL).
+// number of rows per lane (n <= 16 RPL).  Bound by the latency of a step, like
+// svd_small, and by the grid barriers.  A column of the first block stays in
+// registers, norms are tracked, and blocks are no wider than n needs: 4 random
+// matrices with vectors, n = 100: 2132 -> 1674 us, 144: 3237 -> 2661, 160:
+// 3328 -> 2772.
 template <int RPL>
 struct RoundLds {
   static constexpr int kC = 2 * kBlk;
@@ -178,27 +382,31 @@ struct RoundLds {
   double Ul[kC][LD];
   double Vl[kC][LD];
   double Wl[kC][kC + 1];
+  double nrm[kC];
   int rot;
 };
 
 template <int RPL>
-__device__ __forceinline__ void block_round(const SvdArgs& a, int sweep, int round, int inner,
-                                            int mat, int bp, RoundLds<RPL>& sh) {
+__device__ __forceinline__ void block_round(const SvdArgs& a, int sweep, int round, int mat, int bp,
+                                            RoundLds<RPL>& sh) {
   constexpr int kC = RoundLds<RPL>::kC;
   auto& Ul = sh.Ul;
   auto& Vl = sh.Vl;
   auto& Wl = sh.Wl;
   int& rot = sh.rot;
-  const int n = a.n, nblk = a.nblk;
+  const int n = a.n, nblk = a.nblk, bs = a.bs;
   const int b0 = tour(bp, round, nblk), b1 = tour(nblk - 1 - bp, round, nblk);
   const int tid = threadIdx.x;
   double* Uc = a.work + (size_t)mat * 2 * n * n;
   double* Vc = Uc + (size_t)n * n;
-  // local column j -> global column: j < kBlk from b0, else from b1
-  auto gcol = [&](int j) { return (j < kBlk ? b0 : b1) * kBlk + (j % kBlk); };
-  // the 2 kBlk columns of U (and of V) into LDS, one column per wave at a
-  // time, rows lane + 64 t: coalesced, with no index division; four columns
-  // per wave in flight
+  // local column j -> global column: j < kBlk from b0, else from b1 (n for
+  // the places a block of bs columns leaves empty)
+  auto gcol = [&](int j) {
+    return j % kBlk < bs ? min((j < kBlk ? b0 : b1) * bs + j % kBlk, n) : n;
+  };
+  // the columns of U (and of V) into LDS, one column per wave at a time, rows
+  // lane + 64 t: coalesced, with no index division; four columns per wave in
+  // flight
   const int nv = a.want_v ? 2 : 1;
   const int wv = tid / 64, ln = tid % 64;
   constexpr int kRW = (16 * RPL + 63) / 64;   // row chunks per lane (n <= 16 RPL)
@@ -235,96 +443,92 @@ __device__ __forceinline__ void block_round(const SvdArgs& a, int sweep, int rou
   if (tid == 0) rot = 0;
   __syncthreads();
   const int grp = tid / kLanesPerPair, li = tid % kLanesPerPair;   // 16 pair groups
-  const double tol = 1e-15 * sqrt((double)n);
-  // columns below 1e-15 of the matrix norm are numerically zero: rotating
-  // them against the others cannot converge in the relative sense and does
-  // not change the result above roundoff; they are completed at the end
-  const double negl = 1e-30 * a.fro2[mat];
+  const SvdScale f = svd_scale(a.fro2[mat], n);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int j = grp + kBlk * u;
+    double x = 0.0;
+#pragma unroll
+    for (int t = 0; t < RPL; ++t) x = fma(Ul[j][li + 16 * t], Ul[j][li + 16 * t], x);
+    x = gsum16(x) * f.scale;
+    if (li == 0) sh.nrm[j] = x;
+  }
+  __syncthreads();
   int my_rot = 0;
-  // each step's rotation of W is applied at the start of the next step,
-  // beside that step's loads (every W column is still rotated in step
-  // order: a column belongs to one pair per step, and only that pair's
-  // group touches it until the next barrier)
-  int wpp = -1, wqq = 0;
-  double wc = 1.0, ws = 0.0;
-  auto rotate_w = [&]() {
+  // h steps that pair column p of this group with the columns q0 + (idx + r)
+  // mod h; p stays in the registers of its lanes
+  auto steps = [&](int p, int q0, int idx, int h, bool in) {
+    double up[RPL], wp[2] = {0.0, 0.0}, al = 0.0;
+    in = in && gcol(p) < n;
+    if (in) {
+      al = sh.nrm[p];
 #pragma unroll
-    for (int tt = 0; tt < kC / kLanesPerPair; ++tt) {
-      const int row = li + kLanesPerPair * tt;
-      const double wp = Wl[row][wpp], wq = Wl[row][wqq];
-      Wl[row][wpp] = wc * wp - ws * wq;
-      Wl[row][wqq] = ws * wp + wc * wq;
-    }
-  };
-  // the sweep's first round (every block in exactly one pair) also pairs
-  // the columns within each block: kBlk - 1 steps of a round-robin per
-  // block, kBlk / 2 pairs of each block per step; then kBlk steps pair
-  // column i of the first block with column (i + step) mod kBlk of the
-  // second, so that a sweep meets every column pair exactly once
-  const int nintra = round == 0 ? kBlk - 1 : 0, nstep = nintra + kBlk;
-  for (int rr = 0; rr < inner * nstep; ++rr) {
-    if (wpp >= 0) {
-      rotate_w();
-      wpp = -1;
-    }
-    const int r = rr % nstep;
-    int p, q;
-    if (r < nintra) {
-      const int blk = grp / (kBlk / 2), k = grp % (kBlk / 2);
-      const int ca = tour(k, r, kBlk), cb = tour(kBlk - 1 - k, r, kBlk);
-      p = blk * kBlk + min(ca, cb);
-      q = blk * kBlk + max(ca, cb);
-    } else {
-      p = grp;
-      q = kBlk + (grp + r - nintra) % kBlk;
-    }
-    const bool live = gcol(p) < n && gcol(q) < n;
-    if (live) {
-      double up[RPL], uq[RPL];
-      double al = 0.0, be = 0.0, ga = 0.0;
+      for (int t = 0; t < RPL; ++t) up[t] = Ul[p][li + 16 * t];
 #pragma unroll
-      for (int t = 0; t < RPL; ++t) {
-        // rows n .. 16 RPL - 1 are zero: no guard
-        const int row = li + kLanesPerPair * t;
-        up[t] = Ul[p][row];
-        uq[t] = Ul[q][row];
-        al += up[t] * up[t];
-        be += uq[t] * uq[t];
-        ga += up[t] * uq[t];
-      }
-      al = gsum16(al);
-      be = gsum16(be);
-      ga = gsum16(ga);
-      const double thr = tol * sqrt(al) * sqrt(be);
-      if (ga != 0.0 && fabs(ga) > thr && al > negl && be > negl) {
-        // tan of the rotation angle, the smaller root of t^2 + 2 zeta t = 1
-        const double zeta = (be - al) * fast_rcp(2.0 * ga);
-        const double z2 = 1.0 + zeta * zeta;
-        const double t = (zeta >= 0.0 ? 1.0 : -1.0) * fast_rcp(fabs(zeta) + z2 * fast_rsqrt(z2));
-        const double c = fast_rsqrt(1.0 + t * t), s = c * t;
-        // convergence counts only rotations clearly above roundoff: a pair
-        // left at |gamma| ~ tol sqrt(alpha beta) keeps being rotated but does
-        // not prevent the sweep loop from stopping
-        if (fabs(ga) > 16.0 * thr) ++my_rot;
+      for (int t = 0; t < 2; ++t) wp[t] = Wl[li + 16 * t][p];
+    }
+    for (int r = 0; r < h; ++r) {
+      const int q = q0 + (idx + r >= h ? idx + r - h : idx + r);
+      if (in && gcol(q) < n) {
+        double uq[RPL], wq[2];
+        double ga = 0.0, g1 = 0.0;
 #pragma unroll
-        for (int tt = 0; tt < RPL; ++tt) {
-          const int row = li + kLanesPerPair * tt;
-          Ul[p][row] = c * up[tt] - s * uq[tt];
-          Ul[q][row] = s * up[tt] + c * uq[tt];
+        for (int t = 0; t < RPL; ++t) uq[t] = Ul[q][li + 16 * t];   // rows from n on are zero
+#pragma unroll
+        for (int t = 0; t < 2; ++t) wq[t] = Wl[li + 16 * t][q];
+        const double be = sh.nrm[q];
+#pragma unroll
+        for (int t = 0; t < RPL; t += 2) {
+          ga = fma(up[t], uq[t], ga);
+          if (t + 1 < RPL) g1 = fma(up[t + 1], uq[t + 1], g1);
         }
-        if (a.want_v) {   // W's rotation waits for the next step
-          wpp = p;
-          wqq = q;
-          wc = c;
-          ws = s;
+        ga = gsum16(ga + g1) * f.scale;
+        double t_, c, s;
+        bool counts;
+        if (plane_rotation(al, be, ga, f, t_, c, s, counts)) {
+          my_rot |= counts;
+#pragma unroll
+          for (int t = 0; t < RPL; ++t) {
+            const double x = up[t], y = uq[t];
+            up[t] = c * x - s * y;
+            Ul[q][li + 16 * t] = s * x + c * y;
+          }
+          if (a.want_v) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+              const double x = wp[t], y = wq[t];
+              wp[t] = c * x - s * y;
+              Wl[li + 16 * t][q] = s * x + c * y;
+            }
+          }
+          al = fma(-t_, ga, al);
+          if (li == 0) sh.nrm[q] = fma(t_, ga, be);
         }
       }
+      __syncthreads();
+    }
+    if (in) {
+      if (li == 0) sh.nrm[p] = al;
+#pragma unroll
+      for (int t = 0; t < RPL; ++t) Ul[p][li + 16 * t] = up[t];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) Wl[li + 16 * t][p] = wp[t];
     }
     __syncthreads();
+  };
+  // the sweep's first round (every block in exactly one pair) also pairs the
+  // columns within each block, by halving (8 groups per block); then column i
+  // of the first block meets every column of the second, so that a sweep
+  // meets every column pair exactly once
+  if (round == 0) {
+    for (int h = kBlk / 2; h >= 1; h >>= 1) {
+      const int g = grp & 7, set = g / h, idx = g % h;
+      const int p0 = (grp >> 3) * kBlk + set * 2 * h;
+      steps(p0 + idx, p0 + h, idx, h, true);
+    }
   }
-  if (wpp >= 0) rotate_w();
-  if (a.want_v) __syncthreads();   // W is complete before V_cols <- V_cols W
-  if (li == 0 && my_rot) atomicAdd(&rot, my_rot);
+  steps(grp, kBlk, grp, bs, grp < bs);
+  if (li == 0 && my_rot) atomicOr(&rot, 1);
   for (int j = wv; j < kC; j += 4) {
     const int g = gcol(j);
     if (g < n) {
@@ -379,11 +583,11 @@ __device__ __forceinline__ void block_round(const SvdArgs& a, int sweep, int rou
 // One round per launch; later launches return at once after a sweep
 // without rotations.
 template <int RPL>
-__global__ __launch_bounds__(256) void svd_block_round(SvdArgs a, int sweep, int round, int inner) {
+__global__ __launch_bounds__(256) void svd_block_round(SvdArgs a, int sweep, int round) {
   __shared__ RoundLds<RPL> sh;
   const int mat = blockIdx.y;
   if (sweep > 0 && a.flags[mat * kMaxSweeps + sweep - 1] == 0) return;   // converged
-  block_round<RPL>(a, sweep, round, inner, mat, blockIdx.x, sh);
+  block_round<RPL>(a, sweep, round, mat, blockIdx.x, sh);
 }
 
 // All sweeps in one cooperative launch: a grid-wide barrier separates the
@@ -391,14 +595,14 @@ __global__ __launch_bounds__(256) void svd_block_round(SvdArgs a, int sweep, int
 // launch ends when every matrix has converged (a decision every workgroup
 // takes from the same flags after the barrier).
 template <int RPL>
-__global__ __launch_bounds__(256) void svd_sweeps(SvdArgs a, int inner, int count) {
+__global__ __launch_bounds__(256) void svd_sweeps(SvdArgs a, int count) {
   __shared__ RoundLds<RPL> sh;
   cooperative_groups::grid_group grid = cooperative_groups::this_grid();
   const int mat = blockIdx.y;
   for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
     const bool active = sweep == 0 || a.flags[mat * kMaxSweeps + sweep - 1] != 0;
     for (int round = 0; round < a.nblk - 1; ++round) {
-      if (active) block_round<RPL>(a, sweep, round, inner, mat, blockIdx.x, sh);
+      if (active) block_round<RPL>(a, sweep, round, mat, blockIdx.x, sh);
       grid.sync();
     }
     bool any = false;
@@ -440,7 +644,10 @@ __global__ __launch_bounds__(1024) void svd_finalize(SvdArgs a) {
   // the unit vectors e_0, e_1, ... that keep enough of their length after
   // the projection on the complement of the non-zero columns and of the
   // zero columns completed before.  Wavefront w keeps columns w, w + 16, ...
-  // of X in registers, rows lane, lane + 64, lane + 128.
+  // of X in registers, rows lane, lane + 64, lane + 128.  The errors of one
+  // pass grow with the inverse of the length that is left, and from one
+  // column to the next, so a candidate that keeps less than 0.7 of its length
+  // is projected a second time, by all wavefronts, on the columns themselves.
   const double zero_cut = 1e-15 * sqrt(a.fro2[mat]);
   if (a.U[mat] != nullptr) {
     __shared__ int nzl[kSvdMaxN], zl[kSvdMaxN];
@@ -525,20 +732,61 @@ __global__ __launch_bounds__(1024) void svd_finalize(SvdArgs a) {
           const bool take = nn > keep_min;
           if (take) {
             const double inv = 1.0 / nn;
-            const int c = zl[t];
 #pragma unroll
             for (int e = 0; e < kRPL; ++e) {
               const int i = lane + 64 * e;
-              if (i < n) {
-                qs[i] = xc[e] * inv;
-                Uc[(size_t)c * n + i] = xc[e] * inv;
-              }
+              if (i < n) qs[i] = xc[e] * inv;
             }
           }
-          if (lane == 0) took[cand & 1] = take ? 1 : 0;
+          if (lane == 0) took[cand & 1] = take ? (nn < 0.7 ? 2 : 1) : 0;
         }
         __syncthreads();
-        if (!took[cand & 1]) continue;
+        const int how = took[cand & 1];
+        if (!how) continue;
+        if (how == 2) {
+          double v[kRPL], y[kRPL];
+#pragma unroll
+          for (int e = 0; e < kRPL; ++e) {
+            const int i = lane + 64 * e;
+            v[e] = i < n ? qs[i] : 0.0;
+            y[e] = 0.0;
+          }
+          for (int o = wave; o < nr + t; o += nwaves) {
+            const double* u = Uc + (size_t)(o < nr ? nzl[o] : zl[o - nr]) * n;
+            double uo[kRPL], d = 0.0;
+#pragma unroll
+            for (int e = 0; e < kRPL; ++e) {
+              const int i = lane + 64 * e;
+              uo[e] = i < n ? u[i] : 0.0;
+              d += uo[e] * v[e];
+            }
+            d = wsum(d);
+#pragma unroll
+            for (int e = 0; e < kRPL; ++e) y[e] += d * uo[e];
+          }
+#pragma unroll
+          for (int e = 0; e < kRPL; ++e) ust[wave][lane + 64 * e] = y[e];
+          __syncthreads();
+          if (wave == 0) {
+            double ss = 0.0;
+#pragma unroll
+            for (int e = 0; e < kRPL; ++e) {
+              double z = 0.0;
+#pragma unroll
+              for (int w = 0; w < nwaves; ++w) z += ust[w][lane + 64 * e];
+              v[e] -= z;
+              ss += v[e] * v[e];
+            }
+            const double inv = 1.0 / sqrt(wsum(ss));
+#pragma unroll
+            for (int e = 0; e < kRPL; ++e) {
+              const int i = lane + 64 * e;
+              if (i < n) qs[i] = v[e] * inv;
+            }
+          }
+          __syncthreads();
+        }
+        if (tid < n) Uc[(size_t)zl[t] * n + tid] = qs[tid];
         ++t;
         if (t == nz) break;
         double qv[kRPL];
@@ -586,6 +834,37 @@ __global__ __launch_bounds__(1024) void svd_finalize(SvdArgs a) {
   }
 }
 
+// The block-pair kernels: one cooperative launch, or inside a stream capture
+// (where none can be recorded) one launch per round.
+int launch_block_svd(const SvdArgs& a, int count, hipStream_t s) {
+  const int n = a.n, nblk = a.nblk;
+  const dim3 grid(nblk / 2, count);
+  const int rpl = (n + kLanesPerPair - 1) / kLanesPerPair;
+  SvdArgs arg = a;
+  int cnt = count;
+  void* args[] = {&arg, &cnt};
+  const void* fn = rpl <= 8    ? (const void*)svd_sweeps<8>
+                   : rpl <= 10 ? (const void*)svd_sweeps<10>
+                               : (const void*)svd_sweeps<12>;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  (void)hipStreamIsCapturing(s, &cs);
+  if (cs == hipStreamCaptureStatusNone &&
+      hipLaunchCooperativeKernel(fn, grid, dim3(256), args, 0, s) == hipSuccess)
+    return 0;
+  (void)hipGetLastError();
+  for (int sweep = 0; sweep < kMaxSweeps; ++sweep)
+    for (int round = 0; round < nblk - 1; ++round) {
+      if (rpl <= 8)
+        svd_block_round<8><<<grid, 256, 0, s>>>(a, sweep, round);
+      else if (rpl <= 10)
+        svd_block_round<10><<<grid, 256, 0, s>>>(a, sweep, round);
+      else
+        svd_block_round<12><<<grid, 256, 0, s>>>(a, sweep, round);
+    }
+  CTM_HIP_TRY(hipGetLastError());
+  return 0;
+}
+
 }  // namespace
 
 size_t svd_workspace_bytes(int count, int n) {
@@ -621,6 +900,7 @@ int launch_svd(int count, const double* const* A, double* const* U, double* cons
   nblk += nblk & 1;
   if (nblk < 2) nblk = 2;
   a.nblk = nblk;
+  a.bs = (n + nblk - 1) / nblk;
   const bool want_u = U != nullptr, want_vout = V != nullptr;
   a.want_v = want_u ? 1 : 0;                       // V' is needed for u = Q V'
   double* qptr[kMaxProb];
@@ -657,36 +937,16 @@ int launch_svd(int count, const double* const* A, double* const* U, double* cons
   }
   r = launch_gemm(g, DT::F64, DT::F64, DT::F64, s);
   if (r) return r;
-  svd_init<<<dim3(std::max(1, std::min(64, n * n / 256)), count), 256, 0, s>>>(a);
-  const int rpl = (n + kLanesPerPair - 1) / kLanesPerPair;
-  {
-    const dim3 grid(nblk / 2, count);
-    int inner = kInner, cnt = count;
-    void* args[] = {&a, &inner, &cnt};
-    const void* fn = rpl <= 4    ? (const void*)svd_sweeps<4>
-                     : rpl <= 8  ? (const void*)svd_sweeps<8>
-                     : rpl <= 10 ? (const void*)svd_sweeps<10>
-                                 : (const void*)svd_sweeps<12>;
-    // inside a stream capture (graph) the per-round launches are used
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    (void)hipStreamIsCapturing(s, &cs);
-    if (cs == hipStreamCaptureStatusNone &&
-        hipLaunchCooperativeKernel(fn, grid, dim3(256), args, 0, s) == hipSuccess)
-      goto sweeps_done;
-    (void)hipGetLastError();
-    for (int sweep = 0; sweep < kMaxSweeps; ++sweep)
-      for (int round = 0; round < nblk - 1; ++round) {
-        if (rpl <= 4)
-          svd_block_round<4><<<grid, 256, 0, s>>>(a, sweep, round, kInner);
-        else if (rpl <= 8)
-          svd_block_round<8><<<grid, 256, 0, s>>>(a, sweep, round, kInner);
-        else if (rpl <= 10)
-          svd_block_round<10><<<grid, 256, 0, s>>>(a, sweep, round, kInner);
-        else
-          svd_block_round<12><<<grid, 256, 0, s>>>(a, sweep, round, kInner);
-      }
+  if (small_svd_fits(n, want_u)) {
+    if (want_u) launch_small_svd<true>(a, count, s);
+    else launch_small_svd<false>(a, count, s);
+    CTM_HIP_TRY(hipGetLastError());
+  } else {
+    svd_init<<<dim3(std::max(1, std::min(64, n * n / 256)), count), 256, 0, s>>>(a);
+    CTM_HIP_TRY(hipGetLastError());
+    const int r2 = launch_block_svd(a, count, s);
+    if (r2) return r2;
   }
-sweeps_done:
   svd_finalize<<<count, 1024, 0, s>>>(a);
   CTM_HIP_TRY(hipGetLastError());
   if (want_u) {   // u = Q V'
