@@ -121,9 +121,9 @@ int check_gemm(ctm_cell* c, const GemmBatch& g) {
   return 0;
 }
 
-// Launches a float64 GEMM: the split kernel of the SI applications wherever
-// it applies (thin products with long K: the SI applications, rho, the
-// corner and edge renormalisations), else the tile kernels.
+// Launches a float64 GEMM: the split kernel where K is long (the SI
+// applications, rho, the corner and edge renormalisations), else the tile
+// kernels.
 int run(ctm_cell* c, const GemmBatch& g) {
   if (g.count == 0) return 0;
   CTRY(check_gemm(c, g));

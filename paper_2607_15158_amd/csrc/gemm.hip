@@ -576,8 +576,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 512 / (64 * WGM * WGN)) void gemm_s
 }
 
 // ---------------------------------------------------------------------------
-// Split products for the SI applications (stream-K style): C = op(A) B with
-// N <= 160 and long K.  A launch of one tile per workgroup leaves CUs idle or
+// Split products (stream-K style): C = op(A) B with long K.  A launch of one tile per workgroup leaves CUs idle or
 // half loaded when the tiles do not fill the chip evenly.  Here one workgroup
 // of 8 wavefronts per CU takes an equal, contiguous range of the (tile,
 // 16-wide K slice) space.  A tile inside one range is written directly; a
@@ -587,17 +586,19 @@ __global__ __launch_bounds__(64 * WGM * WGN, 512 / (64 * WGM * WGN)) void gemm_s
 // ---------------------------------------------------------------------------
 struct StreamK {
   int nslices;    // BK-slices of K per tile
-  int tiles_m;
+  int tiles_m, tiles_n;
   int nwg;        // workgroups (ranges) of the main kernel
-  int per, rem;   // slices per range; the first `rem` ranges have one more
+  int per, rem;   // units per range; the first `rem` ranges have one more
+  int unit;       // slices per unit: 1, or nslices where no tile is cut
   double* part;   // 2 * nwg partial BM x BN tiles (row-major)
 };
 
 __device__ __forceinline__ int sk_begin(int w, const StreamK& sk) {
-  return w * sk.per + min(w, sk.rem);
+  return (w * sk.per + min(w, sk.rem)) * sk.unit;
 }
 
 __device__ __forceinline__ int sk_owner(int p, const StreamK& sk) {
+  p /= sk.unit;
   const int wide = sk.rem * (sk.per + 1);
   return p < wide ? p / (sk.per + 1) : sk.rem + (p - wide) / sk.per;
 }
@@ -637,10 +638,11 @@ struct SkTile {
   static constexpr int kof(int t) { return 8 * (t >> 1) + (t & 1); }
 };
 
-// acc += op(A)[m0 .. m0+BM) x B over the K slices [s0, s1) of problem prob.
+// acc += op(A)[m0 .. m0+BM) x B[.. n0 .. n0+BN) over the K slices [s0, s1) of
+// problem prob (n0 < N, even).
 // ONE: N == 1 (B has no pairs of columns).
 template <int MI, int NI, int WN, bool TRANS, bool ONE>
-__device__ __forceinline__ void sk_segment(const GemmBatch& g, int prob, int m0, int s0, int s1,
+__device__ __forceinline__ void sk_segment(const GemmBatch& g, int prob, int m0, int n0, int s0, int s1,
                                            double (*Bs)[16][SkTile<MI, NI, WN>::LB],
                                            v4d (&acc)[MI][NI]) {
   using S = SkTile<MI, NI, WN>;
@@ -697,11 +699,11 @@ __device__ __forceinline__ void sk_segment(const GemmBatch& g, int prob, int m0,
 #pragma unroll
   for (int e = 0; e < S::VB; ++e) {
     const int i = min(tid + e * S::NT, S::NB - 1);
-    const int kk = i / (S::BN / 2), n = 2 * (i % (S::BN / 2));
+    const int kk = i / (S::BN / 2), nl = 2 * (i % (S::BN / 2)), n = n0 + nl;
     second[e] = !ONE && n + 1 == N;
-    pb[e] = B + (long)(s0 * BK + kk) * ldb + (n + 1 < N ? n : second[e] ? n - 1 : 0);
+    pb[e] = B + (long)(s0 * BK + kk) * ldb + (n + 1 < N ? n : second[e] ? n - 1 : ONE ? 0 : N - 2);
     kb[e] = kk;
-    lb[e] = kk * S::LB + n;
+    lb[e] = kk * S::LB + nl;
   }
   const long bstep = BK * ldb;
   auto ld_b = [&](const double* q) {
@@ -825,16 +827,17 @@ __global__ __launch_bounds__(512, 2) void gemm_streamk_f64(GemmBatch g, StreamK 
     const int tile = (pend - 1) / sk.nslices;
     const int pos = max(tile * sk.nslices, begin);
     const int s0 = pos - tile * sk.nslices, s1 = pend - tile * sk.nslices;
-    const int prob = tile / sk.tiles_m, m0 = (tile % sk.tiles_m) * BM;
+    const int col = tile / sk.tiles_m, m0 = (tile % sk.tiles_m) * BM;
+    const int prob = col / sk.tiles_n, n0 = (col % sk.tiles_n) * BN;
     v4d acc[MI][NI];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NI; ++j) acc[i][j] = v4d{0, 0, 0, 0};
     if (g.transA[prob])
-      sk_segment<MI, NI, WN, true, ONE>(g, prob, m0, s0, s1, Bs, acc);
+      sk_segment<MI, NI, WN, true, ONE>(g, prob, m0, n0, s0, s1, Bs, acc);
     else
-      sk_segment<MI, NI, WN, false, ONE>(g, prob, m0, s0, s1, Bs, acc);
+      sk_segment<MI, NI, WN, false, ONE>(g, prob, m0, n0, s0, s1, Bs, acc);
     const int mw = wm * MI * 16 + (lane >> 4), nw = wn * NI * 16 + (lane & 15);
     if (s0 == 0 && s1 == sk.nslices) {
       // the whole tile: written here
@@ -843,7 +846,7 @@ __global__ __launch_bounds__(512, 2) void gemm_streamk_f64(GemmBatch g, StreamK 
       bool okn[NI];
 #pragma unroll
       for (int j = 0; j < NI; ++j) {
-        const int n = nw + j * 16;
+        const int n = n0 + nw + j * 16;
         okn[j] = n < N;
         offn[j] = okn[j] ? map2(n, g.cdiv_n, g.cs_n1, g.cs_n0) : 0;
       }
@@ -1093,14 +1096,15 @@ __global__ __launch_bounds__(256) void gemm_streamk_fixup(GemmBatch g, StreamK s
   const int t0 = tile * sk.nslices, t1 = t0 + sk.nslices;
   const int wf = sk_owner(t0, sk), wl = sk_owner(t1 - 1, sk);
   if (wf == wl) return;
-  const int prob = tile / sk.tiles_m, m0 = (tile % sk.tiles_m) * BM;
+  const int col = tile / sk.tiles_m, m0 = (tile % sk.tiles_m) * BM;
+  const int prob = col / sk.tiles_n, n0 = (col % sk.tiles_n) * BN;
   const int first_slot = sk_begin(wf, sk) < t0 ? 2 * wf + 1 : 2 * wf;
   double* C = (double*)g.C[prob];
   constexpr int PR = BN / 2;   // column pairs per row
   for (int q = threadIdx.x; q < kFixRows * PR; q += 256) {
-    const int ml = r0 + q / PR, n = 2 * (q % PR), m = m0 + ml;
+    const int ml = r0 + q / PR, nl = 2 * (q % PR), m = m0 + ml, n = n0 + nl;
     if (m >= g.M || n >= g.N) continue;
-    const double* P = sk.part + (long)ml * BN + n;
+    const double* P = sk.part + (long)ml * BN + nl;
     v2d v = *(const v2d*)(P + (long)first_slot * (BM * BN));
     int w = wf + 1;
     for (; w + 3 <= wl; w += 4) {
@@ -1645,47 +1649,126 @@ bool gemm_si_balanced_applies(const GemmBatch& g, const void* scratch, int ncu) 
   return gemm_si_balanced_useful(g.count, g.M, g.N, g.K, ncu);
 }
 
+// One of the tile shapes on the ranges of sk (nwg, per, rem and unit set).
 template <int MI, int NI, int WN, bool ONE = false>
-static int launch_streamk_f64(const GemmBatch& g, StreamK& sk, int ncu, hipStream_t s) {
+static int launch_streamk_f64(const GemmBatch& g, const StreamK& sk, hipStream_t s) {
   using S = SkTile<MI, NI, WN>;
   static_assert((size_t)S::BM * S::BN <= 192 * 160, "scratch slots");
-  sk.tiles_m = ceil_div(g.M, S::BM);
-  const int total = g.count * sk.tiles_m * sk.nslices;
-  sk.nwg = sk_ranges(total, ncu);
-  sk.per = total / sk.nwg;
-  sk.rem = total % sk.nwg;
   gemm_streamk_f64<MI, NI, WN, ONE><<<sk.nwg, S::NT, 0, s>>>(g, sk);
   CTM_HIP_TRY(hipGetLastError());
+  if (sk.unit > 1) return 0;   // no tile is cut
   gemm_streamk_fixup<S::BM, S::BN>
-      <<<g.count * sk.tiles_m * (S::BM / kFixRows), 256, 0, s>>>(g, sk);
+      <<<g.count * sk.tiles_m * sk.tiles_n * (S::BM / kFixRows), 256, 0, s>>>(g, sk);
   CTM_HIP_TRY(hipGetLastError());
   return 0;
+}
+
+// rows x cols: 128 or 256 rows with 16 to 112 columns, 192 with 128 or 160.
+static int launch_streamk_shape(const GemmBatch& g, const StreamK& sk, int rows, int cols, hipStream_t s) {
+  const bool tall = rows == 256;
+  if (rows == 192)
+    return cols == 160 ? launch_streamk_f64<3, 5, 2>(g, sk, s) : launch_streamk_f64<3, 4, 2>(g, sk, s);
+  if (g.N == 1)
+    return tall ? launch_streamk_f64<2, 1, 1, true>(g, sk, s) : launch_streamk_f64<1, 1, 1, true>(g, sk, s);
+  switch (cols / 16) {
+    case 1: return tall ? launch_streamk_f64<2, 1, 1>(g, sk, s) : launch_streamk_f64<1, 1, 1>(g, sk, s);
+    case 2: return tall ? launch_streamk_f64<2, 2, 1>(g, sk, s) : launch_streamk_f64<1, 2, 1>(g, sk, s);
+    case 3: return tall ? launch_streamk_f64<2, 3, 1>(g, sk, s) : launch_streamk_f64<1, 3, 1>(g, sk, s);
+    case 4: return tall ? launch_streamk_f64<2, 4, 1>(g, sk, s) : launch_streamk_f64<1, 4, 1>(g, sk, s);
+    case 5: return tall ? launch_streamk_f64<2, 5, 1>(g, sk, s) : launch_streamk_f64<1, 5, 1>(g, sk, s);
+    case 6: return tall ? launch_streamk_f64<2, 6, 1>(g, sk, s) : launch_streamk_f64<1, 6, 1>(g, sk, s);
+    default: return tall ? launch_streamk_f64<2, 7, 1>(g, sk, s) : launch_streamk_f64<1, 7, 1>(g, sk, s);
+  }
 }
 
 int launch_gemm_si_balanced(const GemmBatch& g, double* scratch, int ncu, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.count <= 0 || g.nbatch <= 0) return 0;
   if (!gemm_si_balanced_applies(g, scratch, ncu)) return launch_gemm_si(g, s);
+  const int rows = sk_rows(g.M, g.N);
   StreamK sk{};
   sk.nslices = ceil_div(g.K, 16);
   sk.part = scratch;
-  if (g.N > 128) return launch_streamk_f64<3, 5, 2>(g, sk, ncu, s);
-  if (g.N > 112) return launch_streamk_f64<3, 4, 2>(g, sk, ncu, s);
-  const bool tall = sk_rows(g.M, g.N) == 256;
-  if (g.N == 1)
-    return tall ? launch_streamk_f64<2, 1, 1, true>(g, sk, ncu, s) : launch_streamk_f64<1, 1, 1, true>(g, sk, ncu, s);
-  switch ((g.N + 15) / 16) {
-    case 1: return tall ? launch_streamk_f64<2, 1, 1>(g, sk, ncu, s) : launch_streamk_f64<1, 1, 1>(g, sk, ncu, s);
-    case 2: return tall ? launch_streamk_f64<2, 2, 1>(g, sk, ncu, s) : launch_streamk_f64<1, 2, 1>(g, sk, ncu, s);
-    case 3: return tall ? launch_streamk_f64<2, 3, 1>(g, sk, ncu, s) : launch_streamk_f64<1, 3, 1>(g, sk, ncu, s);
-    case 4: return tall ? launch_streamk_f64<2, 4, 1>(g, sk, ncu, s) : launch_streamk_f64<1, 4, 1>(g, sk, ncu, s);
-    case 5: return tall ? launch_streamk_f64<2, 5, 1>(g, sk, ncu, s) : launch_streamk_f64<1, 5, 1>(g, sk, ncu, s);
-    case 6: return tall ? launch_streamk_f64<2, 6, 1>(g, sk, ncu, s) : launch_streamk_f64<1, 6, 1>(g, sk, ncu, s);
-    default: return tall ? launch_streamk_f64<2, 7, 1>(g, sk, ncu, s) : launch_streamk_f64<1, 7, 1>(g, sk, ncu, s);
-  }
+  sk.tiles_m = ceil_div(g.M, rows);
+  sk.tiles_n = 1;
+  sk.unit = 1;
+  const int total = g.count * sk.tiles_m * sk.nslices;
+  sk.nwg = sk_ranges(total, ncu);
+  sk.per = total / sk.nwg;
+  sk.rem = total % sk.nwg;
+  return launch_streamk_shape(g, sk, rows, rows == 192 ? (g.N > 128 ? 160 : 128) : (g.N + 15) / 16 * 16, s);
 }
 
+// Tile and ranges of a split product of any width, by estimated cycles.  A
+// range of whole tiles needs no second kernel but leaves CUs idle where the
+// tiles do not divide evenly; cut ranges keep all busy and pay for the partial
+// tiles.  The constants are rounded from measured launches.  Products whose few
+// tiles each walked all of K on the tile kernels, before and after, us: 1024 x
+// 1024 x 1024 200 -> 50 (whole tiles of 128 x 32), four transposed 256 x 256 x
+// 4096 750 -> 44 + 9 for the second kernel (cut tiles of 256 x 32), 1024 x 64 x
+// 1024 185 -> 10 + 5, four 1024 x 1024 x 576 148 -> 98 (256 x 64), 4096 x 256 x
+// 256 29 -> 19.  Bound by the matrix cores where K is long (50 TF/s on these,
+// 61 on 192 x 160), else by the start of the ranges and the partial tiles.
+namespace {
+struct SplitPlan {
+  StreamK sk;
+  int rows, cols;
+  double cycles;
+};
+
+bool plan_split(const GemmBatch& g, bool cut_ok, int ncu, SplitPlan* best) {
+  best->cycles = 1e300;
+  const long ns = ceil_div(g.K, 16);
+  auto consider = [&](int rows, int cols) {
+    const int tm = ceil_div(g.M, rows), tn = ceil_div(g.N, cols);
+    const long tiles = (long)tm * tn * g.count;
+    if (tiles * ns > (1L << 30)) return;
+    // a slice: 2 matrix instructions of 64 cycles per SIMD, k step and 16 x 16
+    // block of a wavefront, at the rate they reach with the loads between
+    // them, and the barrier; or its operands from L2
+    const double blocks = (double)rows * cols / (128 * 16);
+    const double slice = std::max(620.0 * blocks + 800.0, (rows + cols) * 128.0 / 12.0);
+    auto take = [&](long nwg, long units, int unit, double extra) {
+      const double cyc = (double)((units + nwg - 1) / nwg) * unit * slice + extra;
+      if (cyc >= best->cycles) return;
+      best->cycles = cyc;
+      best->rows = rows;
+      best->cols = cols;
+      best->sk.nslices = (int)ns;
+      best->sk.tiles_m = tm;
+      best->sk.tiles_n = tn;
+      best->sk.nwg = (int)nwg;
+      best->sk.per = (int)(units / nwg);
+      best->sk.rem = (int)(units % nwg);
+      best->sk.unit = unit;
+    };
+    take(std::min<long>(tiles, ncu), tiles, (int)ns, 0.0);
+    const long nwg = sk_ranges(tiles * ns, ncu);
+    // the second kernel's launch, and the partials written and read
+    if (cut_ok && nwg >= 1) take(nwg, tiles * ns, 1, 14000.0 + (double)nwg * rows * cols * 16.0 / 1250.0);
+  };
+  for (int cols = 16; cols <= 112; cols += 16) {
+    consider(128, cols);
+    consider(256, cols);
+  }
+  consider(192, 128);
+  consider(192, 160);
+  return best->cycles < 1e300;
+}
+}  // namespace
+
+// Short K stays on the tile kernels (their tiles are smaller and hold several
+// workgroups per CU, which hides the ends of a tile; 256 x 1 x 256, where the
+// line lies, takes 10 to 14 us on either), and so do few rows, of which the
+// 128-row tiles would waste most, and inner batches, which have no range here.
 int launch_gemm_f64_any(const GemmBatch& g, double* scratch, int ncu, hipStream_t s) {
-  if (gemm_si_balanced_applies(g, scratch, ncu)) return launch_gemm_si_balanced(g, scratch, ncu, s);
+  if (g.M <= 0 || g.N <= 0 || g.count <= 0 || g.nbatch <= 0) return 0;
+  SplitPlan p{};
+  const bool cut_ok = scratch && ((uintptr_t)scratch & 15) == 0;
+  if (g.nbatch == 1 && g.M >= 64 && g.K >= 256 && ncu >= 1 && ncu <= kSplitMaxCus &&
+      plan_split(g, cut_ok, ncu, &p)) {
+    p.sk.part = scratch;
+    return launch_streamk_shape(g, p.sk, p.rows, p.cols, s);
+  }
   return launch_gemm(g, DT::F64, DT::F64, DT::F64, s);
 }
 
@@ -1710,6 +1793,8 @@ int launch_gemm_si_f32_balanced(const GemmBatch& g, double* scratch, int ncu, hi
   StreamK sk;
   sk.nslices = ceil_div(g.K, skf32::BK);
   sk.tiles_m = tm;
+  sk.tiles_n = 1;
+  sk.unit = 1;
   const int total = g.count * tm * sk.nslices;
   sk.nwg = ncu;
   sk.per = total / ncu;
