@@ -125,6 +125,10 @@ inline void gemm_set_rowmajor_c(GemmBatch& g, long ldc) {
 // Launches a batched GEMM; ta = element type of A, tb of B, tc of C.
 // Accumulation is float64 for F64 inputs and float32 otherwise.
 int launch_gemm(const GemmBatch& g, DT ta, DT tb, DT tc, hipStream_t s);
+// Whether a float64 product is small: its workgroups then split K over their
+// wavefronts.  launch_gemm, launch_gemm_si and launch_gemm_f64_any send such
+// products there; its bits do not depend on the grid either.
+bool gemm_short_applies(const GemmBatch& g);
 // float64 C = op(A) B with N <= 160 (the enlarged corner applied to an
 // isometry block); other shapes fall back to launch_gemm.
 int launch_gemm_si(const GemmBatch& g, hipStream_t s);
@@ -162,7 +166,8 @@ struct GroupItem {
   int tiles_m, tiles_n;
   long first;
 };
-// Tile kernel for a group (0: the 96 x 160 skinny tile, which needs N <= 160
+// Tile kernel for a group (below 0: small products, all of the group or none;
+// 0: the 96 x 160 skinny tile, which needs N <= 160
 // and 16-byte aligned rows in every descriptor; else an index into the
 // generic tile shapes), chosen from the descriptors.
 int grouped_kind(const GemmBatch* gs, int n);

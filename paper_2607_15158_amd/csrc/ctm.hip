@@ -483,7 +483,7 @@ int run_gemm(ctm_ctx* c, int cls, const GemmBatch& g0, DT ta, DT tb, DT tc, doub
   // thin float64 products with long K on the split kernel of the SI
   // applications (its own launch in a recorded batch: it sums cut tiles in
   // a fixed order of its own, so the product keeps the bits of a solo move)
-  if (ta == DT::F64 && tb == DT::F64 && tc == DT::F64 && !g.split &&
+  if (ta == DT::F64 && tb == DT::F64 && tc == DT::F64 && !g.split && !gemm_short_applies(g) &&
       gemm_si_balanced_applies(g, c->sk_part, c->sk_cus)) {
     double* part = c->sk_part;
     const int cus = c->sk_cus;
@@ -629,7 +629,7 @@ int apply_step(ctm_ctx* c, int count, const int* ci, const int* trans, double* c
     // the split kernel sums cut tiles in its own order: kept as its own launch
     // so that the product has the bits of a solo move; the tile kernels give
     // the same bits in any grid and are grouped
-    if (gemm_si_balanced_applies(g, c->sk_part, c->sk_cus)) {
+    if (!gemm_short_applies(g) && gemm_si_balanced_applies(g, c->sk_part, c->sk_cus)) {
       double* part = c->sk_part;
       const int cus = c->sk_cus;
       c->rec->push_back(BatchOp{false, GemmBatch{}, [=](hipStream_t st) {
@@ -652,6 +652,7 @@ int apply_step(ctm_ctx* c, int count, const int* ci, const int* trans, double* c
   const int chk = check_gemm(c, g, DT::F64, DT::F64, DT::F64);
   if (chk) return chk;
   ProfScope ps(c, PC_SI_APPLY, gemm_flops(g), bytes);
+  if (gemm_short_applies(g)) return launch_gemm_si(g, c->st);
   return launch_gemm_si_balanced(g, c->sk_part, c->sk_cus, c->st);
 }
 
@@ -1186,6 +1187,7 @@ int c4v_projectors(ctm_ctx* c, int mode, int keep) {
       const int chk = check_gemm(c, g, DT::F64, DT::F64, DT::F64);
       if (chk) return chk;
       ProfScope ps(c, PC_SI_APPLY, gemm_flops(g), (double)N1 * N1 * 8 + 2.0 * N1 * k * 8);
+      if (gemm_short_applies(g)) return launch_gemm_si(g, c->st);
       return launch_gemm_si_balanced(g, c->sk_part, c->sk_cus, c->st);
     };
     for (int step = 0; step < c->cfg.n_si; ++step) {
@@ -1492,8 +1494,8 @@ int drain(ctm_ctx* c) {
 // together).  Each context's SI move is recorded as its sequence of
 // operations; step i of every context is then launched together on one
 // stream: the float64 GEMMs of the step as one persistent grouped launch
-// over a device table of (descriptor, tile) work items, the other operations
-// one after another.  Contexts are independent, so only each context's own
+// over a device table of (descriptor, tile) work items (two where some are
+// small), the other operations one after another.  Contexts are independent, so only each context's own
 // order matters, and every product gets the bits of the solo move (the tile
 // kernels do not depend on the grid; the split SI kernel, whose summation
 // order does, keeps its own launch).
@@ -1568,12 +1570,14 @@ int enqueue_batch(ctm_ctx* const* ctxs, int n) {
   }
   // the grouped GEMMs of every step, in one table
   std::vector<GemmBatch> gs;
-  std::vector<std::pair<size_t, int>> span(steps);   // (first item, items) per step
-  std::vector<std::pair<long, int>> plan(steps);     // (work items, kind) per step
-  for (size_t t = 0; t < steps; ++t) {
+  // two groups per step: the small products, then the others
+  std::vector<std::pair<size_t, int>> span(2 * steps);   // (first item, items) per group
+  std::vector<std::pair<long, int>> plan(2 * steps);     // (work items, kind) per group
+  for (size_t t = 0; t < 2 * steps; ++t) {
     span[t] = {gs.size(), 0};
     for (auto& v : ops)
-      if (t < v.size() && v[t].gemm) gs.push_back(v[t].g);
+      if (t / 2 < v.size() && v[t / 2].gemm && gemm_short_applies(v[t / 2].g) == (t % 2 == 0))
+        gs.push_back(v[t / 2].g);
     span[t].second = (int)(gs.size() - span[t].first);
   }
   int dev = 0;
@@ -1598,7 +1602,7 @@ int enqueue_batch(ctm_ctx* const* ctxs, int n) {
       return restore(fail(nullptr, CTM_E_NOMEM, "descriptor table of the batched move"));
     tb.cap = cap;
   }
-  for (size_t t = 0; t < steps; ++t) {
+  for (size_t t = 0; t < 2 * steps; ++t) {
     const int cnt = span[t].second;
     if (!cnt) continue;
     const GemmBatch* g = gs.data() + span[t].first;
@@ -1609,9 +1613,10 @@ int enqueue_batch(ctm_ctx* const* ctxs, int n) {
     CTM_HIP_TRY(hipMemcpyAsync(tb.dev, tb.host, gs.size() * sizeof(GroupItem),
                                hipMemcpyHostToDevice, S));
   for (size_t t = 0; t < steps; ++t) {
-    if (span[t].second)
-      TRY_B(launch_gemm_grouped(tb.dev + span[t].first, span[t].second, plan[t].first,
-                                plan[t].second, S));
+    for (size_t u = 2 * t; u < 2 * t + 2; ++u)
+      if (span[u].second)
+        TRY_B(launch_gemm_grouped(tb.dev + span[u].first, span[u].second, plan[u].first,
+                                  plan[u].second, S));
     for (size_t i = 0; i < grp.size(); ++i)
       if (t < ops[i].size() && !ops[i][t].gemm) {
         const int r = ops[i][t].fn(S);

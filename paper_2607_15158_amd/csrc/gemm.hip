@@ -1144,6 +1144,112 @@ __global__ __launch_bounds__(64 * WGM * WGN, 512 / (64 * WGM * WGN)) void gemm_s
 }
 
 // ---------------------------------------------------------------------------
+// Small products: a workgroup of 8 wavefronts owns 16 rows and 16 NT columns
+// and splits K over the wavefronts (wavefront w takes the 16-wide slices w,
+// w + 8, ...), each with its operands straight from global memory to the
+// matrix cores' registers; the 8 partial tiles are summed in LDS in wavefront
+// order.  A product whose tiles do not fill the chip is bound by the latency
+// of one tile's walk over K, which this cuts to an eighth, in one launch.  The
+// bits depend on K alone, not on NT or the grid.
+// ---------------------------------------------------------------------------
+template <int NT>
+struct ShortTile {
+  static constexpr int LD = 16 * (NT | 1);   // two rows fall 32 banks apart
+  double red[8][16][LD];
+};
+
+template <int NT, bool TRANS>
+__device__ __forceinline__ void short_tile(const GemmBatch& g, int prob, int tm, int tn, ShortTile<NT>& sh) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+  const int M = g.M, N = g.N, K = g.K, m0 = tm * 16, n0 = tn * 16 * NT;
+  const long lda = g.lda, ldb = g.ldb;
+  const int m = min(m0 + li, M - 1);
+  const double* A = (const double*)g.A[prob] + (TRANS ? (long)m : (long)m * lda);
+  const double* B = (const double*)g.B[prob];
+  int nc[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) nc[j] = min(n0 + 16 * j + li, N - 1);
+  const int ns = (K + 15) >> 4, full = K >> 4;
+  // k of matrix instruction t of a slice: 2 lk + {0, 1, 8, 9}
+  auto load = [&](int s, double (&a)[4], double (&b)[4][NT]) {
+    const int k = 16 * s + 2 * lk;
+    if (s < full) {
+      if (TRANS) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) a[t] = A[(long)(k + 8 * (t >> 1) + (t & 1)) * lda];
+      } else {
+        const v2du x = *(const v2du*)(A + k), y = *(const v2du*)(A + k + 8);
+        a[0] = x.x;
+        a[1] = x.y;
+        a[2] = y.x;
+        a[3] = y.y;
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) b[t][j] = B[(long)(k + 8 * (t >> 1) + (t & 1)) * ldb + nc[j]];
+    } else {   // the partial slice
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int kk = k + 8 * (t >> 1) + (t & 1);
+        const bool in = kk < K;
+        a[t] = in ? A[TRANS ? (long)kk * lda : (long)kk] : 0.0;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) b[t][j] = in ? B[(long)kk * ldb + nc[j]] : 0.0;
+      }
+    }
+  };
+  v4d acc[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) acc[j] = v4d{0, 0, 0, 0};
+  double a[2][4], b[2][4][NT];
+  auto mul = [&](const double (&x)[4], const double (&y)[4][NT]) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[t], y[t][j], acc[j], 0, 0, 0);
+  };
+  int s = wave;
+  if (s < ns) load(s, a[0], b[0]);
+  for (; s < ns; s += 16) {
+    if (s + 8 < ns) load(s + 8, a[1], b[1]);
+    mul(a[0], b[0]);
+    if (s + 8 >= ns) break;
+    if (s + 16 < ns) load(s + 16, a[0], b[0]);
+    mul(a[1], b[1]);
+  }
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sh.red[wave][lk + 4 * r][16 * j + li] = acc[j][r];
+  __syncthreads();
+  double* C = (double*)g.C[prob];
+  for (int i = tid; i < 256 * NT; i += 512) {
+    const int r = i / (16 * NT), c = i % (16 * NT), mm = m0 + r, n = n0 + c;
+    if (mm >= M || n >= N) continue;
+    double v = sh.red[0][r][c];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) v += sh.red[w][r][c];
+    v *= g.alpha;
+    double* q = C + map2(mm, g.cdiv_m, g.cs_m1, g.cs_m0) + map2(n, g.cdiv_n, g.cs_n1, g.cs_n0);
+    *q = g.accumulate ? v + *q : v;
+  }
+}
+
+template <int NT>
+__global__ __launch_bounds__(512, 2) void gemm_short_f64(GemmBatch g, int tiles_m, int tiles_n) {
+  __shared__ ShortTile<NT> sh;
+  const int w = xcd_remap(blockIdx.x, gridDim.x);
+  const int per = tiles_m * tiles_n, prob = w / per, t = w % per;
+  if (g.transA[prob])
+    short_tile<NT, true>(g, prob, t / tiles_n, t % tiles_n, sh);
+  else
+    short_tile<NT, false>(g, prob, t / tiles_n, t % tiles_n, sh);
+}
+
+// ---------------------------------------------------------------------------
 // Grouped launches: the products of several GemmBatch descriptors of
 // different shapes (one per context of a batched move) in one persistent
 // launch.  The descriptors sit in device memory with the prefix sums of
@@ -1176,6 +1282,21 @@ __global__ __launch_bounds__(64 * WGM * WGN, 512 / (64 * WGM * WGN)) void gemm_s
       skinny_tile<BM, BN, WGM, WGN, true>(it.g, it.tiles_m, it.tiles_n, lin, As, Bs);
     else
       skinny_tile<BM, BN, WGM, WGN, false>(it.g, it.tiles_m, it.tiles_n, lin, As, Bs);
+  }
+}
+
+template <int NT>
+__global__ __launch_bounds__(512, 2) void gemm_short_grouped(const GroupItem* items, int nitems, long total) {
+  __shared__ ShortTile<NT> sh;
+  for (long w = blockIdx.x; w < total; w += gridDim.x) {
+    const GroupItem& it = items[group_of(items, nitems, w)];
+    const int lin = (int)(w - it.first), per = it.tiles_m * it.tiles_n;
+    const int prob = lin / per, t = lin % per;
+    if (it.g.transA[prob])
+      short_tile<NT, true>(it.g, prob, t / it.tiles_n, t % it.tiles_n, sh);
+    else
+      short_tile<NT, false>(it.g, prob, t / it.tiles_n, t % it.tiles_n, sh);
+    __syncthreads();   // the sums are read before the next item overwrites them
   }
 }
 
@@ -1562,9 +1683,60 @@ int launch_skinny(const GemmBatch& g, hipStream_t s) {
   return 0;
 }
 
+// Estimated cycles of small products with 16 NT columns per workgroup: the
+// longest wavefront's slices (two wavefronts share a SIMD) times the
+// workgroups a CU takes in turn.
+double short_cycles(const GemmBatch& g, int nt) {
+  const double wgs = (double)ceil_div(g.M, 16) * ceil_div(g.N, 16 * nt) * g.count;
+  return 4000.0 + ceil_div(ceil_div(g.K, 16), 8) * (600.0 + 512.0 * nt) * std::max(1.0, wgs / 256.0);
+}
+
+// Column blocks per workgroup that fit a set of small products best.
+int short_columns(const GemmBatch* gs, int n) {
+  int best = 1;
+  double cost = 1e300;
+  for (int nt = 1; nt <= 5; ++nt) {
+    double c = 0.0;
+    for (int i = 0; i < n; ++i) c += short_cycles(gs[i], nt);
+    if (c < cost) {
+      cost = c;
+      best = nt;
+    }
+  }
+  return best;
+}
+
+int launch_short(const GemmBatch& g, hipStream_t s) {
+  const int nt = short_columns(&g, 1);
+  const int tm = ceil_div(g.M, 16), tn = ceil_div(g.N, 16 * nt), wgs = tm * tn * g.count;
+  switch (nt) {
+    case 1: gemm_short_f64<1><<<wgs, 512, 0, s>>>(g, tm, tn); break;
+    case 2: gemm_short_f64<2><<<wgs, 512, 0, s>>>(g, tm, tn); break;
+    case 3: gemm_short_f64<3><<<wgs, 512, 0, s>>>(g, tm, tn); break;
+    case 4: gemm_short_f64<4><<<wgs, 512, 0, s>>>(g, tm, tn); break;
+    default: gemm_short_f64<5><<<wgs, 512, 0, s>>>(g, tm, tn); break;
+  }
+  CTM_HIP_TRY(hipGetLastError());
+  return 0;
+}
+
 }  // namespace
 
+// Up to about 40000 estimated cycles, where the split kernel's balance begins to
+// count for more than its second launch, and 2600 blocks of 16 x 16 (short K: the
+// operands come from L2 once per 16 rows, which wide products with their larger
+// tiles read less often).  Measured, us, on the kernels used before and here:
+// 8 of 32 x 20 x 32 11 and 3, 8 of 512 x 37 x 512 24 and 10, 105 x 105 x 2500
+// 27 and 15, 4 of 1024 x 64 x 1024 30 and 20, 1024 x 64 x 64 17 and 8; beyond the
+// line, 8 of 1024 x 72 x 1024 41 and 50, 1024 x 1024 x 64 10.5 and 17.
+bool gemm_short_applies(const GemmBatch& g) {
+  if (g.nbatch != 1 || g.split || g.M <= 0 || g.N <= 0 || g.count <= 0 || g.K <= 0) return false;
+  if ((double)ceil_div(g.M, 16) * ceil_div(g.N, 16) * g.count > 2600.0) return false;
+  return short_cycles(g, short_columns(&g, 1)) <= 40000.0;
+}
+
 int grouped_kind(const GemmBatch* gs, int n) {
+  if (n > 0 && gemm_short_applies(gs[0])) return -short_columns(gs, n);
   bool skinny = true;
   int big = 0;
   double most = -1.0;
@@ -1578,7 +1750,8 @@ int grouped_kind(const GemmBatch* gs, int n) {
 }
 
 long grouped_fill(const GemmBatch* gs, int n, int kind, GroupItem* items) {
-  const int bm = kind == 0 ? 96 : kTiles[kind - 1].bm, bn = kind == 0 ? 160 : kTiles[kind - 1].bn;
+  const int bm = kind < 0 ? 16 : kind == 0 ? 96 : kTiles[kind - 1].bm;
+  const int bn = kind < 0 ? -16 * kind : kind == 0 ? 160 : kTiles[kind - 1].bn;
   long total = 0;
   for (int i = 0; i < n; ++i) {
     items[i].g = gs[i];
@@ -1594,7 +1767,15 @@ int launch_gemm_grouped(const GroupItem* items, int n, long total, int kind, hip
   if (n <= 0 || total <= 0) return 0;
   // persistent grid: at most two workgroups per CU of 256
   const int grid = (int)std::min<long>(total, 512);
-  if (kind == 0) {
+  if (kind < 0) {
+    switch (-kind) {
+      case 1: gemm_short_grouped<1><<<grid, 512, 0, s>>>(items, n, total); break;
+      case 2: gemm_short_grouped<2><<<grid, 512, 0, s>>>(items, n, total); break;
+      case 3: gemm_short_grouped<3><<<grid, 512, 0, s>>>(items, n, total); break;
+      case 4: gemm_short_grouped<4><<<grid, 512, 0, s>>>(items, n, total); break;
+      default: gemm_short_grouped<5><<<grid, 512, 0, s>>>(items, n, total); break;
+    }
+  } else if (kind == 0) {
     gemm_skinny_grouped<96, 160, 2, 2><<<grid, 256, 0, s>>>(items, n, total);
   } else {
     switch (kind - 1) {
@@ -1612,6 +1793,7 @@ int launch_gemm_grouped(const GroupItem* items, int n, long total, int kind, hip
 
 int launch_gemm_si(const GemmBatch& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.count <= 0 || g.nbatch <= 0) return 0;
+  if (gemm_short_applies(g)) return launch_short(g, s);
   if (g.N > 160 || !skinny_ok(g)) return launch_gemm(g, DT::F64, DT::F64, DT::F64, s);
   return launch_skinny<96, 160, 2, 2, 1>(g, s);
 }
@@ -1764,7 +1946,7 @@ int launch_gemm_f64_any(const GemmBatch& g, double* scratch, int ncu, hipStream_
   if (g.M <= 0 || g.N <= 0 || g.count <= 0 || g.nbatch <= 0) return 0;
   SplitPlan p{};
   const bool cut_ok = scratch && ((uintptr_t)scratch & 15) == 0;
-  if (g.nbatch == 1 && g.M >= 64 && g.K >= 256 && ncu >= 1 && ncu <= kSplitMaxCus &&
+  if (!gemm_short_applies(g) && g.nbatch == 1 && g.M >= 64 && g.K >= 256 && ncu >= 1 && ncu <= kSplitMaxCus &&
       plan_split(g, cut_ok, ncu, &p)) {
     p.sk.part = scratch;
     return launch_streamk_shape(g, p.sk, p.rows, p.cols, s);
@@ -1887,6 +2069,7 @@ int launch_gemm(const GemmBatch& g, DT ta, DT tb, DT tc, hipStream_t s) {
   }
   if (ta == DT::F64 && tb == DT::F64) {
     int rc = 0;
+    if (tc == DT::F64 && gemm_short_applies(g)) return launch_short(g, s);
     if (tc == DT::F64 && launch_f64_db(g, s, &rc)) return rc;
     if (tc == DT::F64) return launch_k4<double, double, double, double>(g, s);
     if (tc == DT::F32) return launch_k4<double, double, float, double>(g, s);

@@ -572,7 +572,7 @@ int gemm(Run& r, const GemmBatch& g, bool si = false) {
                     std::to_string(g.N) + " K=" + std::to_string(g.K) + ", problem " +
                     std::to_string(i) + "); launch refused");
   }
-  const int rc = si ? launch_gemm_si_balanced(g, r.sk_part, r.sk_cus, r.st)
+  const int rc = si && !gemm_short_applies(g) ? launch_gemm_si_balanced(g, r.sk_part, r.sk_cus, r.st)
                      : launch_gemm_f64_any(g, r.sk_part, r.sk_cus, r.st);
   if (rc) return vjp_fail(r.c, rc == 1 ? CTM_E_ARG : rc, thread_error());
   return 0;
