@@ -33,11 +33,13 @@ namespace sictm {
 namespace {
 
 constexpr int kPanel = 32;
-constexpr int kLeafRows = 192;   // three rows per lane of one wavefront
+constexpr int kLeafRows = 192;       // of the four-wavefront leaves
+constexpr int kWideLeafRows = 384;   // of the eight-wavefront ones
 constexpr int kT = kPanel + 1;   // padded row length of the small LDS matrices
 
 struct QrPlan {
   int N, k, nb, P, depth;
+  bool wide;   // leaves of eight wavefronts
 };
 
 struct QrArgs {
@@ -109,8 +111,8 @@ __device__ __forceinline__ double row_bcast(double x) {
 constexpr int kGL = kPanel + 2;   // row length of Gt: 16-byte aligned rows
 
 struct PanelLds {
-  double part[2][4][kPanel];     // [buffer][wavefront][chunk a | chunk b]: x_j^T x_s below the pivot
-  double alpha[2][16][kPanel];   // [buffer][16-lane row][chunk a | chunk b]: register row 0
+  double part[2][8][kPanel];     // [buffer][wavefront][chunk a | chunk b]: x_j^T x_s below the pivot
+  double alpha[2][32][kPanel];   // [buffer][16-lane row][chunk a | chunk b]: register row 0
   double Rs[kPanel][kT];         // R
   double Gt[kPanel][kGL];        // Gt[j][s] = v_s^T v_j for s < j, Gt[j][j] = tau_j
   double T[kPanel][kT];
@@ -118,7 +120,8 @@ struct PanelLds {
 
 // The pass over the columns works on a pair of column chunks: `a` holds the
 // 16 pivots of this half of the panel, `b` the other 16 columns; register 0
-// of each holds the pivot rows (the halves trade places between the passes).
+// of each holds the pivot rows (of four wavefronts it has 16 rows, and the
+// halves trade places between the passes; of eight it has all 32).
 template <int R>
 struct PanelRegs {
   double a[R], b[R];       // unscaled panel entries
@@ -127,14 +130,15 @@ struct PanelRegs {
 
 // Column j = j0 + JL; j0 = 0 or 16, chunk a starts at column j0, chunk b at
 // 16 - j0.
-template <int JL, int R>
+template <int JL, int R, int NW>
 __device__ __forceinline__ void panel_step(PanelRegs<R>& x, int j0, int w, int lane, int wave,
                                            PanelLds& sh) {
   const int j = j0 + JL;
   if (j < w) {
     constexpr int buf = JL & 1;
     const int c = lane & 15, row = (lane >> 4) + 4 * wave;
-    const bool piv = row == JL;   // this 16-lane row holds the pivot row
+    const int prow = NW == 8 ? j : JL;
+    const bool piv = row == prow;   // this 16-lane row holds the pivot row
     const bool upper = lane >= 32;
     sh.alpha[buf][row][c] = x.a[0];
     sh.alpha[buf][row][16 + c] = x.b[0];
@@ -158,11 +162,16 @@ __device__ __forceinline__ void panel_step(PanelRegs<R>& x, int j0, int w, int l
     p += q;
     sh.part[buf][wave][(upper ? 16 : 0) + c] = p;
     __syncthreads();
-    const double aa = sh.alpha[buf][JL][c], ab = sh.alpha[buf][JL][16 + c];
-    const double Sa = (sh.part[buf][0][c] + sh.part[buf][1][c]) +
-                      (sh.part[buf][2][c] + sh.part[buf][3][c]);
-    const double Sb = (sh.part[buf][0][16 + c] + sh.part[buf][1][16 + c]) +
-                      (sh.part[buf][2][16 + c] + sh.part[buf][3][16 + c]);
+    const double aa = sh.alpha[buf][prow][c], ab = sh.alpha[buf][prow][16 + c];
+    auto sum4 = [&](int o, int w0) {
+      return (sh.part[buf][w0][o] + sh.part[buf][w0 + 1][o]) +
+             (sh.part[buf][w0 + 2][o] + sh.part[buf][w0 + 3][o]);
+    };
+    double Sa = sum4(c, 0), Sb = sum4(16 + c, 0);
+    if (NW == 8) {
+      Sa += sum4(c, 4);
+      Sb += sum4(16 + c, 4);
+    }
     const double ss = row_bcast<JL>(Sa), al = row_bcast<JL>(aa);
     // tau = (beta - alpha) / beta; H = I (tau = 0) when the part below the
     // pivot is exactly zero
@@ -202,15 +211,17 @@ __device__ __forceinline__ void panel_step(PanelRegs<R>& x, int j0, int w, int l
   }
 }
 
-template <int R>
+template <int R, int NW>
 __device__ __forceinline__ void swap_chunks(PanelRegs<R>& x) {
   auto sw = [](double& p, double& q) {
     const double t = p;
     p = q;
     q = t;
   };
-  sw(x.a[0], x.a[1]);
-  sw(x.b[0], x.b[1]);
+  if (NW == 4) {
+    sw(x.a[0], x.a[1]);
+    sw(x.b[0], x.b[1]);
+  }
 #pragma unroll
   for (int r = 0; r < R; ++r) sw(x.a[r], x.b[r]);
   sw(x.sa, x.sb);
@@ -219,13 +230,14 @@ __device__ __forceinline__ void swap_chunks(PanelRegs<R>& x) {
 // T (upper) of H_0...H_(w-1) = I - V T V^T from Gt.  The 8 x 8 diagonal
 // blocks are built columnwise, T_jj = tau_j, T[i, j] = -tau_j sum_{l=i}^{j-1}
 // T[i, l] G[l, j], one block per wavefront, a row per lane; two blocks side
-// by side then merge with T_12 = -T_11 (G_12 T_22), to 16 x 16 and to
+// by side then merge with T_12 = -T_11 (G_12 T_22) (wavefronts beyond the
+// fourth only take part in the barriers), to 16 x 16 and to
 // 32 x 32.  (One wavefront building all 32 columns, a chain of 496
 // multiply-adds fed from LDS, took 11000 cycles of a panel's 63000.)
 __device__ __forceinline__ void build_T(PanelLds& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double (*Y)[kT] = sh.Rs;   // R has been stored
-  {
+  if (wave < 4) {
     const int b = 8 * wave;
     double t[8];
 #pragma unroll
@@ -260,13 +272,13 @@ __device__ __forceinline__ void build_T(PanelLds& sh) {
     __syncthreads();
   };
   merge(8, lane >> 3, lane & 7, 16 * wave, wave < 2);
-  merge(16, tid >> 4, tid & 15, 0, true);
+  merge(16, tid >> 4, tid & 15, 0, tid < 256);
 }
 
 // Loads the panel through ld(g, r, column), factors it, returns V and R
-// through st(g, r, column, V entry, R entry) (row g + 16 r; the R entry is
-// meaningful for r < 2) and forms T.
-template <int R, typename LD, typename ST>
+// through st(g, r, column, V entry, R entry) (row g + 4 NW r; the R entry is
+// meaningful for the first 32 rows) and forms T.
+template <int R, int NW, typename LD, typename ST>
 __device__ __forceinline__ void panel_qr(int w, int lane, int wave, PanelLds& sh, LD ld, ST st) {
   static_assert(R >= 2 && R % 2 == 0, "register rows");
   PanelRegs<R> x;
@@ -278,7 +290,7 @@ __device__ __forceinline__ void panel_qr(int w, int lane, int wave, PanelLds& sh
   }
   x.sa = x.sb = 0.0;
   // rows of Gt and Rs at or beyond w are never written
-  for (int i = threadIdx.x; i < kPanel * kPanel; i += 256) {
+  for (int i = threadIdx.x; i < kPanel * kPanel; i += 64 * NW) {
     sh.Gt[i >> 5][i & 31] = 0.0;
     sh.Rs[i >> 5][i & 31] = 0.0;
   }
@@ -286,29 +298,30 @@ __device__ __forceinline__ void panel_qr(int w, int lane, int wave, PanelLds& sh
   // two passes over one copy of the code (the instruction cache holds it)
 #pragma unroll 1
   for (int j0 = 0; j0 < kPanel; j0 += 16) {
-    panel_step<0>(x, j0, w, lane, wave, sh);
-    panel_step<1>(x, j0, w, lane, wave, sh);
-    panel_step<2>(x, j0, w, lane, wave, sh);
-    panel_step<3>(x, j0, w, lane, wave, sh);
-    panel_step<4>(x, j0, w, lane, wave, sh);
-    panel_step<5>(x, j0, w, lane, wave, sh);
-    panel_step<6>(x, j0, w, lane, wave, sh);
-    panel_step<7>(x, j0, w, lane, wave, sh);
-    panel_step<8>(x, j0, w, lane, wave, sh);
-    panel_step<9>(x, j0, w, lane, wave, sh);
-    panel_step<10>(x, j0, w, lane, wave, sh);
-    panel_step<11>(x, j0, w, lane, wave, sh);
-    panel_step<12>(x, j0, w, lane, wave, sh);
-    panel_step<13>(x, j0, w, lane, wave, sh);
-    panel_step<14>(x, j0, w, lane, wave, sh);
-    panel_step<15>(x, j0, w, lane, wave, sh);
-    swap_chunks(x);
+    panel_step<0, R, NW>(x, j0, w, lane, wave, sh);
+    panel_step<1, R, NW>(x, j0, w, lane, wave, sh);
+    panel_step<2, R, NW>(x, j0, w, lane, wave, sh);
+    panel_step<3, R, NW>(x, j0, w, lane, wave, sh);
+    panel_step<4, R, NW>(x, j0, w, lane, wave, sh);
+    panel_step<5, R, NW>(x, j0, w, lane, wave, sh);
+    panel_step<6, R, NW>(x, j0, w, lane, wave, sh);
+    panel_step<7, R, NW>(x, j0, w, lane, wave, sh);
+    panel_step<8, R, NW>(x, j0, w, lane, wave, sh);
+    panel_step<9, R, NW>(x, j0, w, lane, wave, sh);
+    panel_step<10, R, NW>(x, j0, w, lane, wave, sh);
+    panel_step<11, R, NW>(x, j0, w, lane, wave, sh);
+    panel_step<12, R, NW>(x, j0, w, lane, wave, sh);
+    panel_step<13, R, NW>(x, j0, w, lane, wave, sh);
+    panel_step<14, R, NW>(x, j0, w, lane, wave, sh);
+    panel_step<15, R, NW>(x, j0, w, lane, wave, sh);
+    swap_chunks<R, NW>(x);
   }
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    st(g, r, c, x.sa * x.a[r], r < 2 ? sh.Rs[g + 16 * r][c] : 0.0);
-    st(g, r, c + 16, x.sb * x.b[r], r < 2 ? sh.Rs[g + 16 * r][c + 16] : 0.0);
+    const bool top = r < 8 / NW;
+    st(g, r, c, x.sa * x.a[r], top ? sh.Rs[g + 4 * NW * r][c] : 0.0);
+    st(g, r, c + 16, x.sb * x.b[r], top ? sh.Rs[g + 4 * NW * r][c + 16] : 0.0);
   }
   build_T(sh);
 }
@@ -316,7 +329,7 @@ __device__ __forceinline__ void panel_qr(int w, int lane, int wave, PanelLds& sh
 // ---------------------------------------------------------------------------
 // leaf factorisation of panel p (the trailing columns: leaf_wy)
 // ---------------------------------------------------------------------------
-template <int R>
+template <int R, int NW>
 __device__ __forceinline__ void leaf_factor(const QrArgs& q, int p, int leaf, int mat,
                                             PanelLds& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -328,25 +341,26 @@ __device__ __forceinline__ void leaf_factor(const QrArgs& q, int p, int leaf, in
   const double* src = (p == 0 ? q.W[mat] : q.A[mat]) + (long)a0 * k + c0;
   double* dst = q.A[mat] + (long)a0 * k + c0;
   // rows at or beyond m and columns at or beyond w are held as zeros
-  panel_qr<R>(
+  constexpr int G = 4 * NW;
+  panel_qr<R, NW>(
       w, lane, wave, sh,
       [&](int g, int r, int c) {
-        return g + 16 * r < m && c < w ? (src + (long)(16 * r) * k)[g * k + c] : 0.0;
+        return g + G * r < m && c < w ? (src + (long)(G * r) * k)[g * k + c] : 0.0;
       },
       [&](int g, int r, int c, double v, double rv) {
-        const int row = g + 16 * r;
-        if (row < m && c < w) (dst + (long)(16 * r) * k)[g * k + c] = c >= row ? rv : v;
+        const int row = g + G * r;
+        if (row < m && c < w) (dst + (long)(G * r) * k)[g * k + c] = c >= row ? rv : v;
       });
   const long sl = slot(mat, p, leaf, nb, q.P);
-  for (int idx = tid; idx < kPanel * kPanel; idx += 256)
+  for (int idx = tid; idx < kPanel * kPanel; idx += 64 * NW)
     q.Tl[sl * kPanel * kPanel + idx] = sh.T[idx / kPanel][idx % kPanel];
 }
 
-// R register rows hold leaves of up to 16 R rows.
-template <int R>
-__global__ __launch_bounds__(256) void qr_leaf_factor(QrArgs q, int p) {
+// R register rows of NW wavefronts hold leaves of up to 4 NW R rows.
+template <int R, int NW>
+__global__ __launch_bounds__(64 * NW) void qr_leaf_factor(QrArgs q, int p) {
   __shared__ PanelLds sh;
-  leaf_factor<R>(q, p, blockIdx.x, blockIdx.y, sh);
+  leaf_factor<R, NW>(q, p, blockIdx.x, blockIdx.y, sh);
 }
 
 // Top row of the w x w triangle a leaf holds during panel p.
@@ -372,44 +386,44 @@ __device__ __forceinline__ int node_children(int a, int s, int nb) {
 // The workgroup factors the stacked triangles [R_0; R_1; ...]; the
 // reflectors are [e_j; v_j] with v_j in the upper triangles of the children
 // after the first (the node's trailing columns: tree_wy).  Register row r
-// holds rows g + 16 (r mod 2) of child r / 2.  The rows of child 0 below the
-// pivot are zero in the pivot column, so the panel code needs no mask for
-// them.
-template <int R>
+// holds rows g + 16 (r mod 2) of child r / 2 (of eight wavefronts, rows g of
+// child r).  The rows of child 0 below the pivot are zero in the pivot column,
+// so the panel code needs no mask for them.
+template <int R, int NW>
 __device__ __forceinline__ void tree_factor(const QrArgs& q, int p, int s, int a, int nch, int mat,
                                             PanelLds& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int k = q.k, nb = q.nb;
   const int c0 = p * kPanel, w = min(kPanel, k - c0);
   double* A = q.A[mat];
+  constexpr int H = 8 / NW;   // register rows of a child
   auto base = [&](int r) {   // register row r of the stack (the same in every lane)
-    return A + (long)(top_row(q, a + (r >> 1) * s, c0) + 16 * (r & 1)) * k + c0;
+    return A + (long)(top_row(q, a + r / H * s, c0) + 16 * (r % H)) * k + c0;
   };
-  auto in = [&](int g, int r, int c) {
-    return (r >> 1) < nch && g + 16 * (r & 1) <= c && c < w;
-  };
-  panel_qr<R>(
+  auto in = [&](int g, int r, int c) { return r / H < nch && g + 16 * (r % H) <= c && c < w; };
+  panel_qr<R, NW>(
       w, lane, wave, sh,
       [&](int g, int r, int c) { return in(g, r, c) ? base(r)[g * k + c] : 0.0; },
       [&](int g, int r, int c, double v, double rv) {
-        if (in(g, r, c)) base(r)[g * k + c] = r < 2 ? rv : v;
+        if (in(g, r, c)) base(r)[g * k + c] = r < H ? rv : v;
       });
   const long sl = slot(mat, p, a + s, nb, q.P);
-  for (int idx = tid; idx < kPanel * kPanel; idx += 256)
+  for (int idx = tid; idx < kPanel * kPanel; idx += 64 * NW)
     q.Tn[sl * kPanel * kPanel + idx] = sh.T[idx / kPanel][idx % kPanel];
 }
 
+template <int NW = 4>
 __device__ __forceinline__ void tree_factor_node(const QrArgs& q, int p, int s, int node, int mat,
                                                  PanelLds& sh) {
   const int a = node * s * kArity;
   if (a + s >= q.nb) return;
   const int nch = node_children(a, s, q.nb);
   if (nch <= 2)
-    tree_factor<4>(q, p, s, a, nch, mat, sh);
+    tree_factor<16 / NW, NW>(q, p, s, a, nch, mat, sh);
   else if (nch <= 4)
-    tree_factor<8>(q, p, s, a, nch, mat, sh);
+    tree_factor<32 / NW, NW>(q, p, s, a, nch, mat, sh);
   else
-    tree_factor<2 * kArity>(q, p, s, a, nch, mat, sh);
+    tree_factor<8 * kArity / NW, NW>(q, p, s, a, nch, mat, sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -434,7 +448,7 @@ __device__ __forceinline__ double diag_sign(const double* A, int k, int c) {
   return A[(long)c * k + c] < 0.0 ? -1.0 : 1.0;
 }
 
-// One chunk: C <- C - V op(T) (V^T C) for 4 RW rows, of which this wavefront
+// One chunk: C <- C - V op(T) (V^T C) for NW RW rows, of which this wavefront
 // owns rows RW wave .. RW (wave + 1) - 1.  vval / cval(row, column) give the
 // operands (zeros outside), put(row, column, value) stores the result.  The
 // operands are read from global memory straight into the operand layout of
@@ -447,23 +461,25 @@ __device__ __forceinline__ double diag_sign(const double* A, int k, int c) {
 // products accumulate onto C itself.  `ksteps` k-steps of this wavefront have
 // a C that is not known to be zero.  TREE: the rows are 32-row triangles
 // stacked, whose rows 16 .. 31 are zero in columns 0 .. 15 (those products
-// are left out).  50 KB of LDS lets three workgroups share a CU.
+// are left out).  50 KB of LDS lets three workgroups of four wavefronts share a
+// CU (of eight, the second four add their partial products to the first's).
 //
 // Bound by latency (a chain of two memory round trips, 3 x 8 to 3 x 64
 // dependent f64 MFMAs and three barriers): on 8 blocks of 5184 x 160 a launch
 // forming Q took 20.2 us (nodes) and 38.6 us (leaves) with the second reading
 // issued where it was used and the zeros multiplied, 15.7 and 25.7 us in this
 // form.
-template <bool FORM, bool TREE, int RW, typename VF, typename CF, typename PF>
+template <bool FORM, bool TREE, int RW, int NW, typename VF, typename CF, typename PF>
 __device__ __forceinline__ void wy_apply(const double* Tg, int rows, int ksteps, VF vval, CF cval,
                                          PF put, WyLds& sh) {
   constexpr int KS = RW / 4, RB = RW / 16;
   static_assert(kPanel == 32 && kTrailN == kPanel && RW % 16 == 0, "fragment shapes");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r0 = RW * wave, li = lane & 15, lk = lane >> 4;
-  double tg[kPanel * kPanel / 256];
+  constexpr int NT = 64 * NW;
+  double tg[kPanel * kPanel / NT];
 #pragma unroll
-  for (int i = 0; i < kPanel * kPanel / 256; ++i) tg[i] = Tg[tid + 256 * i];
+  for (int i = 0; i < kPanel * kPanel / NT; ++i) tg[i] = Tg[tid + NT * i];
   {
     double vf[KS][2], cf[KS][2];
 #pragma unroll
@@ -476,8 +492,8 @@ __device__ __forceinline__ void wy_apply(const double* Tg, int rows, int ksteps,
       }
     }
 #pragma unroll
-    for (int i = 0; i < kPanel * kPanel / 256; ++i)
-      sh.T[(tid >> 5) + 8 * i][tid & 31] = tg[i];
+    for (int i = 0; i < kPanel * kPanel / NT; ++i)
+      sh.T[(tid >> 5) + NT / 32 * i][tid & 31] = tg[i];
     v4d acc[2][2] = {{{0, 0, 0, 0}, {0, 0, 0, 0}}, {{0, 0, 0, 0}, {0, 0, 0, 0}}};
 #pragma unroll
     for (int t = 0; t < KS; ++t)
@@ -490,12 +506,22 @@ __device__ __forceinline__ void wy_apply(const double* Tg, int rows, int ksteps,
               acc[i][j] =
                   __builtin_amdgcn_mfma_f64_16x16x4f64(vf[t][i], cf[t][j], acc[i][j], 0, 0, 0);
       }
+    auto partial = [&](bool add) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sh.Wp[wave][16 * i + lk + 4 * r][16 * j + li] = acc[i][j][r];
+          for (int r = 0; r < 4; ++r) {
+            double& d = sh.Wp[wave & 3][16 * i + lk + 4 * r][16 * j + li];
+            d = add ? d + acc[i][j][r] : acc[i][j][r];
+          }
+    };
+    if (wave < 4) partial(false);
+    if (NW == 8) {
+      __syncthreads();
+      if (wave >= 4) partial(true);
+    }
   }
   // the update's operands
   double v2[RB][kPanel / 4];
@@ -512,7 +538,7 @@ __device__ __forceinline__ void wy_apply(const double* Tg, int rows, int ksteps,
       for (int r = 0; r < 4; ++r) u[rb][j][r] = cval(rr0 + lk + 4 * r, 16 * j + li);
   }
   __syncthreads();
-  {
+  if (wave < 4) {
     // W2 block (bi, bj) = op(T) W1 with W1 the sum of the partials in wave order
     const int bi = wave >> 1, bj = wave & 1;
     v4d a2 = {0, 0, 0, 0};
@@ -594,12 +620,12 @@ __device__ __forceinline__ void tree_wy(const QrArgs& q, int p, int s, int node,
   };
   const int ksteps = FORM && chunk == 0 ? (wave == 0 ? kPanel / 4 : 0)
                                         : kPanel / 4 * max(0, min(2, nch - 2 * wave));
-  wy_apply<FORM, true, RW>(q.Tn + slot(mat, p, a + s, nb, q.P) * kPanel * kPanel, kPanel * nch,
+  wy_apply<FORM, true, RW, 4>(q.Tn + slot(mat, p, a + s, nb, q.P) * kPanel * kPanel, kPanel * nch,
                            ksteps, vval, cval, put, sh);
 }
 
 // Leaf rows: V is unit lower-trapezoidal (implicit ones, zeros above).
-template <bool FORM>
+template <bool FORM, int NW>
 __device__ __forceinline__ void leaf_wy(const QrArgs& q, int p, int leaf, int mat, int chunk,
                                         WyLds& sh) {
   constexpr int RW = kLeafRows / 4;
@@ -634,7 +660,7 @@ __device__ __forceinline__ void leaf_wy(const QrArgs& q, int p, int leaf, int ma
   };
   const int r0 = RW * (threadIdx.x >> 6);
   const int live = FORM && chunk == 0 ? w : m;   // rows of C that may be non-zero
-  wy_apply<FORM, false, RW>(q.Tl + slot(mat, p, leaf, nb, q.P) * kPanel * kPanel, m,
+  wy_apply<FORM, false, RW, NW>(q.Tl + slot(mat, p, leaf, nb, q.P) * kPanel * kPanel, m,
                             max(0, min(RW / 4, (live - r0 + 3) >> 2)), vval, cval, put, sh);
 }
 
@@ -649,16 +675,17 @@ union StageLds {
 // After the leaf factors of panel p: the first tree level's factors (`next`
 // nodes per matrix; the first blocks, since the next launch waits for their
 // 32 serial steps) beside the leaves' trailing columns.
-__global__ __launch_bounds__(256, 2) void qr_leaf_trail(QrArgs q, int p, int trail, int next) {
+template <int NW>
+__global__ __launch_bounds__(64 * NW, 2) void qr_leaf_trail(QrArgs q, int p, int trail, int next) {
   __shared__ StageLds sh;
   int x = blockIdx.x;
   if (x < next * q.count) {
-    tree_factor_node(q, p, 1, x % next, x / next, sh.panel);
+    tree_factor_node<NW>(q, p, 1, x % next, x / next, sh.panel);
     return;
   }
   x -= next * q.count;
   const int per = q.nb * trail;
-  leaf_wy<false>(q, p, x % per / trail, x / per, x % trail, sh.wy);
+  leaf_wy<false, NW>(q, p, x % per / trail, x / per, x % trail, sh.wy);
 }
 
 // After the tree factors at stride s: the next level's factors beside those
@@ -681,9 +708,10 @@ __global__ __launch_bounds__(256, 2) void qr_tree_form(QrArgs q, int p, int s, i
   tree_wy<true>(q, p, s, blockIdx.x, blockIdx.y, blockIdx.z, top != 0, sh);
 }
 
-__global__ __launch_bounds__(256, 2) void qr_leaf_form(QrArgs q, int p) {
+template <int NW>
+__global__ __launch_bounds__(64 * NW, 2) void qr_leaf_form(QrArgs q, int p) {
   __shared__ WyLds sh;
-  leaf_wy<true>(q, p, blockIdx.x, blockIdx.y, blockIdx.z, sh);
+  leaf_wy<true, NW>(q, p, blockIdx.x, blockIdx.y, blockIdx.z, sh);
 }
 
 QrPlan make_plan(int N, int k) {
@@ -697,9 +725,21 @@ QrPlan make_plan(int N, int k) {
   if (nb > 1 && N / nb < k) nb = N / k;  // leaf 0 must hold k rows
   pl.nb = nb;
   pl.P = (k + kPanel - 1) / kPanel;
-  int depth = 0;
-  for (long span = 1; span < nb; span *= kArity) ++depth;
-  pl.depth = depth;
+  auto levels = [](int leaves) {
+    int depth = 0;
+    for (long span = 1; span < leaves; span *= kArity) ++depth;
+    return depth;
+  };
+  pl.depth = levels(nb);
+  // twice as tall leaves where that saves a level of the tree (what the rows
+  // above refuse stays refused)
+  pl.wide = false;
+  const int wnb = (N + kWideLeafRows - 1) / kWideLeafRows;
+  if ((N + nb - 1) / nb <= kLeafRows && levels(wnb) < pl.depth) {
+    pl.wide = true;
+    pl.nb = wnb;
+    pl.depth = levels(wnb);
+  }
   return pl;
 }
 
@@ -708,7 +748,7 @@ QrPlan make_plan(int N, int k) {
 bool qr_plan_ok(int N, int k) {
   if (k <= 0 || N < k || k > kLeafRows) return false;
   const QrPlan pl = make_plan(N, k);
-  return (N + pl.nb - 1) / pl.nb <= kLeafRows;
+  return pl.wide || (N + pl.nb - 1) / pl.nb <= kLeafRows;
 }
 
 size_t qr_workspace_bytes(int count, int N, int k) {
@@ -725,7 +765,7 @@ int launch_qr(int count, double* const* W, int N, int k, void* ws, hipStream_t s
     return 1;
   }
   const QrPlan pl = make_plan(N, k);
-  if ((N + pl.nb - 1) / pl.nb > kLeafRows) {
+  if (!pl.wide && (N + pl.nb - 1) / pl.nb > kLeafRows) {
     set_thread_error("launch_qr: N too large for the leaf size (N/k too large)");
     return 1;
   }
@@ -753,14 +793,21 @@ int launch_qr(int count, double* const* W, int N, int k, void* ws, hipStream_t s
     const int trail = (k - c0 - w + kTrailN - 1) / kTrailN;
     const dim3 leaves(pl.nb, count);
     if (leaf_rows <= 64)
-      qr_leaf_factor<4><<<leaves, 256, 0, s>>>(q, p);
+      qr_leaf_factor<4, 4><<<leaves, 256, 0, s>>>(q, p);
     else if (leaf_rows <= 128)
-      qr_leaf_factor<8><<<leaves, 256, 0, s>>>(q, p);
+      qr_leaf_factor<8, 4><<<leaves, 256, 0, s>>>(q, p);
+    else if (leaf_rows <= kLeafRows)
+      qr_leaf_factor<12, 4><<<leaves, 256, 0, s>>>(q, p);
+    else if (leaf_rows <= 256)
+      qr_leaf_factor<8, 8><<<leaves, 512, 0, s>>>(q, p);
     else
-      qr_leaf_factor<12><<<leaves, 256, 0, s>>>(q, p);
+      qr_leaf_factor<12, 8><<<leaves, 512, 0, s>>>(q, p);
     int next = pl.depth > 0 ? nodes_at(1) : 0;   // nodes of the next level to factor
-    if (pl.nb * trail + next)
-      qr_leaf_trail<<<count * (pl.nb * trail + next), 256, 0, s>>>(q, p, trail, next);
+    const int stage = count * (pl.nb * trail + next);
+    if (stage && leaf_rows <= kLeafRows)
+      qr_leaf_trail<4><<<stage, 256, 0, s>>>(q, p, trail, next);
+    else if (stage)
+      qr_leaf_trail<8><<<stage, 512, 0, s>>>(q, p, trail, next);
     for (int L = 0, st = 1; L < pl.depth; ++L, st *= kArity) {
       const int nodes = next;
       next = L + 1 < pl.depth ? nodes_at(st * kArity) : 0;
@@ -775,7 +822,10 @@ int launch_qr(int count, double* const* W, int N, int k, void* ws, hipStream_t s
       for (int i = 0; i < L; ++i) st *= kArity;
       qr_tree_form<<<dim3(nodes_at(st), count, chunks), 256, 0, s>>>(q, p, st, L == pl.depth - 1);
     }
-    qr_leaf_form<<<dim3(pl.nb, count, chunks), 256, 0, s>>>(q, p);
+    if (leaf_rows <= kLeafRows)
+      qr_leaf_form<4><<<dim3(pl.nb, count, chunks), 256, 0, s>>>(q, p);
+    else
+      qr_leaf_form<8><<<dim3(pl.nb, count, chunks), 512, 0, s>>>(q, p);
   }
   CTM_HIP_TRY(hipGetLastError());
   return 0;
