@@ -100,6 +100,42 @@ __global__ __launch_bounds__(256) void k_transpose_tiles(const double* __restric
   }
 }
 
+// Up to 16 matrices of one shape per launch: dst (cols x rows) = src^T, and
+// plain copies.  A launch of one 1024 x 72 matrix takes 4 to 5 us whatever it
+// moves; the adjoint of a move with D 4, chi 64 had 350 transposes and 64
+// copies of one matrix each, 1.8 ms, now 60 launches.
+constexpr int kManyMats = 16;
+struct ManyArgs {
+  const double* src[kManyMats];
+  double* dst[kManyMats];
+};
+
+__global__ __launch_bounds__(256) void k_transpose_many(ManyArgs a, int rows, int cols) {
+  __shared__ double t[32][33];
+  const double* src = a.src[blockIdx.y];
+  double* dst = a.dst[blockIdx.y];
+  const int tiles2 = (cols + 31) / 32;
+  const int b2 = blockIdx.x % tiles2, b3 = blockIdx.x / tiles2;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+#pragma unroll
+  for (int k = 0; k < 32; k += 8) {
+    const int r = b3 * 32 + ty + k, c = b2 * 32 + tx;
+    if (r < rows && c < cols) t[ty + k][tx] = src[(long)r * cols + c];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 32; k += 8) {
+    const int c = b2 * 32 + ty + k, r = b3 * 32 + tx;
+    if (c < cols && r < rows) dst[(long)c * rows + r] = t[tx][ty + k];
+  }
+}
+
+__global__ __launch_bounds__(256) void k_copy_many(ManyArgs a, long n) {
+  const double* src = a.src[blockIdx.y];
+  double* dst = a.dst[blockIdx.y];
+  for (long i = blockIdx.x * 256L + threadIdx.x; i < n; i += (long)gridDim.x * 256) dst[i] = src[i];
+}
+
 __global__ __launch_bounds__(256) void k_fill(double* __restrict__ x, long n, double v) {
   for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
     x[i] = v;
@@ -206,38 +242,49 @@ __global__ __launch_bounds__(256) void k_tri_inv(SmallArgs a) {
   }
 }
 
-// Same result as k_tri_inv, operation for operation, for n <= kTriLds: the
-// upper triangle of X lives in LDS, row-packed (row l starts at
-// l n - l (l - 1) / 2, so the threads of a row step read consecutive words),
-// and row i of R is staged in LDS for step i.  Every thread takes part in
-// the two barriers of each step.
+// The inverse for n <= kTriLds with R's upper triangle in LDS, row-packed (row l
+// starts at l n - l (l - 1) / 2): a wavefront per column of X, its rows in the
+// registers of the lanes (lane, lane + 64, lane + 128).  Step i divides entry i
+// and takes its multiple of R's column i from the entries above, so that a
+// column is n steps of one division and one multiply-add per lane; 16 columns
+// per workgroup.  Bound by the latency of the steps.  (A thread per column, whose
+// entry i is a sum of n - i terms one after another, took 151 us at n = 72 where
+// this takes 21.)
 constexpr int kTriLds = 192;
 
-__global__ __launch_bounds__(256) void k_tri_inv_lds(SmallArgs a) {
-  __shared__ double Xs[kTriLds * (kTriLds + 1) / 2];
-  __shared__ double Rrow[kTriLds];
-  const int b = blockIdx.x, n = a.n, j = threadIdx.x;
+__global__ __launch_bounds__(1024) void k_tri_inv_lds(SmallArgs a) {
+  __shared__ double Rs[kTriLds * (kTriLds + 1) / 2];
+  const int b = blockIdx.y, n = a.n, lane = threadIdx.x & 63;
   const double* R = a.in[b];
   double* X = a.out[b];
   auto at = [n](int l, int c) { return l * n - l * (l - 1) / 2 + (c - l); };   // l <= c
-  for (int i = n - 1; i >= 0; --i) {
-    __syncthreads();
-    if (j < n) Rrow[j] = R[(long)i * n + j];
-    __syncthreads();
-    if (j < n && j >= i) {
-      double acc = i == j ? 1.0 : 0.0;
-      // unrolled so that the LDS loads of later terms issue while earlier
-      // terms are accumulated; the accumulation order is unchanged
-#pragma unroll 4
-      for (int l = i + 1; l <= j; ++l) acc -= Rrow[l] * Xs[at(l, j)];
-      const double d = Rrow[i];
-      Xs[at(i, j)] = d != 0.0 ? acc / d : 0.0;
-    }
+  for (int e = threadIdx.x; e < n * n; e += 1024) {
+    const int r = e / n, c = e % n;
+    if (c >= r) Rs[at(r, c)] = R[e];
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < n * n; e += blockDim.x) {
-    const int r = e / n, c = e % n;
-    X[e] = c >= r ? Xs[at(r, c)] : 0.0;
+  const int j = blockIdx.x * 16 + (threadIdx.x >> 6);   // the same in a wavefront
+  if (j >= n) return;
+  constexpr int RW = kTriLds / 64;
+  double x[RW];
+#pragma unroll
+  for (int e = 0; e < RW; ++e) x[e] = lane + 64 * e == j ? 1.0 : 0.0;
+#pragma unroll
+  for (int e = RW - 1; e >= 0; --e)
+    for (int i = min(j, 64 * e + 63); i >= 64 * e; --i) {
+      const double d = Rs[at(i, i)], v = __shfl(x[e], i & 63);
+      const double xi = d != 0.0 ? v / d : 0.0;
+#pragma unroll
+      for (int u = 0; u <= e; ++u) {
+        const int l = lane + 64 * u;
+        if (l < i) x[u] = fma(-Rs[at(l, i)], xi, x[u]);
+        else if (l == i) x[u] = xi;
+      }
+    }
+#pragma unroll
+  for (int e = 0; e < RW; ++e) {
+    const int l = lane + 64 * e;
+    if (l < n) X[(long)l * n + j] = x[e];
   }
 }
 
@@ -611,6 +658,29 @@ int transpose(Run& r, const double* src, double* dst, long rows, long cols) {
   return gather(r, src, dst, 1, 1, (int)cols, (int)rows, 0, 0, 1, cols);
 }
 
+// dst[i] (cols x rows) = src[i] (rows x cols)^T for count <= kManyMats matrices
+int transpose_many(Run& r, const ManyArgs& a, int count, long rows, long cols) {
+  if (count <= 0 || rows <= 0 || cols <= 0) return 0;
+  for (int i = 0; i < count; ++i)
+    if (!r.inside(a.src[i], (size_t)rows * cols * 8) || !r.inside(a.dst[i], (size_t)rows * cols * 8))
+      return r.fail("adjoint permutation out of its buffer; launch refused");
+  k_transpose_many<<<dim3((unsigned)(((cols + 31) / 32) * ((rows + 31) / 32)), count), 256, 0, r.st>>>(
+      a, (int)rows, (int)cols);
+  CTM_HIP_TRY(hipGetLastError());
+  return 0;
+}
+
+// dst[i] = src[i] for count <= kManyMats arrays of n doubles
+int copy_many(Run& r, const ManyArgs& a, int count, long n) {
+  if (count <= 0 || n <= 0) return 0;
+  for (int i = 0; i < count; ++i)
+    if (!r.inside(a.src[i], (size_t)n * 8) || !r.inside(a.dst[i], (size_t)n * 8))
+      return r.fail("adjoint copy out of its buffer; refused");
+  k_copy_many<<<dim3((unsigned)std::min<long>(256, (n + 255) / 256), count), 256, 0, r.st>>>(a, n);
+  CTM_HIP_TRY(hipGetLastError());
+  return 0;
+}
+
 int fill(Run& r, double* x, long n, double v) {
   if (n <= 0) return 0;
   if (!r.inside(x, (size_t)n * 8)) return r.fail("adjoint fill out of its buffer; launch refused");
@@ -718,10 +788,12 @@ int forward(Run& r, const VjpView& v, const Dims& m, Bufs& b, const State& in, d
         VTRY(gemm(r, g, true));
       }
       double* q[8];
+      ManyArgs qc{};
       for (int j = 0; j < 8; ++j) {
-        VTRY(copy(r, b.tape[j][base + 3], b.tape[j][base + 4], (long)N * k));
-        q[j] = b.tape[j][base + 4];
+        qc.src[j] = b.tape[j][base + 3];
+        q[j] = qc.dst[j] = b.tape[j][base + 4];
       }
+      VTRY(copy_many(r, qc, 8, (long)N * k));
       const int rc = launch_qr(8, q, N, k, b.qr_ws, r.st);
       if (rc) return vjp_fail(r.c, rc == 1 ? CTM_E_ARG : rc, thread_error());
       for (int j = 0; j < 8; ++j) cur[j] = q[j];
@@ -943,7 +1015,12 @@ int backward(Run& r, const VjpView& v, const Dims& m, Bufs& b, const State& in,
     VTRY(fill(r, Tb_out[i], (long)x * Dl * x, 0.0));
   }
   VTRY(fill(r, b.ab, (long)Dl * Dl * Dl * Dl, 0.0));
-  for (int i = 0; i < 4; ++i) VTRY(transpose(r, v.ap[i], b.apT[i], (long)Dl * Dl, (long)Dl * Dl));
+  ManyArgs ma{};
+  for (int i = 0; i < 4; ++i) {
+    ma.src[i] = v.ap[i];
+    ma.dst[i] = b.apT[i];
+  }
+  VTRY(transpose_many(r, ma, 4, (long)Dl * Dl, (long)Dl * Dl));
   // unit-norm scaling
   {
     DotArgs da{};
@@ -1004,7 +1081,11 @@ int backward(Run& r, const VjpView& v, const Dims& m, Bufs& b, const State& in,
   // go through each step in one launch
   {
     const long D2 = (long)Dl * Dl;
-    for (int j = 0; j < 4; ++j) VTRY(transpose(r, b.Thb[j], b.Gb[j], x, (long)Dl * x));
+    for (int j = 0; j < 4; ++j) {
+      ma.src[j] = b.Thb[j];
+      ma.dst[j] = b.Gb[j];
+    }
+    VTRY(transpose_many(r, ma, 4, x, (long)Dl * x));
     GemmBatch g = rowmajor(4, N, x, Dl * x, (long)Dl * x, x, x);
     g.accumulate = 1;
     for (int j = 0; j < 4; ++j) {
@@ -1044,8 +1125,10 @@ int backward(Run& r, const VjpView& v, const Dims& m, Bufs& b, const State& in,
     VTRY(gemm(r, g4));
     for (int j = 0; j < 4; ++j) {                          // -> [(b,u)][(r,g')]
       VTRY(gather(r, b.Ga[j], b.Gb[j], x, Dl, Dl, x, (long)x * D2, Dl, 1, D2));
-      VTRY(transpose(r, b.Pl[j], b.Ga[j], x, (long)Dl * x));
+      ma.src[j] = b.Pl[j];
+      ma.dst[j] = b.Ga[j];
     }
+    VTRY(transpose_many(r, ma, 4, x, (long)Dl * x));
     GemmBatch g5 = rowmajor(4, x * Dl, x, Dl * x, (long)Dl * x, x, x);
     g5.accumulate = 1;
     for (int j = 0; j < 4; ++j) {
@@ -1072,11 +1155,19 @@ int backward(Run& r, const VjpView& v, const Dims& m, Bufs& b, const State& in,
     Yf[i] = m.nsi > 0 ? b.tape[4 + i][10 * m.nsi - 1] : (double*)in.Yt[i];
   }
   for (int i = 0; i < 4; ++i) {
-    VTRY(transpose(r, b.vsc[i], b.vscT[i], k, x));
-    VTRY(transpose(r, b.usc[i], b.uscT[i], k, x));
-    VTRY(transpose(r, b.vs[i], b.vsT[i], k, k));
-    VTRY(transpose(r, b.us[i], b.usT[i], k, k));
+    ma.src[i] = b.vsc[i];
+    ma.dst[i] = b.vscT[i];
+    ma.src[4 + i] = b.usc[i];
+    ma.dst[4 + i] = b.uscT[i];
   }
+  VTRY(transpose_many(r, ma, 8, k, x));
+  for (int i = 0; i < 4; ++i) {
+    ma.src[i] = b.vs[i];
+    ma.dst[i] = b.vsT[i];
+    ma.src[4 + i] = b.us[i];
+    ma.dst[4 + i] = b.usT[i];
+  }
+  VTRY(transpose_many(r, ma, 8, k, k));
   {
     // A_bar = P_l_bar vsc^T -> Hb[i];  B^T_bar = P_rT_bar usc^T -> Hb[4+i]
     GemmBatch g = rowmajor(8, N, k, x, x, k, k);
@@ -1177,7 +1268,11 @@ int backward(Run& r, const VjpView& v, const Dims& m, Bufs& b, const State& in,
       g2.C[i] = b.rhob[i];
     }
     VTRY(gemm(r, g2));
-    for (int i = 0; i < 4; ++i) VTRY(transpose(r, b.rhob[i], b.rhobT[i], k, k));
+    for (int i = 0; i < 4; ++i) {
+      ma.src[i] = b.rhob[i];
+      ma.dst[i] = b.rhobT[i];
+    }
+    VTRY(transpose_many(r, ma, 4, k, k));
     // rho = B A:  A_bar += B^T rho_bar,  B^T_bar += A rho_bar^T
     GemmBatch g3 = rowmajor(8, N, k, k, k, k, k);
     g3.accumulate = 1;
@@ -1194,8 +1289,13 @@ int backward(Run& r, const VjpView& v, const Dims& m, Bufs& b, const State& in,
   // A = Ct[b+1] W1, W1 = Ct[b+2] Xf;  B^T = Ct[b]^T W2, W2 = Ct[b-1]^T Yf
   {
     // rank-k terms of the outer applications (A and B^T)
-    for (int i = 0; i < 4; ++i) VTRY(transpose(r, b.W1[i], b.tr[i], N, k));
-    for (int i = 0; i < 4; ++i) VTRY(transpose(r, b.Hb[4 + i], b.tr[4 + i], N, k));
+    for (int i = 0; i < 4; ++i) {
+      ma.src[i] = b.W1[i];
+      ma.dst[i] = b.tr[i];
+      ma.src[4 + i] = b.Hb[4 + i];
+      ma.dst[4 + i] = b.tr[4 + i];
+    }
+    VTRY(transpose_many(r, ma, 8, N, k));
     GemmBatch g = rowmajor(4, N, N, k, k, N, N);
     g.accumulate = 1;
     for (int i = 0; i < 4; ++i) {
@@ -1222,8 +1322,13 @@ int backward(Run& r, const VjpView& v, const Dims& m, Bufs& b, const State& in,
       g2.C[4 + i] = b.Yq[4 + i];
     }
     VTRY(gemm(r, g2, true));
-    for (int i = 0; i < 4; ++i) VTRY(transpose(r, Xf[i], b.tr[i], N, k));
-    for (int i = 0; i < 4; ++i) VTRY(transpose(r, b.Yq[4 + i], b.tr[4 + i], N, k));
+    for (int i = 0; i < 4; ++i) {
+      ma.src[i] = Xf[i];
+      ma.dst[i] = b.tr[i];
+      ma.src[4 + i] = b.Yq[4 + i];
+      ma.dst[4 + i] = b.tr[4 + i];
+    }
+    VTRY(transpose_many(r, ma, 8, N, k));
     for (int i = 0; i < 4; ++i) {
       g.A[i] = b.Yq[i];
       g.B[i] = b.tr[i];
@@ -1285,14 +1390,19 @@ int backward(Run& r, const VjpView& v, const Dims& m, Bufs& b, const State& in,
         sa.out[j] = b.Rinv[j];
       }
       if (k <= kTriLds)
-        k_tri_inv_lds<<<8, 256, 0, r.st>>>(sa);
+        k_tri_inv_lds<<<dim3((k + 15) / 16, 8), 1024, 0, r.st>>>(sa);
       else
         k_tri_inv<<<8, 256, 0, r.st>>>(sa);
       CTM_HIP_TRY(hipGetLastError());
+      ManyArgs qc{};
       for (int j = 0; j < 8; ++j) {
-        VTRY(transpose(r, b.Rinv[j], b.RinvT[j], k, k));
-        VTRY(copy(r, b.Qb[j], b.Yq[j], Nk));
+        ma.src[j] = b.Rinv[j];
+        ma.dst[j] = b.RinvT[j];
+        qc.src[j] = b.Qb[j];
+        qc.dst[j] = b.Yq[j];
       }
+      VTRY(transpose_many(r, ma, 8, k, k));
+      VTRY(copy_many(r, qc, 8, Nk));
       GemmBatch gy = rowmajor(8, N, k, k, k, k, k);
       gy.accumulate = 1;
       for (int j = 0; j < 8; ++j) {
@@ -1331,9 +1441,12 @@ int backward(Run& r, const VjpView& v, const Dims& m, Bufs& b, const State& in,
         // the stacks are contracted once per half step below.
         for (int j = 0; j < 8; ++j) {
           const long slot = (2 * t + (j >= 4 ? 1 : 0)) * Nk;
-          VTRY(transpose(r, trn[j] ? hin[j] : b.Hb[j], b.PTs[ci[j]] + slot, N, k));
-          VTRY(transpose(r, trn[j] ? b.Hb[j] : hin[j], b.QTs[ci[j]] + slot, N, k));
+          ma.src[j] = trn[j] ? hin[j] : b.Hb[j];
+          ma.dst[j] = b.PTs[ci[j]] + slot;
+          ma.src[8 + j] = trn[j] ? b.Hb[j] : hin[j];
+          ma.dst[8 + j] = b.QTs[ci[j]] + slot;
         }
+        VTRY(transpose_many(r, ma, 16, N, k));
         GemmBatch gb = rowmajor(8, N, k, N, N, k, k);
         for (int j = 0; j < 8; ++j) {
           gb.A[j] = b.Ct[ci[j]];
@@ -1360,9 +1473,12 @@ int backward(Run& r, const VjpView& v, const Dims& m, Bufs& b, const State& in,
     }
   }
   for (int i = 0; i < 4; ++i) {
-    VTRY(copy(r, b.Qb[i], Xb_out[i], Nk));
-    VTRY(copy(r, b.Qb[4 + i], Yb_out[i], Nk));
+    ma.src[i] = b.Qb[i];
+    ma.dst[i] = Xb_out[i];
+    ma.src[4 + i] = b.Qb[4 + i];
+    ma.dst[4 + i] = Yb_out[i];
   }
+  VTRY(copy_many(r, ma, 8, Nk));
   // enlarged corners, the four corners batched in every step
   {
     const long D2 = (long)Dl * Dl;
@@ -1389,8 +1505,10 @@ int backward(Run& r, const VjpView& v, const Dims& m, Bufs& b, const State& in,
       VTRY(gather(r, b.apb4[i], b.ab, Dl, Dl, Dl, Dl, inv[0], inv[1], inv[2], inv[3], true));
       // Wbp[(x_in,p),(q,y)] from W_bar[(x_in,y),(p,q)]
       VTRY(gather(r, b.Gb[i], b.Ga[i], x, Dl, Dl, x, (long)x * D2, Dl, 1, D2));
-      VTRY(transpose(r, b.CT[i], b.Gb[i], x, (long)Dl * x));
+      ma.src[i] = b.CT[i];
+      ma.dst[i] = b.Gb[i];
     }
+    VTRY(transpose_many(r, ma, 4, x, (long)Dl * x));
     GemmBatch g3 = rowmajor(4, x * Dl, x, Dl * x, (long)Dl * x, x, x);
     g3.accumulate = 1;
     for (int i = 0; i < 4; ++i) {
@@ -1407,7 +1525,11 @@ int backward(Run& r, const VjpView& v, const Dims& m, Bufs& b, const State& in,
       g4.C[i] = b.Gb[i];                                   // CT_bar [a][(q,y)]
     }
     VTRY(gemm(r, g4));
-    for (int i = 0; i < 4; ++i) VTRY(transpose(r, in.T[i], b.Ga[i], x, (long)Dl * x));
+    for (int i = 0; i < 4; ++i) {
+      ma.src[i] = in.T[i];
+      ma.dst[i] = b.Ga[i];
+    }
+    VTRY(transpose_many(r, ma, 4, x, (long)Dl * x));
     GemmBatch g5 = rowmajor(4, x, x, Dl * x, (long)Dl * x, x, x);
     for (int i = 0; i < 4; ++i) {
       g5.A[i] = b.Gb[i];
