@@ -126,24 +126,25 @@ inline void gemm_set_rowmajor_c(GemmBatch& g, long ldc) {
 // Accumulation is float64 for F64 inputs and float32 otherwise.
 int launch_gemm(const GemmBatch& g, DT ta, DT tb, DT tc, hipStream_t s);
 // Whether a float64 product is small: its workgroups then split K over their
-// wavefronts.  launch_gemm, launch_gemm_si and launch_gemm_f64_any send such
-// products there; its bits do not depend on the grid either.
+// wavefronts; or else runs on whole tiles of the split kernel: at least 64 rows
+// (its tiles have 128 or more) and more than one slice of K.  launch_gemm sends
+// such products there.  Their bits do not depend on the grid, but differ from
+// the tile kernels'.
 bool gemm_short_applies(const GemmBatch& g);
+bool gemm_whole_applies(const GemmBatch& g);
 // float64 C = op(A) B with N <= 160 (the enlarged corner applied to an
-// isometry block); other shapes fall back to launch_gemm.
-int launch_gemm_si(const GemmBatch& g, hipStream_t s);
-// The same product with the (192-row tile, 16-wide K slice) space split
-// evenly over ncu workgroups of 8 wavefronts (one per CU; at most
-// kSplitMaxCus) and the cut tiles summed by a second kernel in a fixed order;
-// scratch holds gemm_si_scratch_bytes().  Other shapes: launch_gemm_si.
+// isometry block) with the (tile, 16-wide K slice) space split evenly over ncu
+// workgroups of 8 wavefronts (one per CU; at most kSplitMaxCus) and the cut
+// tiles summed by a second kernel in a fixed order; scratch holds
+// gemm_si_scratch_bytes().  Other shapes: launch_gemm.
 constexpr int kSplitMaxCus = 256;
 size_t gemm_si_scratch_bytes();
 bool gemm_si_balanced_useful(int count, int M, int N, int K, int ncu);
 bool gemm_si_balanced_applies(const GemmBatch& g, const void* scratch, int ncu);
 int launch_gemm_si_balanced(const GemmBatch& g, double* scratch, int ncu, hipStream_t s);
 // A float64 product of any width on the split kernel where K is long (tile and
-// ranges by estimated cycles; without scratch no tile is cut), else on the
-// tile kernels.
+// ranges by estimated cycles; cut tiles where K >= 256 and there is scratch),
+// else as launch_gemm.
 int launch_gemm_f64_any(const GemmBatch& g, double* scratch, int ncu, hipStream_t s);
 // float32 contractions of the same shape: A float32, B and C float64 (B
 // rounded to float32, float32 accumulation); other shapes fall back to
@@ -166,10 +167,8 @@ struct GroupItem {
   int tiles_m, tiles_n;
   long first;
 };
-// Tile kernel for a group (below 0: small products, all of the group or none;
-// 0: the 96 x 160 skinny tile, which needs N <= 160
-// and 16-byte aligned rows in every descriptor; else an index into the
-// generic tile shapes), chosen from the descriptors.
+// Kernel for a group, chosen from the descriptors: below 0 small products (all
+// of the group or none), else an index into the generic tile shapes.
 int grouped_kind(const GemmBatch* gs, int n);
 // Fills items[0..n) for the kind and returns the total number of work items.
 long grouped_fill(const GemmBatch* gs, int n, int kind, GroupItem* items);

@@ -627,8 +627,8 @@ int apply_step(ctm_ctx* c, int count, const int* ci, const int* trans, double* c
     const int chk = check_gemm(c, g, DT::F64, DT::F64, DT::F64);
     if (chk) return chk;
     // the split kernel sums cut tiles in its own order: kept as its own launch
-    // so that the product has the bits of a solo move; the tile kernels give
-    // the same bits in any grid and are grouped
+    // so that the product has the bits of a solo move; the bits of other
+    // products do not depend on the grid
     if (!gemm_short_applies(g) && gemm_si_balanced_applies(g, c->sk_part, c->sk_cus)) {
       double* part = c->sk_part;
       const int cus = c->sk_cus;
@@ -652,7 +652,7 @@ int apply_step(ctm_ctx* c, int count, const int* ci, const int* trans, double* c
   const int chk = check_gemm(c, g, DT::F64, DT::F64, DT::F64);
   if (chk) return chk;
   ProfScope ps(c, PC_SI_APPLY, gemm_flops(g), bytes);
-  if (gemm_short_applies(g)) return launch_gemm_si(g, c->st);
+  if (gemm_short_applies(g)) return launch_gemm(g, DT::F64, DT::F64, DT::F64, c->st);
   return launch_gemm_si_balanced(g, c->sk_part, c->sk_cus, c->st);
 }
 
@@ -1187,7 +1187,7 @@ int c4v_projectors(ctm_ctx* c, int mode, int keep) {
       const int chk = check_gemm(c, g, DT::F64, DT::F64, DT::F64);
       if (chk) return chk;
       ProfScope ps(c, PC_SI_APPLY, gemm_flops(g), (double)N1 * N1 * 8 + 2.0 * N1 * k * 8);
-      if (gemm_short_applies(g)) return launch_gemm_si(g, c->st);
+      if (gemm_short_applies(g)) return launch_gemm(g, DT::F64, DT::F64, DT::F64, c->st);
       return launch_gemm_si_balanced(g, c->sk_part, c->sk_cus, c->st);
     };
     for (int step = 0; step < c->cfg.n_si; ++step) {
@@ -1495,10 +1495,10 @@ int drain(ctm_ctx* c) {
 // operations; step i of every context is then launched together on one
 // stream: the float64 GEMMs of the step as one persistent grouped launch
 // over a device table of (descriptor, tile) work items (two where some are
-// small), the other operations one after another.  Contexts are independent, so only each context's own
-// order matters, and every product gets the bits of the solo move (the tile
-// kernels do not depend on the grid; the split SI kernel, whose summation
-// order does, keeps its own launch).
+// small), the other operations one after another.  Contexts are independent,
+// so only each context's own order matters, and every product gets the bits of
+// the solo move (small products and the tile kernels do not depend on the grid;
+// the split kernel's products keep their own launches).
 // ---------------------------------------------------------------------------
 constexpr int kBatchMaxDevices = 64;
 
@@ -1570,13 +1570,16 @@ int enqueue_batch(ctm_ctx* const* ctxs, int n) {
   }
   // the grouped GEMMs of every step, in one table
   std::vector<GemmBatch> gs;
-  // two groups per step: the small products, then the others
+  // two groups per step: the small products, then those on the tile kernels;
+  // whole tiles of the split kernel have bits of their own and fill the chip
+  // alone, so those keep their own launches
+  auto grouped = [](const BatchOp& op) { return op.gemm && !gemm_whole_applies(op.g); };
   std::vector<std::pair<size_t, int>> span(2 * steps);   // (first item, items) per group
   std::vector<std::pair<long, int>> plan(2 * steps);     // (work items, kind) per group
   for (size_t t = 0; t < 2 * steps; ++t) {
     span[t] = {gs.size(), 0};
     for (auto& v : ops)
-      if (t / 2 < v.size() && v[t / 2].gemm && gemm_short_applies(v[t / 2].g) == (t % 2 == 0))
+      if (t / 2 < v.size() && grouped(v[t / 2]) && gemm_short_applies(v[t / 2].g) == (t % 2 == 0))
         gs.push_back(v[t / 2].g);
     span[t].second = (int)(gs.size() - span[t].first);
   }
@@ -1618,8 +1621,9 @@ int enqueue_batch(ctm_ctx* const* ctxs, int n) {
         TRY_B(launch_gemm_grouped(tb.dev + span[u].first, span[u].second, plan[u].first,
                                   plan[u].second, S));
     for (size_t i = 0; i < grp.size(); ++i)
-      if (t < ops[i].size() && !ops[i][t].gemm) {
-        const int r = ops[i][t].fn(S);
+      if (t < ops[i].size() && !grouped(ops[i][t])) {
+        const BatchOp& op = ops[i][t];
+        const int r = op.gemm ? launch_gemm(op.g, DT::F64, DT::F64, DT::F64, S) : op.fn(S);
         if (r) return fail(grp[i], r == 1 ? CTM_E_ARG : r, g_err.empty() ? "batched launch" : g_err);
       }
   }
@@ -2516,7 +2520,7 @@ ctm_status ctm_gemm_f64(int count, const double* const* A, const double* const* 
     g.C[i] = C[i];
     g.transA[i] = trans_a;
   }
-  int r = launch_gemm_si(g, (hipStream_t)stream);   // skinny kernel when N <= 160
+  int r = launch_gemm(g, DT::F64, DT::F64, DT::F64, (hipStream_t)stream);
   return r ? CTM_E_DEVICE : CTM_OK;
 }
 
@@ -2550,7 +2554,7 @@ ctm_status ctm_gemm_f64_split(int count, const double* const* A, const double* c
   const bool split = aligned && gemm_si_balanced_applies(g, scratch, ncu);
   if (used_split) *used_split = split ? 1 : 0;
   const int r = split ? launch_gemm_si_balanced(g, (double*)scratch, ncu, (hipStream_t)stream)
-                      : launch_gemm_si(g, (hipStream_t)stream);
+                      : launch_gemm(g, DT::F64, DT::F64, DT::F64, (hipStream_t)stream);
   return r ? CTM_E_DEVICE : CTM_OK;
 }
 

@@ -205,193 +205,10 @@ __global__ __launch_bounds__(256) void gemm_k4(GemmBatch g, int tiles_m, int til
   k4_tile<TA, TB, TC, CT, BM, BN, WGM, WGN>(g, prob, batch, tile / tiles_n, tile % tiles_n, As, Bs);
 }
 
-// ---------------------------------------------------------------------------
-// Skinny float64 path for C (M x N) = op(A) (M x K) B (K x N) with N <= BN:
-// the enlarged corner applied to an N x k isometry block.  One workgroup owns
-// a BM x BN tile (the whole width of B), so A is streamed from HBM exactly
-// once; K is staged through double-buffered LDS in BK slices with 16-byte
-// global loads, one barrier per slice.  The launch is flattened over
-// (problem, tile) and dealt to the XCDs in contiguous chunks, so the
-// workgroups of one problem share an L2 and its slice of B.
-// ROLE only separates instantiations (and kernel names in profiles).
-// ---------------------------------------------------------------------------
 typedef double v2d __attribute__((ext_vector_type(2)));
 
-// LDS layouts of the A slice: transposed operands arrive m-contiguous and are
-// kept as [k][m] (rows padded by 16 doubles); plain ones arrive
-// k-contiguous and are kept as [m][k] with rows of BK + 1 doubles, so that
-// both the 16-byte row loads and the fragment reads (16 consecutive m at
-// fixed k per lane group) avoid bank conflicts.
-// Two adjacent doubles: one 16-byte load, or two 8-byte ones where odd
-// leading dimensions leave every other row 8-byte aligned only.
-template <bool ODD>
-__device__ __forceinline__ v2d ld_pair(const double* p) {
-  if (ODD) {
-    v2d v;
-    v.x = p[0];
-    v.y = p[1];
-    return v;
-  }
-  return *(const v2d*)p;
-}
-
-template <int BM, int BK>
-struct SkinnyA {
-  static constexpr int LT = BM + 16;          // [k][m] row length
-  static constexpr int LN = BK + 1;           // [m][k] row length
-  static constexpr int SIZE = (BK * LT > BM * LN) ? BK * LT : BM * LN;
-};
-
-template <int BM, int BN, int WGM, int WGN, bool TRANS, bool ODD = false>
-__device__ __forceinline__ void skinny_tile(const GemmBatch& g, int tiles_m, int tiles_n, int lin,
-                                            double (*As)[SkinnyA<BM, 16>::SIZE],
-                                            double (*Bs)[16][BN + 16]) {
-  constexpr int BK = 16;
-  using AL = SkinnyA<BM, BK>;
-  constexpr int WTM = BM / WGM, WTN = BN / WGN;
-  constexpr int MI = WTM / 16, NI = WTN / 16;
-  constexpr int NT = 64 * WGM * WGN;                   // threads per workgroup
-  constexpr int NA = BM * BK / 2, NB = BN * BK / 2;    // 16-byte loads per slice
-  constexpr int VA = (NA + NT - 1) / NT, VB = (NB + NT - 1) / NT;
-  static_assert(WTM % 16 == 0 && WTN % 16 == 0, "wave tile multiple of 16");
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave % WGM, wn = wave / WGM;
-  const int per_prob = tiles_m * tiles_n;
-  const int pb = lin / per_prob, tile = lin % per_prob;
-  const int prob = pb / g.nbatch, batch = pb % g.nbatch;
-  const int tn = tile % tiles_n, tm = tile / tiles_n;
-  const int m0 = tm * BM, n0 = tn * BN;
-  const int M = g.M, N = g.N, K = g.K;
-  const double* A = (const double*)g.A[prob] + (long)batch * g.a_bs;
-  const double* B = (const double*)g.B[prob] + (long)batch * g.b_bs;
-  double* C = (double*)g.C[prob] + (long)batch * g.c_bs;
-  const long lda = g.lda, ldb = g.ldb;
-
-  v2d ra[VA], rb[VB];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int e = 0; e < VA; ++e) {
-      const int i = tid + e * NT;
-      v2d v = {0.0, 0.0};
-      if (i < NA) {
-        if (TRANS) {
-          const int gk = k0 + i / (BM / 2), gm = m0 + 2 * (i % (BM / 2));
-          if (gk < K) {
-            const double* p = A + (long)gk * lda + gm;
-            if (gm + 1 < M) v = ld_pair<ODD>(p);
-            else if (gm < M) v.x = p[0];
-          }
-        } else {
-          const int gm = m0 + i / (BK / 2), gk = k0 + 2 * (i % (BK / 2));
-          if (gm < M) {
-            const double* p = A + (long)gm * lda + gk;
-            if (gk + 1 < K) v = ld_pair<ODD>(p);
-            else if (gk < K) v.x = p[0];
-          }
-        }
-      }
-      ra[e] = v;
-    }
-#pragma unroll
-    for (int e = 0; e < VB; ++e) {
-      const int i = tid + e * NT;
-      const int gk = k0 + i / (BN / 2), gn = n0 + 2 * (i % (BN / 2));
-      v2d v = {0.0, 0.0};
-      if (i < NB && gk < K) {
-        const double* p = B + (long)gk * ldb + gn;
-        if (gn + 1 < N) v = ld_pair<ODD>(p);
-        else if (gn < N) v.x = p[0];
-      }
-      rb[e] = v;
-    }
-  };
-  auto store = [&](int buf) {
-#pragma unroll
-    for (int e = 0; e < VA; ++e) {
-      const int i = tid + e * NT;
-      if (i < NA) {
-        if (TRANS) {
-          const int kk = i / (BM / 2), m = 2 * (i % (BM / 2));
-          *(v2d*)&As[buf][kk * AL::LT + m] = ra[e];
-        } else {
-          const int m = i / (BK / 2), kk = 2 * (i % (BK / 2));
-          As[buf][m * AL::LN + kk] = ra[e].x;
-          As[buf][m * AL::LN + kk + 1] = ra[e].y;
-        }
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < VB; ++e) {
-      const int i = tid + e * NT;
-      if (i < NB) *(v2d*)&Bs[buf][i / (BN / 2)][2 * (i % (BN / 2))] = rb[e];
-    }
-  };
-
-  v4d acc[MI][NI];
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < NI; ++j) acc[i][j] = v4d{0, 0, 0, 0};
-
-  const int nk = (K + BK - 1) / BK;
-  load(0);
-  store(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) load((kt + 1) * BK);
-#pragma unroll
-    for (int ks = 0; ks < BK; ks += 4) {
-      double a[MI], b[NI];
-      const int kr = ks + (lane >> 4);
-#pragma unroll
-      for (int i = 0; i < MI; ++i) {
-        const int m = wm * WTM + i * 16 + (lane & 15);
-        a[i] = TRANS ? As[buf][kr * AL::LT + m] : As[buf][m * AL::LN + kr];
-      }
-#pragma unroll
-      for (int j = 0; j < NI; ++j) b[j] = Bs[buf][kr][wn * WTN + j * 16 + (lane & 15)];
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    if (kt + 1 < nk) store(buf ^ 1);
-    __syncthreads();
-  }
-
-  long offn[NI];
-  bool okn[NI];
-#pragma unroll
-  for (int j = 0; j < NI; ++j) {
-    const int n = n0 + wn * WTN + j * 16 + (lane & 15);
-    okn[j] = n < N;
-    offn[j] = okn[j] ? map2(n, g.cdiv_n, g.cs_n1, g.cs_n0) : 0;
-  }
-  const double alpha = g.alpha;
-#pragma unroll
-  for (int i = 0; i < MI; ++i) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int m = m0 + wm * WTM + i * 16 + (lane >> 4) + 4 * r;
-      if (m >= M) continue;
-      const long offm = map2(m, g.cdiv_m, g.cs_m1, g.cs_m0);
-#pragma unroll
-      for (int j = 0; j < NI; ++j) {
-        if (!okn[j]) continue;
-        double* p = C + offm + offn[j];
-        double v = alpha * acc[i][j][r];
-        if (g.accumulate) v += *p;
-        *p = v;
-      }
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------
-// Float32 form of the double-buffered skinny tile, for the float32
+// Double-buffered tile as wide as B, for the float32
 // contractions with long K (the site absorptions of the corners and of the
 // edges' renormalisation, 20736 x 1296 x 1296 per corner at D = 6, and
 // Zc = Ct P_l): operands of type TA / TB are rounded to float32 on their way
@@ -642,7 +459,7 @@ struct SkTile {
 // problem prob (n0 < N, even).
 // ONE: N == 1 (B has no pairs of columns).
 template <int MI, int NI, int WN, bool TRANS, bool ONE>
-__device__ __forceinline__ void sk_segment(const GemmBatch& g, int prob, int m0, int n0, int s0, int s1,
+__device__ __forceinline__ void sk_segment(const GemmBatch& g, int prob, int batch, int m0, int n0, int s0, int s1,
                                            double (*Bs)[16][SkTile<MI, NI, WN>::LB],
                                            v4d (&acc)[MI][NI]) {
   using S = SkTile<MI, NI, WN>;
@@ -652,8 +469,8 @@ __device__ __forceinline__ void sk_segment(const GemmBatch& g, int prob, int m0,
   const int wm = wave / WN, wn = wave % WN;
   const int M = g.M, N = g.N, K = g.K;
   const long lda = g.lda, ldb = g.ldb;
-  const double* A = (const double*)g.A[prob];
-  const double* B = (const double*)g.B[prob];
+  const double* A = (const double*)g.A[prob] + (long)batch * g.a_bs;
+  const double* B = (const double*)g.B[prob] + (long)batch * g.b_bs;
   const int full = K / BK;   // slices before the partial one
   const int sf = min(s1, full);
 
@@ -828,20 +645,21 @@ __global__ __launch_bounds__(512, 2) void gemm_streamk_f64(GemmBatch g, StreamK 
     const int pos = max(tile * sk.nslices, begin);
     const int s0 = pos - tile * sk.nslices, s1 = pend - tile * sk.nslices;
     const int col = tile / sk.tiles_m, m0 = (tile % sk.tiles_m) * BM;
-    const int prob = col / sk.tiles_n, n0 = (col % sk.tiles_n) * BN;
+    const int pb = col / sk.tiles_n, n0 = (col % sk.tiles_n) * BN;
+    const int prob = pb / g.nbatch, batch = pb % g.nbatch;
     v4d acc[MI][NI];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NI; ++j) acc[i][j] = v4d{0, 0, 0, 0};
     if (g.transA[prob])
-      sk_segment<MI, NI, WN, true, ONE>(g, prob, m0, n0, s0, s1, Bs, acc);
+      sk_segment<MI, NI, WN, true, ONE>(g, prob, batch, m0, n0, s0, s1, Bs, acc);
     else
-      sk_segment<MI, NI, WN, false, ONE>(g, prob, m0, n0, s0, s1, Bs, acc);
+      sk_segment<MI, NI, WN, false, ONE>(g, prob, batch, m0, n0, s0, s1, Bs, acc);
     const int mw = wm * MI * 16 + (lane >> 4), nw = wn * NI * 16 + (lane & 15);
     if (s0 == 0 && s1 == sk.nslices) {
       // the whole tile: written here
-      double* C = (double*)g.C[prob];
+      double* C = (double*)g.C[prob] + (long)batch * g.c_bs;
       long offn[NI];
       bool okn[NI];
 #pragma unroll
@@ -1097,9 +915,9 @@ __global__ __launch_bounds__(256) void gemm_streamk_fixup(GemmBatch g, StreamK s
   const int wf = sk_owner(t0, sk), wl = sk_owner(t1 - 1, sk);
   if (wf == wl) return;
   const int col = tile / sk.tiles_m, m0 = (tile % sk.tiles_m) * BM;
-  const int prob = col / sk.tiles_n, n0 = (col % sk.tiles_n) * BN;
+  const int pb = col / sk.tiles_n, n0 = (col % sk.tiles_n) * BN;
   const int first_slot = sk_begin(wf, sk) < t0 ? 2 * wf + 1 : 2 * wf;
-  double* C = (double*)g.C[prob];
+  double* C = (double*)g.C[pb / g.nbatch] + (long)(pb % g.nbatch) * g.c_bs;
   constexpr int PR = BN / 2;   // column pairs per row
   for (int q = threadIdx.x; q < kFixRows * PR; q += 256) {
     const int ml = r0 + q / PR, nl = 2 * (q % PR), m = m0 + ml, n = n0 + nl;
@@ -1127,20 +945,6 @@ __global__ __launch_bounds__(256) void gemm_streamk_fixup(GemmBatch g, StreamK s
     *p0 = o0;
     if (two) *p1 = o1;
   }
-}
-
-template <int BM, int BN, int WGM, int WGN, int ROLE, bool ODD = false>
-__global__ __launch_bounds__(64 * WGM * WGN, 512 / (64 * WGM * WGN)) void gemm_skinny_f64(
-    GemmBatch g, int tiles_m, int tiles_n) {
-  __shared__ double As[2][SkinnyA<BM, 16>::SIZE];
-  __shared__ double Bs[2][16][BN + 16];
-  const int per_prob = tiles_m * tiles_n;
-  const int lin = xcd_remap(blockIdx.x, gridDim.x);
-  const int prob = lin / per_prob / g.nbatch;
-  if (g.transA[prob])
-    skinny_tile<BM, BN, WGM, WGN, true, ODD>(g, tiles_m, tiles_n, lin, As, Bs);
-  else
-    skinny_tile<BM, BN, WGM, WGN, false, ODD>(g, tiles_m, tiles_n, lin, As, Bs);
 }
 
 // ---------------------------------------------------------------------------
@@ -1267,22 +1071,6 @@ __device__ __forceinline__ int group_of(const GroupItem* items, int n, long w) {
     else hi = mid - 1;
   }
   return lo;
-}
-
-template <int BM, int BN, int WGM, int WGN>
-__global__ __launch_bounds__(64 * WGM * WGN, 512 / (64 * WGM * WGN)) void gemm_skinny_grouped(
-    const GroupItem* items, int nitems, long total) {
-  __shared__ double As[2][SkinnyA<BM, 16>::SIZE];
-  __shared__ double Bs[2][16][BN + 16];
-  for (long w = blockIdx.x; w < total; w += gridDim.x) {
-    const GroupItem& it = items[group_of(items, nitems, w)];
-    const int lin = (int)(w - it.first);
-    const int prob = lin / (it.tiles_m * it.tiles_n) / it.g.nbatch;
-    if (it.g.transA[prob])
-      skinny_tile<BM, BN, WGM, WGN, true>(it.g, it.tiles_m, it.tiles_n, lin, As, Bs);
-    else
-      skinny_tile<BM, BN, WGM, WGN, false>(it.g, it.tiles_m, it.tiles_n, lin, As, Bs);
-  }
 }
 
 template <int NT>
@@ -1665,24 +1453,6 @@ int launch_bx3(const GemmBatch& g, hipStream_t s) {
   return 0;
 }
 
-// The skinny kernel needs 16-byte aligned rows: even leading dimensions and
-// batch strides, 16-byte aligned base pointers.
-bool skinny_ok(const GemmBatch& g) {
-  if ((g.lda & 1) || (g.ldb & 1) || (g.a_bs & 1) || (g.b_bs & 1)) return false;
-  for (int i = 0; i < g.count; ++i)
-    if (((uintptr_t)g.A[i] & 15) || ((uintptr_t)g.B[i] & 15)) return false;
-  return true;
-}
-
-template <int BM, int BN, int WGM, int WGN, int ROLE, bool ODD = false>
-int launch_skinny(const GemmBatch& g, hipStream_t s) {
-  const int tm = ceil_div(g.M, BM), tn = ceil_div(g.N, BN);
-  dim3 grid(tm * tn * g.count * g.nbatch), block(64 * WGM * WGN);
-  gemm_skinny_f64<BM, BN, WGM, WGN, ROLE, ODD><<<grid, block, 0, s>>>(g, tm, tn);
-  CTM_HIP_TRY(hipGetLastError());
-  return 0;
-}
-
 // Estimated cycles of small products with 16 NT columns per workgroup: the
 // longest wavefront's slices (two wavefronts share a SIMD) times the
 // workgroups a CU takes in turn.
@@ -1737,21 +1507,17 @@ bool gemm_short_applies(const GemmBatch& g) {
 
 int grouped_kind(const GemmBatch* gs, int n) {
   if (n > 0 && gemm_short_applies(gs[0])) return -short_columns(gs, n);
-  bool skinny = true;
   int big = 0;
   double most = -1.0;
   for (int i = 0; i < n; ++i) {
-    skinny = skinny && gs[i].N <= 160 && skinny_ok(gs[i]);
     const double f = (double)gs[i].M * gs[i].N * (double)gs[i].K * gs[i].count * gs[i].nbatch;
     if (f > most) { most = f; big = i; }
   }
-  if (skinny) return 0;
-  return 1 + pick_tile(gs[big]);
+  return pick_tile(gs[big]);
 }
 
 long grouped_fill(const GemmBatch* gs, int n, int kind, GroupItem* items) {
-  const int bm = kind < 0 ? 16 : kind == 0 ? 96 : kTiles[kind - 1].bm;
-  const int bn = kind < 0 ? -16 * kind : kind == 0 ? 160 : kTiles[kind - 1].bn;
+  const int bm = kind < 0 ? 16 : kTiles[kind].bm, bn = kind < 0 ? -16 * kind : kTiles[kind].bn;
   long total = 0;
   for (int i = 0; i < n; ++i) {
     items[i].g = gs[i];
@@ -1775,10 +1541,8 @@ int launch_gemm_grouped(const GroupItem* items, int n, long total, int kind, hip
       case 4: gemm_short_grouped<4><<<grid, 512, 0, s>>>(items, n, total); break;
       default: gemm_short_grouped<5><<<grid, 512, 0, s>>>(items, n, total); break;
     }
-  } else if (kind == 0) {
-    gemm_skinny_grouped<96, 160, 2, 2><<<grid, 256, 0, s>>>(items, n, total);
   } else {
-    switch (kind - 1) {
+    switch (kind) {
       case 0: gemm_k4_grouped<128, 128, 2, 2><<<grid, 256, 0, s>>>(items, n, total); break;
       case 1: gemm_k4_grouped<128, 144, 4, 1><<<grid, 256, 0, s>>>(items, n, total); break;
       case 2: gemm_k4_grouped<64, 160, 2, 2><<<grid, 256, 0, s>>>(items, n, total); break;
@@ -1789,13 +1553,6 @@ int launch_gemm_grouped(const GroupItem* items, int n, long total, int kind, hip
   }
   CTM_HIP_TRY(hipGetLastError());
   return 0;
-}
-
-int launch_gemm_si(const GemmBatch& g, hipStream_t s) {
-  if (g.M <= 0 || g.N <= 0 || g.count <= 0 || g.nbatch <= 0) return 0;
-  if (gemm_short_applies(g)) return launch_short(g, s);
-  if (g.N > 160 || !skinny_ok(g)) return launch_gemm(g, DT::F64, DT::F64, DT::F64, s);
-  return launch_skinny<96, 160, 2, 2, 1>(g, s);
 }
 
 size_t gemm_si_scratch_bytes() { return (size_t)2 * kSplitMaxCus * 192 * 160 * sizeof(double); }
@@ -1840,7 +1597,7 @@ static int launch_streamk_f64(const GemmBatch& g, const StreamK& sk, hipStream_t
   CTM_HIP_TRY(hipGetLastError());
   if (sk.unit > 1) return 0;   // no tile is cut
   gemm_streamk_fixup<S::BM, S::BN>
-      <<<g.count * sk.tiles_m * sk.tiles_n * (S::BM / kFixRows), 256, 0, s>>>(g, sk);
+      <<<g.count * g.nbatch * sk.tiles_m * sk.tiles_n * (S::BM / kFixRows), 256, 0, s>>>(g, sk);
   CTM_HIP_TRY(hipGetLastError());
   return 0;
 }
@@ -1865,7 +1622,7 @@ static int launch_streamk_shape(const GemmBatch& g, const StreamK& sk, int rows,
 
 int launch_gemm_si_balanced(const GemmBatch& g, double* scratch, int ncu, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.count <= 0 || g.nbatch <= 0) return 0;
-  if (!gemm_si_balanced_applies(g, scratch, ncu)) return launch_gemm_si(g, s);
+  if (!gemm_si_balanced_applies(g, scratch, ncu)) return launch_gemm(g, DT::F64, DT::F64, DT::F64, s);
   const int rows = sk_rows(g.M, g.N);
   StreamK sk{};
   sk.nslices = ceil_div(g.K, 16);
@@ -1890,6 +1647,10 @@ int launch_gemm_si_balanced(const GemmBatch& g, double* scratch, int ncu, hipStr
 // 1024 185 -> 10 + 5, four 1024 x 1024 x 576 148 -> 98 (256 x 64), 4096 x 256 x
 // 256 29 -> 19.  Bound by the matrix cores where K is long (50 TF/s on these,
 // 61 on 192 x 160), else by the start of the ranges and the partial tiles.
+// Short K on whole tiles, where the tile kernels waited for a tile's first loads
+// and stores: eight 2500 x 2500 x 100 409 -> 257 us, four 5184 x 5184 x 144 639 ->
+// 590 (476 at the matrix cores' rate), 3600 x 3600 x 64 253 -> 172, 8192 x 64 x 64
+// 27 -> 14.
 namespace {
 struct SplitPlan {
   StreamK sk;
@@ -1902,7 +1663,7 @@ bool plan_split(const GemmBatch& g, bool cut_ok, int ncu, SplitPlan* best) {
   const long ns = ceil_div(g.K, 16);
   auto consider = [&](int rows, int cols) {
     const int tm = ceil_div(g.M, rows), tn = ceil_div(g.N, cols);
-    const long tiles = (long)tm * tn * g.count;
+    const long tiles = (long)tm * tn * g.count * g.nbatch;
     if (tiles * ns > (1L << 30)) return;
     // a slice: 2 matrix instructions of 64 cycles per SIMD, k step and 16 x 16
     // block of a wavefront, at the rate they reach with the loads between
@@ -1923,7 +1684,9 @@ bool plan_split(const GemmBatch& g, bool cut_ok, int ncu, SplitPlan* best) {
       best->sk.rem = (int)(units % nwg);
       best->sk.unit = unit;
     };
-    take(std::min<long>(tiles, ncu), tiles, (int)ns, 0.0);
+    // a tile's first loads, and its stores beside the other CUs' products
+    const long whole = std::min<long>(tiles, ncu);
+    take(whole, tiles, (int)ns, (tiles + whole - 1) / whole * (3000.0 + rows * cols / 2.0));
     const long nwg = sk_ranges(tiles * ns, ncu);
     // the second kernel's launch, and the partials written and read
     if (cut_ok && nwg >= 1) take(nwg, tiles * ns, 1, 14000.0 + (double)nwg * rows * cols * 16.0 / 1250.0);
@@ -1938,16 +1701,21 @@ bool plan_split(const GemmBatch& g, bool cut_ok, int ncu, SplitPlan* best) {
 }
 }  // namespace
 
-// Short K stays on the tile kernels (their tiles are smaller and hold several
-// workgroups per CU, which hides the ends of a tile; 256 x 1 x 256, where the
-// line lies, takes 10 to 14 us on either), and so do few rows, of which the
-// 128-row tiles would waste most, and inner batches, which have no range here.
+// Few rows leave much of the split kernel's tiles of 128 or more empty, which
+// long K makes up for by spreading the work: four of 64 x 8192 x 64 take 15.6 us on
+// the tile kernels and 17.5 here, of 64 x 8192 x 300 70 and 49.
+bool gemm_whole_applies(const GemmBatch& g) {
+  return !g.split && g.M >= (g.K >= 256 ? 64 : 97) && g.N > 0 && g.K > 16 && g.count > 0 &&
+         g.nbatch > 0 && !gemm_short_applies(g);
+}
+
+// Tiles are cut where K >= 256: below that the partial tiles outweigh what
+// the CUs would idle (243 x 32 x 243: 14 + 4 us cut, 10 us on a tile kernel).
 int launch_gemm_f64_any(const GemmBatch& g, double* scratch, int ncu, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.count <= 0 || g.nbatch <= 0) return 0;
   SplitPlan p{};
-  const bool cut_ok = scratch && ((uintptr_t)scratch & 15) == 0;
-  if (!gemm_short_applies(g) && g.nbatch == 1 && g.M >= 64 && g.K >= 256 && ncu >= 1 && ncu <= kSplitMaxCus &&
-      plan_split(g, cut_ok, ncu, &p)) {
+  if (scratch && ((uintptr_t)scratch & 15) == 0 && g.K >= 256 && ncu >= 1 && ncu <= kSplitMaxCus &&
+      gemm_whole_applies(g) && plan_split(g, true, ncu, &p)) {
     p.sk.part = scratch;
     return launch_streamk_shape(g, p.sk, p.rows, p.cols, s);
   }
@@ -1998,8 +1766,7 @@ bool pairs_ok(const GemmBatch& g) {
   return true;
 }
 
-// float32 contractions long enough for the double-buffered float32 tile
-// (the same shape rule as the float64 one below).
+// float32 contractions long enough for the double-buffered float32 tile.
 template <typename TA, typename TB, typename TC>
 bool launch_f32_db(const GemmBatch& g, hipStream_t s, int* rc) {
   if (g.K < 512 || g.M < 256 || !pairs_ok(g)) return false;
@@ -2018,34 +1785,6 @@ bool launch_f32_db(const GemmBatch& g, hipStream_t s, int* rc) {
   return true;
 }
 
-// float64 GEMMs long enough for the double-buffered tiles: N <= 160 takes
-// the 96 x 160 tile, wider N the 128 x 144 tile (144 divides the D^4 = 1296
-// columns of the double-layer absorptions at D = 6).
-bool launch_f64_db(const GemmBatch& g, hipStream_t s, int* rc) {
-  // short K (a few slices per tile) gains nothing from the double buffer,
-  // except on the wide products with many rows (the corner stems, K = chi),
-  // which the 256 x 144 tile covers with fewer, fuller workgroups
-  const bool wide = g.K >= 128 && g.N > 160 && (long)g.M * g.count * g.nbatch >= 16384;
-  if ((g.K < 512 && !wide) || g.M < 256) return false;
-  // odd leading dimensions or batch strides: the same tiles with operand
-  // pairs loaded one element at a time
-  if (!skinny_ok(g)) {
-    if (g.N <= 160)
-      *rc = launch_skinny<96, 160, 2, 2, 0, true>(g, s);
-    else if ((long)g.M * g.count * g.nbatch >= 16384)
-      *rc = launch_skinny<256, 144, 8, 1, 0, true>(g, s);
-    else
-      *rc = launch_skinny<128, 144, 4, 1, 0, true>(g, s);
-    return true;
-  }
-  if (g.N <= 160)
-    *rc = launch_skinny<96, 160, 2, 2, 0>(g, s);
-  else if ((long)g.M * g.count * g.nbatch >= 16384)
-    *rc = launch_skinny<256, 144, 8, 1, 0>(g, s);
-  else
-    *rc = launch_skinny<128, 144, 4, 1, 0>(g, s);
-  return true;
-}
 }  // namespace
 
 // Compute type: float64 when any operand is float64 and the mode is f64;
@@ -2068,9 +1807,10 @@ int launch_gemm(const GemmBatch& g, DT ta, DT tb, DT tc, hipStream_t s) {
     return 1;
   }
   if (ta == DT::F64 && tb == DT::F64) {
-    int rc = 0;
     if (tc == DT::F64 && gemm_short_applies(g)) return launch_short(g, s);
-    if (tc == DT::F64 && launch_f64_db(g, s, &rc)) return rc;
+    SplitPlan p{};
+    if (tc == DT::F64 && gemm_whole_applies(g) && plan_split(g, false, kSplitMaxCus, &p))
+      return launch_streamk_shape(g, p.sk, p.rows, p.cols, s);
     if (tc == DT::F64) return launch_k4<double, double, double, double>(g, s);
     if (tc == DT::F32) return launch_k4<double, double, float, double>(g, s);
   }
