@@ -25,6 +25,7 @@
 #include "common.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace sictm {
 namespace {
@@ -1453,12 +1454,15 @@ int launch_bx3(const GemmBatch& g, hipStream_t s) {
   return 0;
 }
 
-// Estimated cycles of small products with 16 NT columns per workgroup: the
-// longest wavefront's slices (two wavefronts share a SIMD) times the
-// workgroups a CU takes in turn.
-double short_cycles(const GemmBatch& g, int nt) {
-  const double wgs = (double)ceil_div(g.M, 16) * ceil_div(g.N, 16 * nt) * g.count;
-  return 4000.0 + ceil_div(ceil_div(g.K, 16), 8) * (600.0 + 512.0 * nt) * std::max(1.0, wgs / 256.0);
+// Workgroups of a small product with 16 nt columns each, and its estimated
+// microseconds: the launch with the first loads and the sums, and for each 256
+// workgroups the longest wavefront's slices (within 15 % of kernel times
+// measured from 32 x 20 x 32 to 1875 x 83 x 1875).
+double short_groups(const GemmBatch& g, int nt) {
+  return (double)ceil_div(g.M, 16) * ceil_div(g.N, 16 * nt) * g.count;
+}
+double short_us(const GemmBatch& g, int nt) {
+  return 3.9 + std::ceil(short_groups(g, nt) / 256.0) * ceil_div(ceil_div(g.K, 16), 8) * (0.31 + 0.32 * nt);
 }
 
 // Column blocks per workgroup that fit a set of small products best.
@@ -1467,7 +1471,7 @@ int short_columns(const GemmBatch* gs, int n) {
   double cost = 1e300;
   for (int nt = 1; nt <= 5; ++nt) {
     double c = 0.0;
-    for (int i = 0; i < n; ++i) c += short_cycles(gs[i], nt);
+    for (int i = 0; i < n; ++i) c += short_us(gs[i], nt);
     if (c < cost) {
       cost = c;
       best = nt;
@@ -1492,17 +1496,18 @@ int launch_short(const GemmBatch& g, hipStream_t s) {
 
 }  // namespace
 
-// Up to about 40000 estimated cycles, where the split kernel's balance begins to
-// count for more than its second launch, and 2600 blocks of 16 x 16 (short K: the
-// operands come from L2 once per 16 rows, which wide products with their larger
-// tiles read less often).  Measured, us, on the kernels used before and here:
-// 8 of 32 x 20 x 32 11 and 3, 8 of 512 x 37 x 512 24 and 10, 105 x 105 x 2500
-// 27 and 15, 4 of 1024 x 64 x 1024 30 and 20, 1024 x 64 x 64 17 and 8; beyond the
-// line, 8 of 1024 x 72 x 1024 41 and 50, 1024 x 1024 x 64 10.5 and 17.
+// Small: up to 24 estimated us, and two rounds of 256 workgroups, or one where a
+// wavefront has a single slice (K <= 128): beyond, the split kernel's tiles win,
+// which read their operands less often.  Measured kernel times, us, on the
+// kernels used before, on those tiles and here: 8 of 32 x 20 x 32 11, 5 and 4.5,
+// 8 of 512 x 37 x 512 24, 21 and 10, 105 x 105 x 2500 27, 70 and 15, 4 of 1024 x 64
+// x 1024 30, 38 and 19.5, 1875 x 83 x 1875 27, 61 and 23, 1024 x 64 x 64 17, 7 and
+// 4; beyond the line, 8 of 1024 x 72 x 1024 42, 50 and 50, 8 of 1024 x 72 x 72 21,
+// 9 and 13, 4 of 2500 x 100 x 105 18, 13 and 22, 512 x 512 x 64 11, 9 and 14.
 bool gemm_short_applies(const GemmBatch& g) {
   if (g.nbatch != 1 || g.split || g.M <= 0 || g.N <= 0 || g.count <= 0 || g.K <= 0) return false;
-  if ((double)ceil_div(g.M, 16) * ceil_div(g.N, 16) * g.count > 2600.0) return false;
-  return short_cycles(g, short_columns(&g, 1)) <= 40000.0;
+  const int nt = short_columns(&g, 1);
+  return short_us(g, nt) <= 24.0 && short_groups(g, nt) <= (g.K <= 128 ? 256.0 : 512.0);
 }
 
 int grouped_kind(const GemmBatch* gs, int n) {
