@@ -985,7 +985,7 @@ ctm_status ctm_cell_create(ctm_cell** out, const ctm_cell_config* cfg, const dou
   const size_t bytes = carve_cell(c, nullptr);
   if (hipStreamCreateWithFlags(&c->st, hipStreamNonBlocking) != hipSuccess)
     return bail(cfail(nullptr, CTM_E_DEVICE, "hipStreamCreate failed"));
-  if (hipMalloc((void**)&c->mem, bytes) != hipSuccess)
+  if (device_malloc((void**)&c->mem, bytes) != hipSuccess)
     return bail(cfail(nullptr, CTM_E_NOMEM, "hipMalloc of the cell workspace failed"));
   carve_cell(c, c->mem);
   const int Dl = c->Dl;
@@ -1049,6 +1049,7 @@ void ctm_cell_destroy(ctm_cell* cell) {
   if (cell->mem) (void)hipFree(cell->mem);
   if (cell->st) (void)hipStreamDestroy(cell->st);
   delete cell;
+  release_kept_blocks();
 }
 
 ctm_status ctm_cell_set_blocks(ctm_cell* cell, const double* X_dev, const double* Yt_dev) {

@@ -176,6 +176,12 @@ long grouped_fill(const GemmBatch* gs, int n, int kind, GroupItem* items);
 // device memory at dev_items.
 int launch_gemm_grouped(const GroupItem* dev_items, int n, long total, int kind, hipStream_t s);
 
+// hipMalloc on the current device; on failure the blocks that the standalone
+// factorisations keep there are freed and it is tried again.
+hipError_t device_malloc(void** p, size_t bytes);
+// Frees the kept blocks of the current device.
+void release_kept_blocks();
+
 // Householder QR (in place, Q returned with R_ii >= 0) of `count` N x k
 // row-major matrices.  ws must hold qr_workspace_bytes(count, N, k) bytes.
 size_t qr_workspace_bytes(int count, int N, int k);

@@ -2042,6 +2042,119 @@ int observable(ctm_ctx* c, int kind, const double* op_host, double* out_host) {
 
 }  // namespace
 
+// ---------------------------------------------------------------------------
+// Workspaces of ctm_qr_f64 and ctm_svd_f64.  hipMalloc and hipFree of the 71 MiB
+// of eight 5184 x 160 blocks took 340 us of 1180 a call, the kernels 840, so a
+// device keeps the last blocks: at most kKeptBlocks of together kKeptBytes.  A call
+// owns the block it has taken, and hands it back after its stream has been
+// synchronised, so blocks pass between threads and streams idle.  They are freed
+// when a context or cell is destroyed, when an allocation fails, and to make room.
+// Inside a stream capture, where no allocation is allowed, none is used.
+// ---------------------------------------------------------------------------
+namespace sictm {
+namespace {
+
+constexpr int kKeptBlocks = 4;
+constexpr size_t kKeptBytes = (size_t)256 << 20;
+
+struct KeptBlock {
+  void* p;
+  size_t bytes;
+};
+struct KeptSet {
+  KeptBlock b[kKeptBlocks];   // oldest first
+  int n;
+  size_t bytes;
+};
+std::mutex g_kept_mu;
+KeptSet g_kept[kBatchMaxDevices];
+
+int kept_device() {
+  int dev = 0;
+  return hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kBatchMaxDevices ? dev : -1;
+}
+
+KeptBlock kept_remove(KeptSet& k, int i) {
+  const KeptBlock b = k.b[i];
+  for (int j = i + 1; j < k.n; ++j) k.b[j - 1] = k.b[j];
+  --k.n;
+  k.bytes -= b.bytes;
+  return b;
+}
+
+// The workspace of one call on `stream`; p is null where the allocation failed.
+struct CallScratch {
+  void* p = nullptr;
+  size_t bytes;
+  hipStream_t stream;
+  int dev = -1;
+  bool idle = false;
+
+  CallScratch(size_t need, hipStream_t s) : bytes(need), stream(s) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone)
+      dev = kept_device();
+    if (dev >= 0) {
+      std::lock_guard<std::mutex> lock(g_kept_mu);
+      KeptSet& k = g_kept[dev];
+      int best = -1;
+      for (int i = 0; i < k.n; ++i)
+        if (k.b[i].bytes >= need && (best < 0 || k.b[i].bytes < k.b[best].bytes)) best = i;
+      if (best >= 0) {
+        const KeptBlock b = kept_remove(k, best);
+        p = b.p;
+        bytes = b.bytes;
+        return;
+      }
+    }
+    const hipError_t e = dev >= 0 ? device_malloc(&p, need) : hipMalloc(&p, need);
+    if (e != hipSuccess) p = nullptr;
+  }
+  // ends the call: its kernels have run
+  void finish() { idle = hipStreamSynchronize(stream) == hipSuccess; }
+  ~CallScratch() {
+    if (!p) return;
+    KeptBlock out[kKeptBlocks + 1];
+    int n = 0;
+    if (idle && dev >= 0 && bytes <= kKeptBytes) {
+      std::lock_guard<std::mutex> lock(g_kept_mu);
+      KeptSet& k = g_kept[dev];
+      while (k.n == kKeptBlocks || k.bytes + bytes > kKeptBytes) out[n++] = kept_remove(k, 0);
+      k.b[k.n++] = {p, bytes};
+      k.bytes += bytes;
+    } else {
+      out[n++] = {p, bytes};
+    }
+    for (int i = 0; i < n; ++i) (void)hipFree(out[i].p);
+  }
+  CallScratch(const CallScratch&) = delete;
+  CallScratch& operator=(const CallScratch&) = delete;
+};
+
+}  // namespace
+
+void release_kept_blocks() {
+  const int dev = kept_device();
+  if (dev < 0) return;
+  KeptSet k;
+  {
+    std::lock_guard<std::mutex> lock(g_kept_mu);
+    k = g_kept[dev];
+    g_kept[dev] = KeptSet{};
+  }
+  for (int i = 0; i < k.n; ++i) (void)hipFree(k.b[i].p);
+}
+
+hipError_t device_malloc(void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipSuccess) return e;
+  (void)hipGetLastError();
+  release_kept_blocks();
+  return hipMalloc(p, bytes);
+}
+
+}  // namespace sictm
+
 // ===========================================================================
 // C ABI
 // ===========================================================================
@@ -2102,7 +2215,7 @@ ctm_status ctm_init(ctm_ctx** out, const ctm_config* cfg, const double* site_dev
     }
     c->ws = workspace;
   } else {
-    if (hipMalloc(&c->ws, need) != hipSuccess) {
+    if (device_malloc(&c->ws, need) != hipSuccess) {
       delete c;
       return (ctm_status)fail(nullptr, CTM_E_NOMEM, "hipMalloc of the workspace failed");
     }
@@ -2197,6 +2310,7 @@ void ctm_destroy(ctm_ctx* c) {
   if (c->rb) rocblas_destroy_handle(c->rb);
   if (c->own_ws && c->ws) (void)hipFree(c->ws);
   delete c;
+  release_kept_blocks();
 }
 
 ctm_status ctm_set_isometries(ctm_ctx* c, const double* X_dev, const double* Yt_dev) {
@@ -2561,12 +2675,10 @@ ctm_status ctm_gemm_f64_split(int count, const double* const* A, const double* c
 ctm_status ctm_qr_f64(int count, double* const* W, int N, int k, void* stream) {
   if (count < 0 || count > kMaxProb || !W || k < 1 || N < k)
     return (ctm_status)fail(nullptr, CTM_E_ARG, "invalid qr arguments");
-  void* ws = nullptr;
-  if (hipMalloc(&ws, qr_workspace_bytes(count, N, k)) != hipSuccess)
-    return (ctm_status)fail(nullptr, CTM_E_NOMEM, "hipMalloc failed");
-  int r = launch_qr(count, W, N, k, ws, (hipStream_t)stream);
-  (void)hipStreamSynchronize((hipStream_t)stream);
-  (void)hipFree(ws);
+  CallScratch ws(qr_workspace_bytes(count, N, k), (hipStream_t)stream);
+  if (!ws.p) return (ctm_status)fail(nullptr, CTM_E_NOMEM, "hipMalloc failed");
+  int r = launch_qr(count, W, N, k, ws.p, (hipStream_t)stream);
+  ws.finish();
   return r ? (ctm_status)(r == 1 ? CTM_E_ARG : r) : CTM_OK;
 }
 
@@ -2637,12 +2749,10 @@ ctm_status ctm_svd_f64(int count, const double* const* rho, double* const* u, do
                        double* const* v, int n, void* stream) {
   if (count < 0 || count > kMaxProb || !rho || !s || n < 1)
     return (ctm_status)fail(nullptr, CTM_E_ARG, "invalid svd arguments");
-  void* ws = nullptr;
-  if (hipMalloc(&ws, svd_workspace_bytes(count, n)) != hipSuccess)
-    return (ctm_status)fail(nullptr, CTM_E_NOMEM, "hipMalloc failed");
-  int r = launch_svd(count, rho, u, s, v, n, ws, (hipStream_t)stream);
-  (void)hipStreamSynchronize((hipStream_t)stream);
-  (void)hipFree(ws);
+  CallScratch ws(svd_workspace_bytes(count, n), (hipStream_t)stream);
+  if (!ws.p) return (ctm_status)fail(nullptr, CTM_E_NOMEM, "hipMalloc failed");
+  int r = launch_svd(count, rho, u, s, v, n, ws.p, (hipStream_t)stream);
+  ws.finish();
   return r ? (ctm_status)(r == 1 ? CTM_E_ARG : r) : CTM_OK;
 }
 

@@ -214,8 +214,8 @@ __device__ __forceinline__ bool plane_rotation(double al, double be, double ga, 
 // U and V (U alone for values only) fit the LDS; above that the block-pair
 // kernels spread the columns over several CUs.  Measured, 4 random matrices with
 // vectors, before (block pairs of 16 columns at every size) and after: n = 20
-// 374 and 176 us, 64 872 and 497, 87 1724 and 1032, 96 1630 and 1108; values
-// only, n = 100: 1732 and 1149.
+// 374 and 154 us, 64 872 and 480, 87 1724 and 950, 96 1630 and 1013; values
+// only, n = 100: 1732 and 1066.
 template <int RPL, bool WANT_V>
 struct SmallSvd {
   static constexpr int ROWS = 16 * RPL;
@@ -373,8 +373,8 @@ void launch_small_svd(const SvdArgs& a, int count, hipStream_t s) {
 // number of rows per lane (n <= 16 RPL).  Bound by the latency of a step, like
 // svd_small, and by the grid barriers.  A column of the first block stays in
 // registers, norms are tracked, and blocks are no wider than n needs: 4 random
-// matrices with vectors, n = 100: 2132 -> 1674 us, 144: 3237 -> 2661, 160:
-// 3328 -> 2772.
+// matrices with vectors, n = 100: 2132 -> 1588 us, 144: 3237 -> 2562, 160:
+// 3328 -> 2675.
 template <int RPL>
 struct RoundLds {
   static constexpr int kC = 2 * kBlk;

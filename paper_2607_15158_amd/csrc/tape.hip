@@ -350,7 +350,7 @@ int Tape::reserve() {
     if (mem_) (void)hipFree(mem_);
     mem_ = nullptr;
     cap_ = 0;
-    if (hipMalloc((void**)&mem_, need) != hipSuccess)
+    if (device_malloc((void**)&mem_, need) != hipSuccess)
       return fail(CTM_E_NOMEM, "hipMalloc of the adjoint tape (" + std::to_string(need >> 20) +
                                    " MiB) failed");
     cap_ = need;
