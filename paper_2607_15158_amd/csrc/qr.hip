@@ -29,6 +29,8 @@
 
 #include "common.h"
 
+#include <type_traits>
+
 namespace sictm {
 namespace {
 
@@ -356,13 +358,6 @@ __device__ __forceinline__ void leaf_factor(const QrArgs& q, int p, int leaf, in
     q.Tl[sl * kPanel * kPanel + idx] = sh.T[idx / kPanel][idx % kPanel];
 }
 
-// R register rows of NW wavefronts hold leaves of up to 4 NW R rows.
-template <int R, int NW>
-__global__ __launch_bounds__(64 * NW) void qr_leaf_factor(QrArgs q, int p) {
-  __shared__ PanelLds sh;
-  leaf_factor<R, NW>(q, p, blockIdx.x, blockIdx.y, sh);
-}
-
 // Top row of the w x w triangle a leaf holds during panel p.
 __device__ __forceinline__ int top_row(const QrArgs& q, int leaf, int c0) {
   return leaf == 0 ? c0 : leaf_start(q, leaf);
@@ -672,6 +667,21 @@ union StageLds {
   WyLds wy;
 };
 
+// R register rows of NW wavefronts hold leaves of up to 4 NW R rows.  ALONE: the
+// leaf and the panel are the only ones, and Q is formed here, from what this
+// workgroup has just written.  Eight blocks of 32 x 20 took 15.1 and 9.3 us in two
+// launches and 23.2 in one, 243 x 32 32.9 and 15.1, and 46.1; the gap between the
+// launches goes too.
+template <int R, int NW, bool ALONE = false>
+__global__ __launch_bounds__(64 * NW) void qr_leaf_factor(QrArgs q, int p) {
+  __shared__ StageLds sh;
+  leaf_factor<R, NW>(q, p, blockIdx.x, blockIdx.y, sh.panel);
+  if (ALONE) {
+    __syncthreads();
+    leaf_wy<true, NW>(q, 0, 0, blockIdx.y, 0, sh.wy);
+  }
+}
+
 // After the leaf factors of panel p: the first tree level's factors (`next`
 // nodes per matrix; the first blocks, since the next launch waits for their
 // 32 serial steps) beside the leaves' trailing columns.
@@ -792,16 +802,25 @@ int launch_qr(int count, double* const* W, int N, int k, void* ws, hipStream_t s
     const int c0 = p * kPanel, w = std::min(kPanel, k - c0);
     const int trail = (k - c0 - w + kTrailN - 1) / kTrailN;
     const dim3 leaves(pl.nb, count);
-    if (leaf_rows <= 64)
-      qr_leaf_factor<4, 4><<<leaves, 256, 0, s>>>(q, p);
-    else if (leaf_rows <= 128)
-      qr_leaf_factor<8, 4><<<leaves, 256, 0, s>>>(q, p);
-    else if (leaf_rows <= kLeafRows)
-      qr_leaf_factor<12, 4><<<leaves, 256, 0, s>>>(q, p);
-    else if (leaf_rows <= 256)
-      qr_leaf_factor<8, 8><<<leaves, 512, 0, s>>>(q, p);
-    else
-      qr_leaf_factor<12, 8><<<leaves, 512, 0, s>>>(q, p);
+    auto factor = [&](auto alone) {
+      constexpr bool A = decltype(alone)::value;
+      if (leaf_rows <= 64)
+        qr_leaf_factor<4, 4, A><<<leaves, 256, 0, s>>>(q, p);
+      else if (leaf_rows <= 128)
+        qr_leaf_factor<8, 4, A><<<leaves, 256, 0, s>>>(q, p);
+      else if (leaf_rows <= kLeafRows)
+        qr_leaf_factor<12, 4, A><<<leaves, 256, 0, s>>>(q, p);
+      else if (leaf_rows <= 256)
+        qr_leaf_factor<8, 8, A><<<leaves, 512, 0, s>>>(q, p);
+      else
+        qr_leaf_factor<12, 8, A><<<leaves, 512, 0, s>>>(q, p);
+    };
+    if (pl.nb == 1 && pl.P == 1) {
+      factor(std::true_type{});
+      CTM_HIP_TRY(hipGetLastError());
+      return 0;
+    }
+    factor(std::false_type{});
     int next = pl.depth > 0 ? nodes_at(1) : 0;   // nodes of the next level to factor
     const int stage = count * (pl.nb * trail + next);
     if (stage && leaf_rows <= kLeafRows)
