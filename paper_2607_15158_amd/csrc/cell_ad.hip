@@ -619,6 +619,21 @@ int impl_get_state_device(ctm_cell* cell, double* dev, size_t n) {
   if (!cur && !c->blocks_set) return afail(c, CTM_E_STATE, "no blocks to export");
   const size_t cc = (size_t)c->chi * c->chi * 8, tt = (size_t)c->chi * c->Dl * c->chi * 8,
                nk = (size_t)c->Nf * c->k * 8;
+  if (elem_device_range(dev, n * 8)) {   // all tensors by one kernel, else a copy each
+    PackList pack(c->st);
+    for (int s = 0; s < c->ns; ++s)
+      for (int i = 0; i < 4; ++i) {
+        pack.add(c->env[s].C[i], dev + L.C(s, i), (long)(cc / 8));
+        pack.add(c->env[s].T[i], dev + L.T(s, i), (long)(tt / 8));
+      }
+    for (int id = 0; id < 4 * c->ns; ++id) {
+      pack.add(cur ? c->X[id] : c->X0[id], dev + L.X(id), (long)(nk / 8));
+      pack.add(cur ? c->Y[id] : c->Y0[id], dev + L.Y(id), (long)(nk / 8));
+    }
+    ATRY(pack.flush());
+    CTM_HIP_TRY(hipStreamSynchronize(c->st));
+    return CTM_OK;
+  }
   for (int s = 0; s < c->ns; ++s)
     for (int i = 0; i < 4; ++i) {
       CTM_HIP_TRY(hipMemcpyAsync(dev + L.C(s, i), c->env[s].C[i], cc, hipMemcpyDeviceToDevice, c->st));
@@ -642,17 +657,27 @@ int impl_set_state_device(ctm_cell* cell, const double* dev, size_t n) {
   if (n != (size_t)L.total()) return afail(c, CTM_E_SHAPE, "wrong state size");
   const size_t cc = (size_t)c->chi * c->chi * 8, tt = (size_t)c->chi * c->Dl * c->chi * 8,
                nk = (size_t)c->Nf * c->k * 8;
+  const bool packed = elem_device_range(dev, n * 8);   // by one kernel, else a copy each
+  PackList pack(c->st);
+  auto load = [&](double* dst, const double* src, size_t bytes) -> int {
+    if (packed)
+      pack.add(src, dst, (long)(bytes / 8));
+    else
+      CTM_HIP_TRY(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, c->st));
+    return 0;
+  };
   for (int s = 0; s < c->ns; ++s)
     for (int i = 0; i < 4; ++i) {
       SiteEnv& e = c->env[s];
-      CTM_HIP_TRY(hipMemcpyAsync(e.C[i], dev + L.C(s, i), cc, hipMemcpyDeviceToDevice, c->st));
-      CTM_HIP_TRY(hipMemcpyAsync(e.T[i], dev + L.T(s, i), tt, hipMemcpyDeviceToDevice, c->st));
+      ATRY(load(e.C[i], dev + L.C(s, i), cc));
+      ATRY(load(e.T[i], dev + L.T(s, i), tt));
       e.Cd[i][0] = e.Cd[i][1] = e.Td[i][0] = e.Td[i][1] = c->chi;
     }
   for (int id = 0; id < 4 * c->ns; ++id) {
-    CTM_HIP_TRY(hipMemcpyAsync(c->X[id], dev + L.X(id), nk, hipMemcpyDeviceToDevice, c->st));
-    CTM_HIP_TRY(hipMemcpyAsync(c->Y[id], dev + L.Y(id), nk, hipMemcpyDeviceToDevice, c->st));
+    ATRY(load(c->X[id], dev + L.X(id), nk));
+    ATRY(load(c->Y[id], dev + L.Y(id), nk));
   }
+  ATRY(pack.flush());
   c->cur_set = true;
   c->last_mode = CTM_CELL_SI;
   CTM_HIP_TRY(hipStreamSynchronize(c->st));

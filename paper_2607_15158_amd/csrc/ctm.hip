@@ -2447,6 +2447,28 @@ int copy_state(ctm_ctx* c, double* dst, size_t n, bool device) {
   const size_t chi = c->chi, Dl = c->Dl, N = c->N, k = c->k;
   const size_t x = c->chi_env;
   const hipMemcpyKind kind = device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
+  if (device && elem_device_range(dst, need * sizeof(double))) {
+    // all tensors, and the zeros behind those of a growing environment, in one
+    // launch; the counters go by a copy of their own
+    const bool blocks = c->iso_pending || c->si_ready;
+    PackList pack(c->st);
+    double* p = dst;
+    auto add = [&](const double* src, size_t used, size_t room) {
+      pack.add(src, p, (long)used);
+      pack.add(nullptr, p + used, (long)(room - used));
+      p += room;
+    };
+    for (int i = 0; i < 4; ++i) add(c->C[c->cur][i], x * x, chi * chi);
+    for (int i = 0; i < 4; ++i) add(c->T[c->cur][i], x * Dl * x, chi * Dl * chi);
+    for (int i = 0; i < 4; ++i) add(blocks ? (c->iso_pending ? c->X0[i] : c->X[i]) : nullptr, N * k, N * k);
+    for (int i = 0; i < 4; ++i) add(blocks ? (c->iso_pending ? c->Yt0[i] : c->Yt[i]) : nullptr, N * k, N * k);
+    TRY(pack.flush());
+    const double tail[4] = {(double)c->chi_env, (double)c->si_moves, c->recycling ? 1.0 : 0.0,
+                            (double)c->si_upd};
+    CTM_HIP_TRY(hipMemcpyAsync(p, tail, sizeof(tail), hipMemcpyHostToDevice, c->st));
+    CTM_HIP_TRY(hipStreamSynchronize(c->st));
+    return CTM_OK;
+  }
   if (device) {
     CTM_HIP_TRY(hipMemsetAsync(dst, 0, need * sizeof(double), c->st));
   } else {

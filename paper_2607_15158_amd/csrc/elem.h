@@ -73,6 +73,35 @@ int elem_transpose(const double* src, double* dst, long rows, long cols, hipStre
 constexpr int kMaxSmallEig = 16;
 int elem_xi_from_ritz(const double* H, int m, int squarings, double* out, hipStream_t s);
 int elem_ratio(const double* a, const double* b, double* out, hipStream_t s);
+// dst[0 .. n) = src[0 .. n), or zeros where src is null, for a list of segments in
+// one launch per kPackSegs.
+struct PackSeg {
+  const double* src;
+  double* dst;
+  long n;
+};
+constexpr int kPackSegs = 64;
+int elem_pack(const PackSeg* segs, int count, hipStream_t s);
+// Collects segments and launches them kPackSegs at a time.
+struct PackList {
+  PackSeg segs[kPackSegs];
+  int count = 0, rc = 0;
+  hipStream_t st;
+  explicit PackList(hipStream_t s) : st(s) {}
+  void add(const double* src, double* dst, long n) {
+    if (n <= 0) return;
+    if (count == kPackSegs) flush();
+    segs[count++] = {src, dst, n};
+  }
+  int flush() {
+    if (!rc && count) rc = elem_pack(segs, count, st);
+    count = 0;
+    return rc;
+  }
+};
+// Whether [p, p + bytes) is memory of the current device inside one allocation
+// (what a copy checks by itself).
+bool elem_device_range(const void* p, size_t bytes);
 int elem_permute4(const double* src, void* dst, DT t, int n, long s0, long s1, long s2, long s3,
                   hipStream_t s);
 int elem_init_env(const double* a, const double* e, int n, double* const* C, double* const* T,
