@@ -724,7 +724,8 @@ __global__ __launch_bounds__(64 * NW, 2) void qr_leaf_form(QrArgs q, int p) {
   leaf_wy<true, NW>(q, p, blockIdx.x, blockIdx.y, blockIdx.z, sh);
 }
 
-QrPlan make_plan(int N, int k) {
+// wide: with eight-wavefront leaves where they pay.
+QrPlan make_plan(int N, int k, bool wide = true) {
   QrPlan pl;
   pl.N = N;
   pl.k = k;
@@ -745,7 +746,7 @@ QrPlan make_plan(int N, int k) {
   // above refuse stays refused)
   pl.wide = false;
   const int wnb = (N + kWideLeafRows - 1) / kWideLeafRows;
-  if ((N + nb - 1) / nb <= kLeafRows && levels(wnb) < pl.depth) {
+  if (wide && (N + nb - 1) / nb <= kLeafRows && levels(wnb) < pl.depth) {
     pl.wide = true;
     pl.nb = wnb;
     pl.depth = levels(wnb);
@@ -761,8 +762,11 @@ bool qr_plan_ok(int N, int k) {
   return pl.wide || (N + pl.nb - 1) / pl.nb <= kLeafRows;
 }
 
+// Sized by the four-wavefront leaves, whose number grows with N: callers carve
+// the workspace for their full N and also run fewer rows, whose plan may have more
+// leaves than the full one's tall leaves (1152 rows 3, 1100 rows 8).
 size_t qr_workspace_bytes(int count, int N, int k) {
-  const QrPlan pl = make_plan(N, k);
+  const QrPlan pl = make_plan(N, k, false);
   const size_t slots = (size_t)count * pl.P * pl.nb;
   const size_t n = 2 * slots * kPanel * kPanel + (size_t)count * N * k;
   return n * sizeof(double);
