@@ -642,11 +642,19 @@ __global__ __launch_bounds__(512, 2) void gemm_streamk_f64(GemmBatch g, StreamK 
   // phases and reuse each B slice from L2
   int pend = end;
   while (pend > begin) {
-    const int tile = (pend - 1) / sk.nslices;
-    const int pos = max(tile * sk.nslices, begin);
-    const int s0 = pos - tile * sk.nslices, s1 = pend - tile * sk.nslices;
-    const int col = tile / sk.tiles_m, m0 = (tile % sk.tiles_m) * BM;
-    const int pb = col / sk.tiles_n, n0 = (col % sk.tiles_n) * BN;
+    const int at = (pend - 1) / sk.nslices;
+    const int pos = max(at * sk.nslices, begin);
+    const int s0 = pos - at * sk.nslices, s1 = pend - at * sk.nslices;
+    // cut tiles go down the rows first (ranges side by side share B).  Whole ones
+    // are dealt out in turn along the columns, so that neighbouring columns are
+    // worked on side by side: where the output map sends columns of different
+    // tiles to one cache line, they meet in one L2 (four transposed 5184 x 5184 x
+    // 144 with every 144th column adjacent: 3.25 ms in contiguous ranges, 1.34 so)
+    const bool whole = sk.unit > 1;
+    const int tile = whole ? (at - begin / sk.nslices) * sk.nwg + w : at;
+    const int per = sk.tiles_m * sk.tiles_n, pb = tile / per, tt = tile % per;
+    const int m0 = (whole ? tt / sk.tiles_n : tt % sk.tiles_m) * BM;
+    const int n0 = (whole ? tt % sk.tiles_n : tt / sk.tiles_m) * BN;
     const int prob = pb / g.nbatch, batch = pb % g.nbatch;
     v4d acc[MI][NI];
 #pragma unroll
@@ -1654,7 +1662,7 @@ int launch_gemm_si_balanced(const GemmBatch& g, double* scratch, int ncu, hipStr
 // 61 on 192 x 160), else by the start of the ranges and the partial tiles.
 // Short K on whole tiles, where the tile kernels waited for a tile's first loads
 // and stores: eight 2500 x 2500 x 100 409 -> 257 us, four 5184 x 5184 x 144 639 ->
-// 590 (476 at the matrix cores' rate), 3600 x 3600 x 64 253 -> 172, 8192 x 64 x 64
+// 618 (476 at the matrix cores' rate), 3600 x 3600 x 64 253 -> 172, 8192 x 64 x 64
 // 27 -> 14.
 namespace {
 struct SplitPlan {
