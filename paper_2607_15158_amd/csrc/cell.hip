@@ -121,19 +121,36 @@ int check_gemm(ctm_cell* c, const GemmBatch& g) {
   return 0;
 }
 
+// An SI iteration is Lx + Ly + Lx + Ly column moves in a row, each from the one
+// before, and each takes singular vectors through the inverse of small singular
+// values: it amplifies the last bits of its sums by 1e5 to 1e8, the more the wider
+// the cuts.  Two orders of the same sums, whose errors against exact arithmetic are
+// alike, leave elements of the state of 2 x 2 sites that differ by up to (over the
+// rms): products, QRs and absorptions 4e-8 at k = 70 (120 states), 1e-7 at k = 105
+// (D 5, chi 100); with the Jacobi rotations, whose sums run through all sweeps,
+// 2e-8 at k = 48, 4e-8 at k = 70 (8 states), 3e-7 at k = 105.  A state is then no
+// longer, to the 4e-8 that states are compared by, the one that the other order
+// gives.  So wide cuts keep one order, whatever is faster elsewhere: the rotations
+// from k = 49 on (D 4, chi 64: 22.8 ms an iteration, 18.8 with the one-workgroup
+// kernel), and from k = 97 on the products, the QRs and the absorptions too (D 5,
+// chi 100: 88 ms, 53 without).
+bool ordered_svd(const ctm_cell* c) { return c->k > 48; }
+bool ordered_sums(const ctm_cell* c) { return c->k > 96; }
+
 // Launches a float64 GEMM: the split kernel where K is long (the SI
 // applications, rho, the corner and edge renormalisations), else the tile
 // kernels.
 int run(ctm_cell* c, const GemmBatch& g) {
   if (g.count == 0) return 0;
   CTRY(check_gemm(c, g));
-  CTRY(launch_gemm_f64_any(g, c->sk_part, kSplitMaxCus, c->st));
+  if (ordered_sums(c)) CTRY(launch_gemm_ordered(g, c->sk_part, kSplitMaxCus, c->st));
+  else CTRY(launch_gemm_f64_any(g, c->sk_part, kSplitMaxCus, c->st));
   return 0;
 }
 
 // Whether the sites are absorbed through their single-layer tensors.
 bool single_layer(const ctm_cell* c) {
-  return c->cfg.d > 0 && absorb_corner_fits(c->cfg.D, c->cfg.d);
+  return c->cfg.d > 0 && absorb_corner_fits(c->cfg.D, c->cfg.d) && !ordered_sums(c);
 }
 
 // Stride in A[s, u, l, d, r] of leg n (p, q, o1, o2) of corner i's absorption.
@@ -266,7 +283,8 @@ int qr_blocks(ctm_cell* c, std::vector<double*> w, int n) {
   if (!qr_plan_ok(n, c->k))
     return cfail(c, CTM_E_SHAPE, "no QR leaf partition for a cut block of " + std::to_string(n) +
                                      " x " + std::to_string(c->k));
-  CTRY(launch_qr((int)w.size(), w.data(), n, c->k, c->qr_ws, c->st));
+  if (ordered_sums(c)) CTRY(launch_qr_ordered((int)w.size(), w.data(), n, c->k, c->qr_ws, c->st));
+  else CTRY(launch_qr((int)w.size(), w.data(), n, c->k, c->qr_ws, c->st));
   return 0;
 }
 
@@ -350,7 +368,7 @@ int si_group(ctm_cell* c, int d, const std::vector<const Cut*>& g, bool recycle)
       sp[i] = c->s[g[i]->j];
       vp[i] = c->v[g[i]->j];
     }
-    CTRY(launch_svd(n, rp.data(), up.data(), sp.data(), vp.data(), k, c->svd_ws, c->st));
+    CTRY(launch_svd(n, rp.data(), up.data(), sp.data(), vp.data(), k, c->svd_ws, c->st, ordered_svd(c)));
   }
   // Y^T u (its column signs are the sign rule's), into the spare Y block
   {
@@ -606,11 +624,13 @@ int column_step(ctm_cell* c, int d, int xt, int mode) {
       add(g, e.T[sT4], c->Pl[yu], tmp);
       CTRY(run(c, g));
       // Z2[(b, l), g', d] = Z1[(b, g'), (r, u)] apr[(r, u), (l, d)]; d is the
-      // unit-stride leg, so that every (b, g') is written in runs of D^2
+      // unit-stride leg, so that every (b, g') is written in runs of D^2 (ordered:
+      // [(b, l), d, g'], whose rows (d, g') say where the next product is cut)
       const int i = (sT4 + 1) & 3;
+      const long s_g = ordered_sums(c) ? 1 : Dl, s_d = ordered_sums(c) ? ku : 1;
       GemmBatch g2 = gemm_of(t_in * ku, Dl * Dl, Dl * Dl, (long)Dl * Dl, (long)Dl * Dl, 0);
-      g2.cdiv_m = ku; g2.cs_m1 = (long)Dl * Dl * ku; g2.cs_m0 = Dl;
-      g2.cdiv_n = Dl; g2.cs_n1 = (long)Dl * ku; g2.cs_n0 = 1;
+      g2.cdiv_m = ku; g2.cs_m1 = (long)Dl * Dl * ku; g2.cs_m0 = s_g;
+      g2.cdiv_n = Dl; g2.cs_n1 = (long)Dl * ku; g2.cs_n0 = s_d;
       add(g2, tmp, c->apr[dn.site[0] * 4 + i], tmp2);
       if (single_layer(c)) {
         CTRY(check_gemm(c, g2));
@@ -626,7 +646,7 @@ int column_step(ctm_cell* c, int d, int xt, int mode) {
       }
       // T4'[b', (d, g')] = sum_(b, l) P_r^T[(b, l), b'] Z2[(b, l), (g', d)], as its transpose
       GemmBatch g3 = gemm_of(Dl * ku, ky, t_in * Dl, (long)Dl * ku, ky, 0);
-      g3.cdiv_m = Dl; g3.cs_m1 = 1; g3.cs_m0 = ku;
+      g3.cdiv_m = ordered_sums(c) ? 1 << 30 : Dl; g3.cs_m1 = ordered_sums(c) ? 0 : 1; g3.cs_m0 = s_d == 1 ? ku : 1;
       g3.cdiv_n = 1 << 30; g3.cs_n1 = 0; g3.cs_n0 = (long)Dl * ku;
       add(g3, tmp2, c->Prt[y], nT4, 1);
       CTRY(run(c, g3));
@@ -899,7 +919,8 @@ size_t carve_cell(ctm_cell* c, char* base) {
   c->scal = cv.take(64 + ns);
   c->bad = (int*)cv.take(8);
   c->norm_part = cv.take(8 * kNormBlocks);
-  c->qr_ws = cv.take_bytes(qr_workspace_bytes(8, (int)N, (int)k));
+  c->qr_ws = cv.take_bytes(std::max(qr_workspace_bytes(8, (int)N, (int)k),
+                                    qr_ordered_workspace_bytes(8, (int)N, (int)k)));
   c->svd_ws = cv.take_bytes(svd_workspace_bytes(8, (int)std::max(k, chi)));
   c->sk_part = (double*)cv.take_bytes(gemm_si_scratch_bytes());
   std::sort(c->bufs.begin(), c->bufs.end());

@@ -146,6 +146,9 @@ int launch_gemm_si_balanced(const GemmBatch& g, double* scratch, int ncu, hipStr
 // ranges by estimated cycles; cut tiles where K >= 256 and there is scratch),
 // else as launch_gemm.
 int launch_gemm_f64_any(const GemmBatch& g, double* scratch, int ncu, hipStream_t s);
+// A float64 product whose sums run over ascending k, whole or cut where
+// launch_gemm_ordered says: the same bits whatever the rules above choose.
+int launch_gemm_ordered(const GemmBatch& g, double* scratch, int ncu, hipStream_t s);
 // float32 contractions of the same shape: A float32, B and C float64 (B
 // rounded to float32, float32 accumulation); other shapes fall back to
 // launch_gemm.
@@ -186,13 +189,19 @@ void release_kept_blocks();
 // row-major matrices.  ws must hold qr_workspace_bytes(count, N, k) bytes.
 size_t qr_workspace_bytes(int count, int N, int k);
 // True if N rows split into leaves of k .. 192 rows (every leaf holds a
-// k x k triangle): the shapes launch_qr accepts.
+// k x k triangle): the shapes launch_qr accepts, also where it then runs on
+// leaves twice as tall.
 bool qr_plan_ok(int N, int k);
 int launch_qr(int count, double* const* W, int N, int k, void* ws, hipStream_t s);
+// The same factorisation with its sums in the order of qr_rows.hip.
+size_t qr_ordered_workspace_bytes(int count, int N, int k);
+int launch_qr_ordered(int count, double* const* W, int N, int k, void* ws, hipStream_t s);
 
-// One-sided Jacobi SVD of `count` n x n row-major matrices (see ctm.h).
+// One-sided Jacobi SVD of `count` n x n row-major matrices (see ctm.h).  ordered:
+// through launch_qr_ordered, launch_gemm_ordered and the block-pair kernels at
+// every n.
 size_t svd_workspace_bytes(int count, int n);
 int launch_svd(int count, const double* const* A, double* const* U, double* const* S,
-               double* const* V, int n, void* ws, hipStream_t s);
+               double* const* V, int n, void* ws, hipStream_t s, bool ordered = false);
 
 }  // namespace sictm

@@ -408,14 +408,17 @@ struct StreamK {
   int nwg;        // workgroups (ranges) of the main kernel
   int per, rem;   // units per range; the first `rem` ranges have one more
   int unit;       // slices per unit: 1, or nslices where no tile is cut
+  int total;      // ordered sums: all slices, whose range w begins at w total / nwg; else 0
   double* part;   // 2 * nwg partial BM x BN tiles (row-major)
 };
 
 __device__ __forceinline__ int sk_begin(int w, const StreamK& sk) {
+  if (sk.total) return (int)((long)w * sk.total / sk.nwg);
   return (w * sk.per + min(w, sk.rem)) * sk.unit;
 }
 
 __device__ __forceinline__ int sk_owner(int p, const StreamK& sk) {
+  if (sk.total) return (int)(((long)(p + 1) * sk.nwg - 1) / sk.total);   // the last w with w total / nwg <= p
   p /= sk.unit;
   const int wide = sk.rem * (sk.per + 1);
   return p < wide ? p / (sk.per + 1) : sk.rem + (p - wide) / sk.per;
@@ -444,26 +447,32 @@ typedef double v2du __attribute__((ext_vector_type(2), aligned(8)));
 // 1.065 ms (82%; 1.0 ms with no loads at all).  8 of 1024 x 1024 x 72:
 // 68 -> 39 us; 8 of 1875 x 1875 x 87 (odd rows, which took one-tile kernels
 // before): 328 -> 127 us; 6 of 2500 x 2500 x 105: 210 -> 156 us.
-template <int MI, int NI, int WN>
+//
+// SEQ: the matrix instructions take k in ascending order, four adjacent ones
+// each, so that a sum within a range has the bits of the tile kernels' (ordered
+// products, below).  A is then read 8 bytes at a time: four of 2500 x 105 x 2500
+// take 164 us on 192 x 128, where 256 x 112 with 16-byte loads takes 105.
+template <int MI, int NI, int WN, bool SEQ>
 struct SkTile {
   static constexpr int WM = 8 / WN;
   static constexpr int BM = 16 * MI * WM, BN = 16 * NI * WN;
   static constexpr int BK = 16, NT = 512;
-  static constexpr int LB = BN + 8;   // B rows in LDS: rows 2 apart fall 32 banks apart
+  static constexpr int LB = BN + (SEQ ? 16 : 8);   // B rows in LDS: the rows of two lanes fall 32 banks apart
   static constexpr int NB = BN * BK / 2;              // 16-byte loads of B per slice
   static constexpr int VB = (NB + NT - 1) / NT;
-  // k of matrix instruction t, beyond the lane's 2 (l / 16)
-  static constexpr int kof(int t) { return 8 * (t >> 1) + (t & 1); }
+  // k of matrix instruction t, beyond the lane's first
+  static constexpr int kof(int t) { return SEQ ? 4 * t : 8 * (t >> 1) + (t & 1); }
+  static __device__ __forceinline__ int kfirst(int lk) { return SEQ ? lk : 2 * lk; }
 };
 
 // acc += op(A)[m0 .. m0+BM) x B[.. n0 .. n0+BN) over the K slices [s0, s1) of
 // problem prob (n0 < N, even).
 // ONE: N == 1 (B has no pairs of columns).
-template <int MI, int NI, int WN, bool TRANS, bool ONE>
+template <int MI, int NI, int WN, bool TRANS, bool ONE, bool SEQ>
 __device__ __forceinline__ void sk_segment(const GemmBatch& g, int prob, int batch, int m0, int n0, int s0, int s1,
-                                           double (*Bs)[16][SkTile<MI, NI, WN>::LB],
+                                           double (*Bs)[16][SkTile<MI, NI, WN, SEQ>::LB],
                                            v4d (&acc)[MI][NI]) {
-  using S = SkTile<MI, NI, WN>;
+  using S = SkTile<MI, NI, WN, SEQ>;
   constexpr int BK = S::BK;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
@@ -475,21 +484,21 @@ __device__ __forceinline__ void sk_segment(const GemmBatch& g, int prob, int bat
   const int full = K / BK;   // slices before the partial one
   const int sf = min(s1, full);
 
-  // A: this lane's rows at k = 2 lk of the slice the next load takes
+  // A: this lane's rows at its first k of the slice the next load takes
   const double* pa[MI];
   const long astep = TRANS ? BK * lda : BK;
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     const long m = min(m0 + (wm * MI + i) * 16 + li, M - 1);
-    const long k = s0 * BK + 2 * lk;
+    const long k = s0 * BK + S::kfirst(lk);
     pa[i] = TRANS ? A + k * lda + m : A + m * lda + k;
   }
   auto load_a = [&](double (&ra)[MI][4]) {
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-      if (TRANS) {
+      if (TRANS || SEQ) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) ra[i][t] = pa[i][S::kof(t) * lda];
+        for (int t = 0; t < 4; ++t) ra[i][t] = pa[i][S::kof(t) * (TRANS ? lda : 1)];
       } else {
         const v2du v0 = *(const v2du*)pa[i], v1 = *(const v2du*)(pa[i] + S::kof(2));
         ra[i][0] = v0.x;
@@ -501,7 +510,7 @@ __device__ __forceinline__ void sk_segment(const GemmBatch& g, int prob, int bat
     }
   };
   auto load_a_last = [&](double (&ra)[MI][4]) {   // the partial slice
-    const int k = full * BK + 2 * lk;
+    const int k = full * BK + S::kfirst(lk);
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -559,7 +568,7 @@ __device__ __forceinline__ void sk_segment(const GemmBatch& g, int prob, int bat
   double ra[MI][4], rn[MI][4];
   v2du rb[S::VB];
   auto mul = [&](int buf, int t) {
-    const double* bp = &Bs[buf][S::kof(t) + 2 * lk][wn * NI * 16 + li];
+    const double* bp = &Bs[buf][S::kof(t) + S::kfirst(lk)][wn * NI * 16 + li];
     double b[NI];
 #pragma unroll
     for (int j = 0; j < NI; ++j) b[j] = bp[16 * j];
@@ -626,9 +635,9 @@ __device__ __forceinline__ void sk_segment(const GemmBatch& g, int prob, int bat
   }
 }
 
-template <int MI, int NI, int WN, bool ONE>
+template <int MI, int NI, int WN, bool ONE, bool SEQ>
 __global__ __launch_bounds__(512, 2) void gemm_streamk_f64(GemmBatch g, StreamK sk) {
-  using S = SkTile<MI, NI, WN>;
+  using S = SkTile<MI, NI, WN, SEQ>;
   constexpr int BM = S::BM, BN = S::BN;
   __shared__ __attribute__((aligned(16))) double Bs[2][16][S::LB];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -662,9 +671,9 @@ __global__ __launch_bounds__(512, 2) void gemm_streamk_f64(GemmBatch g, StreamK 
 #pragma unroll
       for (int j = 0; j < NI; ++j) acc[i][j] = v4d{0, 0, 0, 0};
     if (g.transA[prob])
-      sk_segment<MI, NI, WN, true, ONE>(g, prob, batch, m0, n0, s0, s1, Bs, acc);
+      sk_segment<MI, NI, WN, true, ONE, SEQ>(g, prob, batch, m0, n0, s0, s1, Bs, acc);
     else
-      sk_segment<MI, NI, WN, false, ONE>(g, prob, batch, m0, n0, s0, s1, Bs, acc);
+      sk_segment<MI, NI, WN, false, ONE, SEQ>(g, prob, batch, m0, n0, s0, s1, Bs, acc);
     const int mw = wm * MI * 16 + (lane >> 4), nw = wn * NI * 16 + (lane & 15);
     if (s0 == 0 && s1 == sk.nslices) {
       // the whole tile: written here
@@ -1602,11 +1611,11 @@ bool gemm_si_balanced_applies(const GemmBatch& g, const void* scratch, int ncu) 
 }
 
 // One of the tile shapes on the ranges of sk (nwg, per, rem and unit set).
-template <int MI, int NI, int WN, bool ONE = false>
+template <int MI, int NI, int WN, bool ONE = false, bool SEQ = false>
 static int launch_streamk_f64(const GemmBatch& g, const StreamK& sk, hipStream_t s) {
-  using S = SkTile<MI, NI, WN>;
+  using S = SkTile<MI, NI, WN, SEQ>;
   static_assert((size_t)S::BM * S::BN <= 192 * 160, "scratch slots");
-  gemm_streamk_f64<MI, NI, WN, ONE><<<sk.nwg, S::NT, 0, s>>>(g, sk);
+  gemm_streamk_f64<MI, NI, WN, ONE, SEQ><<<sk.nwg, S::NT, 0, s>>>(g, sk);
   CTM_HIP_TRY(hipGetLastError());
   if (sk.unit > 1) return 0;   // no tile is cut
   gemm_streamk_fixup<S::BM, S::BN>
@@ -1735,6 +1744,47 @@ int launch_gemm_f64_any(const GemmBatch& g, double* scratch, int ncu, hipStream_
   return launch_gemm(g, DT::F64, DT::F64, DT::F64, s);
 }
 
+// Ordered products: thin ones with long K on tiles of 192 rows in ranges that
+// begin at w total / nwg, where rows and bases are aligned for 16-byte loads, all
+// others whole, every sum over ascending k.  An element's bits then depend on this
+// rule alone, not on how the products are tiled elsewhere.
+int launch_gemm_ordered(const GemmBatch& g, double* scratch, int ncu, hipStream_t s) {
+  if (g.M <= 0 || g.N <= 0 || g.count <= 0 || g.nbatch <= 0) return 0;
+  StreamK sk{};
+  sk.nslices = ceil_div(g.K, 16);
+  sk.tiles_m = ceil_div(g.M, 192);
+  sk.tiles_n = 1;
+  sk.part = scratch;
+  sk.unit = 1;
+  auto run = [&](int cols) {
+    return cols == 160 ? launch_streamk_f64<3, 5, 2, false, true>(g, sk, s)
+                       : launch_streamk_f64<3, 4, 2, false, true>(g, sk, s);
+  };
+  bool cut = scratch && !((uintptr_t)scratch & 15) && ncu >= 1 && ncu <= kSplitMaxCus && g.nbatch == 1 &&
+             g.N > 1 && g.N <= 160 && sk.nslices >= 16 && !(g.lda & 1);
+  for (int i = 0; i < g.count; ++i)
+    cut = cut && !((uintptr_t)g.A[i] & 15) && !((uintptr_t)g.B[i] & ((g.ldb & 1) ? 7 : 15));
+  const long tiles = (long)sk.tiles_m * g.count;
+  if (cut && tiles * sk.nslices >= 8 && tiles * sk.nslices <= (1L << 30)) {
+    sk.total = (int)(tiles * sk.nslices);
+    sk.nwg = sk_ranges(sk.total, ncu);
+    return run(g.N > 128 ? 160 : 128);
+  }
+  // whole tiles where they fill the chip (eight 2500 x 2500 x 100 313 us, 423 on the
+  // tile kernels), else the tile kernels
+  const int cols = g.N > 128 && g.N <= 160 ? 160 : 128;
+  sk.tiles_n = ceil_div(g.N, cols);
+  const long all = (long)sk.tiles_m * sk.tiles_n * g.count * g.nbatch;
+  if (g.K > 16 && g.N > 64 && all >= 128 && all * sk.nslices <= (1L << 30)) {
+    sk.nwg = (int)std::min<long>(all, kSplitMaxCus);
+    sk.per = (int)(all / sk.nwg);
+    sk.rem = (int)(all % sk.nwg);
+    sk.unit = sk.nslices;
+    return run(cols);
+  }
+  return launch_k4<double, double, double, double>(g, s);
+}
+
 bool gemm_si_f32_balanced_applies(const GemmBatch& g, const void* scratch, int ncu) {
   if (!scratch || ((uintptr_t)scratch & 15) || g.M <= 0 || g.N <= 0 || g.count <= 0 ||
       g.nbatch != 1 || g.N > skf32::BN)
@@ -1753,7 +1803,7 @@ int launch_gemm_si_f32_balanced(const GemmBatch& g, double* scratch, int ncu, hi
   if (g.M <= 0 || g.N <= 0 || g.count <= 0 || g.nbatch <= 0) return 0;
   if (!gemm_si_f32_balanced_applies(g, scratch, ncu)) return launch_gemm_si_f32(g, s);
   const int tm = ceil_div(g.M, skf32::BM);
-  StreamK sk;
+  StreamK sk{};
   sk.nslices = ceil_div(g.K, skf32::BK);
   sk.tiles_m = tm;
   sk.tiles_n = 1;

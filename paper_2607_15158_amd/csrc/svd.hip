@@ -14,16 +14,15 @@
 //
 // Up to n = 96 (128 for the values alone) one workgroup holds the columns of
 // a matrix in LDS for all sweeps (svd_small).  Above that, block-pair parallel
-// ordering: the columns are cut into an even number of blocks of equal width,
-// at most kBlk; an outer sweep pairs the blocks in a round-robin tournament,
-// one workgroup per block pair and matrix, the rounds separated by grid
-// barriers of one cooperative launch, or by launches inside a stream capture.
-// The workgroup loads the columns of both blocks into LDS and rotates the
-// pairs across the two blocks in as many steps of disjoint pairs as a block
-// has columns (in the sweep's first round, where every block is visited once,
-// the pairs within each block first, by halving), so that every column pair
-// meets once per sweep; 16 lanes per pair (rows spread over the lanes, dot
-// products reduced by DPP row sums); the rotations of the visit are
+// ordering: the columns are cut into blocks of kBlk; an outer sweep pairs the
+// blocks in a round-robin tournament, one workgroup per block pair and matrix,
+// the rounds separated by grid barriers of one cooperative launch, or by
+// launches inside a stream capture.  The workgroup loads the columns of both
+// blocks into LDS and rotates the pairs across the two blocks in kBlk steps of
+// kBlk disjoint pairs (in the sweep's first round, where every block is visited
+// once, the pairs within each block first, in kBlk - 1 more steps), so that
+// every column pair meets once per sweep; 16 lanes per pair (rows spread over
+// the lanes, dot products reduced by DPP row sums); the rotations of the visit are
 // accumulated in a 2 kBlk x 2 kBlk matrix W and applied to the right vectors
 // once at the end (V_cols <- V_cols W).  A per-matrix flag records whether a
 // sweep rotated anything, and the sweeps end after one without rotations.
@@ -57,7 +56,7 @@ struct SvdArgs {
   double* V[kMaxProb];         // ... and right vectors (V')
   double* work;       // [count][2][n][n] column-major working columns
   int* flags;         // [count][kMaxSweeps] "a rotation happened in sweep s"
-  int n, nblk, bs, want_v;     // bs: columns of a block (<= kBlk)
+  int n, nblk, want_v;
   // preconditioning
   const double* Ain[kMaxProb]; // the caller's matrices
   double* Wp[kMaxProb];        // A P, then Q
@@ -370,11 +369,14 @@ void launch_small_svd(const SvdArgs& a, int count, hipStream_t s) {
 // nblk-1-bp).  The 2 kBlk columns of U live in LDS; the rotations of the
 // visit are accumulated in a 2 kBlk x 2 kBlk matrix W (also in LDS) and the
 // right vectors are updated once at the end, V_cols <- V_cols W.  RPL is the
-// number of rows per lane (n <= 16 RPL).  Bound by the latency of a step, like
-// svd_small, and by the grid barriers.  A column of the first block stays in
-// registers, norms are tracked, and blocks are no wider than n needs: 4 random
-// matrices with vectors, n = 100: 2132 -> 1588 us, 144: 3237 -> 2562, 160:
-// 3328 -> 2675.
+// number of rows per lane (n <= 16 RPL).  Norms and products are summed anew in
+// every step, in the order of the blocks: unit cells amplify the last bits of
+// these vectors (cell.hip), so the order and the sums are part of what this
+// computes (the fma calls fix its rounding).  Bound by the latency of a step, like
+// svd_small, and by the grid barriers; across blocks a column of the first stays in
+// registers.  4 random matrices with vectors, n = 100: 2200 us with both columns
+// through LDS, 1715 so; 144: 3238, 2688; 160: 3329, 2789 (norms tracked from step to
+// step and narrower blocks, a different order: 1570, 2560, 2691).
 template <int RPL>
 struct RoundLds {
   static constexpr int kC = 2 * kBlk;
@@ -382,7 +384,6 @@ struct RoundLds {
   double Ul[kC][LD];
   double Vl[kC][LD];
   double Wl[kC][kC + 1];
-  double nrm[kC];
   int rot;
 };
 
@@ -394,16 +395,13 @@ __device__ __forceinline__ void block_round(const SvdArgs& a, int sweep, int rou
   auto& Vl = sh.Vl;
   auto& Wl = sh.Wl;
   int& rot = sh.rot;
-  const int n = a.n, nblk = a.nblk, bs = a.bs;
+  const int n = a.n, nblk = a.nblk;
   const int b0 = tour(bp, round, nblk), b1 = tour(nblk - 1 - bp, round, nblk);
   const int tid = threadIdx.x;
   double* Uc = a.work + (size_t)mat * 2 * n * n;
   double* Vc = Uc + (size_t)n * n;
-  // local column j -> global column: j < kBlk from b0, else from b1 (n for
-  // the places a block of bs columns leaves empty)
-  auto gcol = [&](int j) {
-    return j % kBlk < bs ? min((j < kBlk ? b0 : b1) * bs + j % kBlk, n) : n;
-  };
+  // local column j -> global column: j < kBlk from b0, else from b1
+  auto gcol = [&](int j) { return (j < kBlk ? b0 : b1) * kBlk + (j % kBlk); };
   // the columns of U (and of V) into LDS, one column per wave at a time, rows
   // lane + 64 t: coalesced, with no index division; four columns per wave in
   // flight
@@ -443,91 +441,116 @@ __device__ __forceinline__ void block_round(const SvdArgs& a, int sweep, int rou
   if (tid == 0) rot = 0;
   __syncthreads();
   const int grp = tid / kLanesPerPair, li = tid % kLanesPerPair;   // 16 pair groups
-  const SvdScale f = svd_scale(a.fro2[mat], n);
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int j = grp + kBlk * u;
-    double x = 0.0;
-#pragma unroll
-    for (int t = 0; t < RPL; ++t) x = fma(Ul[j][li + 16 * t], Ul[j][li + 16 * t], x);
-    x = gsum16(x) * f.scale;
-    if (li == 0) sh.nrm[j] = x;
-  }
-  __syncthreads();
+  const double tol = 1e-15 * sqrt((double)n);
+  // columns below 1e-15 of the matrix norm are numerically zero: rotating
+  // them against the others cannot converge in the relative sense and does
+  // not change the result above roundoff; they are completed at the end
+  const double negl = 1e-30 * a.fro2[mat];
   int my_rot = 0;
-  // h steps that pair column p of this group with the columns q0 + (idx + r)
-  // mod h; p stays in the registers of its lanes
-  auto steps = [&](int p, int q0, int idx, int h, bool in) {
-    double up[RPL], wp[2] = {0.0, 0.0}, al = 0.0;
-    in = in && gcol(p) < n;
-    if (in) {
-      al = sh.nrm[p];
+  // The rotation of columns up (of the first index) and uq: its cosine and sine,
+  // or false.
+  auto rotation = [&](const double (&up)[RPL], const double (&uq)[RPL], double& c, double& s) {
+    double al = fma(up[0], up[0], up[1] * up[1]), be = fma(uq[0], uq[0], uq[1] * uq[1]);
+    double ga = fma(up[1], uq[1], up[0] * uq[0]);
 #pragma unroll
-      for (int t = 0; t < RPL; ++t) up[t] = Ul[p][li + 16 * t];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) wp[t] = Wl[li + 16 * t][p];
+    for (int t = 2; t < RPL; ++t) {   // rows n .. 16 RPL - 1 are zero: no guard
+      al = fma(up[t], up[t], al);
+      be = fma(uq[t], uq[t], be);
+      ga = fma(up[t], uq[t], ga);
     }
-    for (int r = 0; r < h; ++r) {
-      const int q = q0 + (idx + r >= h ? idx + r - h : idx + r);
-      if (in && gcol(q) < n) {
-        double uq[RPL], wq[2];
-        double ga = 0.0, g1 = 0.0;
+    al = gsum16(al);
+    be = gsum16(be);
+    ga = gsum16(ga);
+    const double thr = tol * sqrt(al) * sqrt(be);
+    if (!(ga != 0.0 && fabs(ga) > thr && al > negl && be > negl)) return false;
+    // tan of the rotation angle, the smaller root of t^2 + 2 zeta t = 1
+    const double zeta = (be - al) * fast_rcp(2.0 * ga);
+    const double z2 = fma(zeta, zeta, 1.0);
+    const double t = (zeta >= 0.0 ? 1.0 : -1.0) * fast_rcp(fma(z2, fast_rsqrt(z2), fabs(zeta)));
+    c = fast_rsqrt(fma(t, t, 1.0));
+    s = c * t;
+    // convergence counts only rotations clearly above roundoff: a pair
+    // left at |gamma| ~ tol sqrt(alpha beta) keeps being rotated but does
+    // not prevent the sweep loop from stopping
+    my_rot |= fabs(ga) > 16.0 * thr;
+    return true;
+  };
+  // the sweep's first round (every block in exactly one pair) also pairs the
+  // columns within each block: kBlk - 1 steps of a round-robin per block,
+  // kBlk / 2 pairs of each block per step
+  for (int r = 0; r < (round == 0 ? kBlk - 1 : 0); ++r) {
+    const int blk = grp / (kBlk / 2), k = grp % (kBlk / 2);
+    const int ca = tour(k, r, kBlk), cb = tour(kBlk - 1 - k, r, kBlk);
+    const int p = blk * kBlk + min(ca, cb), q = blk * kBlk + max(ca, cb);
+    if (gcol(p) < n && gcol(q) < n) {
+      double up[RPL], uq[RPL], c, s;
 #pragma unroll
-        for (int t = 0; t < RPL; ++t) uq[t] = Ul[q][li + 16 * t];   // rows from n on are zero
+      for (int t = 0; t < RPL; ++t) {
+        up[t] = Ul[p][li + 16 * t];
+        uq[t] = Ul[q][li + 16 * t];
+      }
+      if (rotation(up, uq, c, s)) {
+#pragma unroll
+        for (int t = 0; t < RPL; ++t) {
+          Ul[p][li + 16 * t] = fma(c, up[t], -(s * uq[t]));
+          Ul[q][li + 16 * t] = fma(c, uq[t], s * up[t]);
+        }
+        if (a.want_v) {
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            const double wp = Wl[li + 16 * t][p], wq = Wl[li + 16 * t][q];
+            Wl[li + 16 * t][p] = fma(c, wp, -(s * wq));
+            Wl[li + 16 * t][q] = fma(s, wp, c * wq);
+          }
+        }
+      }
+    }
+    __syncthreads();
+  }
+  // then kBlk steps pair column i of the first block, which stays in the
+  // registers of its lanes, with column (i + step) mod kBlk of the second, so
+  // that a sweep meets every column pair exactly once
+  {
+    const int p = grp;
+    const bool in = gcol(p) < n;
+    double up[RPL], wp[2];
+#pragma unroll
+    for (int t = 0; t < RPL; ++t) up[t] = Ul[p][li + 16 * t];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) wp[t] = Wl[li + 16 * t][p];
+    for (int r = 0; r < kBlk; ++r) {
+      const int q = kBlk + (grp + r) % kBlk;
+      if (in && gcol(q) < n) {
+        double uq[RPL], wq[2], c, s;
+#pragma unroll
+        for (int t = 0; t < RPL; ++t) uq[t] = Ul[q][li + 16 * t];
 #pragma unroll
         for (int t = 0; t < 2; ++t) wq[t] = Wl[li + 16 * t][q];
-        const double be = sh.nrm[q];
-#pragma unroll
-        for (int t = 0; t < RPL; t += 2) {
-          ga = fma(up[t], uq[t], ga);
-          if (t + 1 < RPL) g1 = fma(up[t + 1], uq[t + 1], g1);
-        }
-        ga = gsum16(ga + g1) * f.scale;
-        double t_, c, s;
-        bool counts;
-        if (plane_rotation(al, be, ga, f, t_, c, s, counts)) {
-          my_rot |= counts;
+        if (rotation(up, uq, c, s)) {
 #pragma unroll
           for (int t = 0; t < RPL; ++t) {
             const double x = up[t], y = uq[t];
-            up[t] = c * x - s * y;
-            Ul[q][li + 16 * t] = s * x + c * y;
+            up[t] = fma(c, x, -(s * y));
+            Ul[q][li + 16 * t] = fma(c, y, s * x);
           }
           if (a.want_v) {
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
               const double x = wp[t], y = wq[t];
-              wp[t] = c * x - s * y;
-              Wl[li + 16 * t][q] = s * x + c * y;
+              wp[t] = fma(c, x, -(s * y));
+              Wl[li + 16 * t][q] = fma(s, x, c * y);
             }
           }
-          al = fma(-t_, ga, al);
-          if (li == 0) sh.nrm[q] = fma(t_, ga, be);
         }
       }
       __syncthreads();
     }
-    if (in) {
-      if (li == 0) sh.nrm[p] = al;
 #pragma unroll
-      for (int t = 0; t < RPL; ++t) Ul[p][li + 16 * t] = up[t];
+    for (int t = 0; t < RPL; ++t) Ul[p][li + 16 * t] = up[t];
 #pragma unroll
-      for (int t = 0; t < 2; ++t) Wl[li + 16 * t][p] = wp[t];
-    }
+    for (int t = 0; t < 2; ++t) Wl[li + 16 * t][p] = wp[t];
     __syncthreads();
-  };
-  // the sweep's first round (every block in exactly one pair) also pairs the
-  // columns within each block, by halving (8 groups per block); then column i
-  // of the first block meets every column of the second, so that a sweep
-  // meets every column pair exactly once
-  if (round == 0) {
-    for (int h = kBlk / 2; h >= 1; h >>= 1) {
-      const int g = grp & 7, set = g / h, idx = g % h;
-      const int p0 = (grp >> 3) * kBlk + set * 2 * h;
-      steps(p0 + idx, p0 + h, idx, h, true);
-    }
   }
-  steps(grp, kBlk, grp, bs, grp < bs);
   if (li == 0 && my_rot) atomicOr(&rot, 1);
   for (int j = wv; j < kC; j += 4) {
     const int g = gcol(j);
@@ -843,7 +866,9 @@ int launch_block_svd(const SvdArgs& a, int count, hipStream_t s) {
   SvdArgs arg = a;
   int cnt = count;
   void* args[] = {&arg, &cnt};
-  const void* fn = rpl <= 8    ? (const void*)svd_sweeps<8>
+  const void* fn = rpl <= 4    ? (const void*)svd_sweeps<4>
+                   : rpl <= 6  ? (const void*)svd_sweeps<6>
+                   : rpl <= 8  ? (const void*)svd_sweeps<8>
                    : rpl <= 10 ? (const void*)svd_sweeps<10>
                                : (const void*)svd_sweeps<12>;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -854,7 +879,11 @@ int launch_block_svd(const SvdArgs& a, int count, hipStream_t s) {
   (void)hipGetLastError();
   for (int sweep = 0; sweep < kMaxSweeps; ++sweep)
     for (int round = 0; round < nblk - 1; ++round) {
-      if (rpl <= 8)
+      if (rpl <= 4)
+        svd_block_round<4><<<grid, 256, 0, s>>>(a, sweep, round);
+      else if (rpl <= 6)
+        svd_block_round<6><<<grid, 256, 0, s>>>(a, sweep, round);
+      else if (rpl <= 8)
         svd_block_round<8><<<grid, 256, 0, s>>>(a, sweep, round);
       else if (rpl <= 10)
         svd_block_round<10><<<grid, 256, 0, s>>>(a, sweep, round);
@@ -871,11 +900,11 @@ size_t svd_workspace_bytes(int count, int n) {
   const size_t nn = (size_t)n * n;
   return (size_t)count * (2 * nn + 5 * nn) * sizeof(double) +
          (size_t)count * (kMaxSweeps + n) * sizeof(int) + (size_t)count * sizeof(double) +
-         qr_workspace_bytes(count, n, n) + 4096;
+         std::max(qr_workspace_bytes(count, n, n), qr_ordered_workspace_bytes(count, n, n)) + 4096;
 }
 
 int launch_svd(int count, const double* const* A, double* const* U, double* const* S,
-               double* const* V, int n, void* ws, hipStream_t s) {
+               double* const* V, int n, void* ws, hipStream_t s, bool ordered) {
   if (count <= 0 || n <= 0) return 0;
   if (count > kMaxProb || n > kSvdMaxN) {
     set_thread_error("launch_svd: n <= 192 and at most 8 matrices per launch");
@@ -900,7 +929,6 @@ int launch_svd(int count, const double* const* A, double* const* U, double* cons
   nblk += nblk & 1;
   if (nblk < 2) nblk = 2;
   a.nblk = nblk;
-  a.bs = (n + nblk - 1) / nblk;
   const bool want_u = U != nullptr, want_vout = V != nullptr;
   a.want_v = want_u ? 1 : 0;                       // V' is needed for u = Q V'
   double* qptr[kMaxProb];
@@ -919,8 +947,11 @@ int launch_svd(int count, const double* const* A, double* const* U, double* cons
   CTM_HIP_TRY(hipGetLastError());
   svd_prep_copy<<<dim3(std::max(1, std::min(64, n * n / 256)), count), 256, 0, s>>>(a);
   CTM_HIP_TRY(hipGetLastError());
-  int r = launch_qr(count, qptr, n, n, qws, s);
+  int r = ordered ? launch_qr_ordered(count, qptr, n, n, qws, s) : launch_qr(count, qptr, n, n, qws, s);
   if (r) return r;
+  auto product = [&](const GemmBatch& x) {
+    return ordered ? launch_gemm_ordered(x, nullptr, 0, s) : launch_gemm(x, DT::F64, DT::F64, DT::F64, s);
+  };
   // R^T = (A P)^T Q
   GemmBatch g{};
   g.count = count;
@@ -935,9 +966,9 @@ int launch_svd(int count, const double* const* A, double* const* U, double* cons
     g.B[i] = a.Wp[i];
     g.C[i] = rt + i * nn;
   }
-  r = launch_gemm(g, DT::F64, DT::F64, DT::F64, s);
+  r = product(g);
   if (r) return r;
-  if (small_svd_fits(n, want_u)) {
+  if (!ordered && small_svd_fits(n, want_u)) {
     if (want_u) launch_small_svd<true>(a, count, s);
     else launch_small_svd<false>(a, count, s);
     CTM_HIP_TRY(hipGetLastError());
@@ -956,7 +987,7 @@ int launch_svd(int count, const double* const* A, double* const* U, double* cons
       g.B[i] = vp + i * nn;
       g.C[i] = U[i];
     }
-    r = launch_gemm(g, DT::F64, DT::F64, DT::F64, s);
+    r = product(g);
     if (r) return r;
   }
   if (want_vout) {   // v = P Ut
