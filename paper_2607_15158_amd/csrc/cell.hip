@@ -126,16 +126,17 @@ int check_gemm(ctm_cell* c, const GemmBatch& g) {
 // values: it amplifies the last bits of its sums by 1e5 to 1e8, the more the wider
 // the cuts.  Two orders of the same sums, whose errors against exact arithmetic are
 // alike, leave elements of the state of 2 x 2 sites that differ by up to (over the
-// rms): products, QRs and absorptions 4e-8 at k = 70 (120 states), 1e-7 at k = 105
-// (D 5, chi 100); with the Jacobi rotations, whose sums run through all sweeps,
-// 2e-8 at k = 48, 4e-8 at k = 70 (8 states), 3e-7 at k = 105.  A state is then no
-// longer, to the 4e-8 that states are compared by, the one that the other order
-// gives.  So wide cuts keep one order, whatever is faster elsewhere: the rotations
-// from k = 49 on (D 4, chi 64: 22.8 ms an iteration, 18.8 with the one-workgroup
-// kernel), and from k = 97 on the products, the QRs and the absorptions too (D 5,
-// chi 100: 88 ms, 53 without).
-bool ordered_svd(const ctm_cell* c) { return c->k > 48; }
-bool ordered_sums(const ctm_cell* c) { return c->k > 96; }
+// rms): products, QRs and absorptions 2e-8 at k = 48 (180 states), 4e-8 at k = 70
+// (120), 1e-7 at k = 105 (12 of D 5, chi 100); the Jacobi rotations too, whose sums
+// run through all sweeps, 7e-9 up to k = 35, 2e-8 at k = 48, 4e-8 at k = 70 (of 8
+// states), 3e-7 at k = 105.  A state is then no longer, to the 4e-8 that states are
+// compared by, the one that the other order gives.  So wide cuts keep one order,
+// whatever is faster elsewhere: the rotations from kOrderedSvd = 33 on (k = 48: 12.2
+// ms an iteration, 9.5 with the one-workgroup kernel; D 4, chi 64: 22.8 and 18.8),
+// and from kOrderedSums = 97 on the products, the QRs and the absorptions (D 5, chi
+// 100: 87 ms, 52 without).
+bool ordered_svd(const ctm_cell* c) { return c->k >= kOrderedSvd; }
+bool ordered_sums(const ctm_cell* c) { return c->k >= kOrderedSums; }
 
 // Launches a float64 GEMM: the split kernel where K is long (the SI
 // applications, rho, the corner and edge renormalisations), else the tile

@@ -203,5 +203,8 @@ int launch_qr_ordered(int count, double* const* W, int N, int k, void* ws, hipSt
 size_t svd_workspace_bytes(int count, int n);
 int launch_svd(int count, const double* const* A, double* const* U, double* const* S,
                double* const* V, int n, void* ws, hipStream_t s, bool ordered = false);
+// Cut widths k from which unit cells take the ordered rotations, and the ordered
+// products, QRs and absorptions too (the reasons: cell.hip).
+constexpr int kOrderedSvd = 33, kOrderedSums = 97;
 
 }  // namespace sictm

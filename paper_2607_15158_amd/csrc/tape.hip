@@ -888,7 +888,8 @@ int Tape::svdproj(int count, const double* const* rho, const double* const* Yt, 
     svd_need_ = std::max(svd_need_, ws);
   } else {
     if (ws > svd_need_) return fail(CTM_E_NOMEM, "adjoint SVD workspace exceeds the reservation");
-    int rc = launch_svd(count, rho, u.data(), s.data(), v.data(), k, svd_ws_, st_);
+    // the rotations of the cell's own iterations, whose state this reproduces
+    int rc = launch_svd(count, rho, u.data(), s.data(), v.data(), k, svd_ws_, st_, k >= kOrderedSvd);
     if (rc) return fail(rc == 1 ? CTM_E_ARG : rc, thread_error());
     // the sign source Yt u (a constant: not recorded)
     GemmBatch gy{};
