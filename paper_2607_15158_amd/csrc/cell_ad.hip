@@ -619,7 +619,7 @@ int impl_get_state_device(ctm_cell* cell, double* dev, size_t n) {
   if (!cur && !c->blocks_set) return afail(c, CTM_E_STATE, "no blocks to export");
   const size_t cc = (size_t)c->chi * c->chi * 8, tt = (size_t)c->chi * c->Dl * c->chi * 8,
                nk = (size_t)c->Nf * c->k * 8;
-  if (elem_device_range(dev, n * 8)) {   // all tensors by one kernel, else a copy each
+  if (elem_device_range(dev, n * 8, c->mem)) {   // all tensors by one kernel, else a copy each
     PackList pack(c->st);
     for (int s = 0; s < c->ns; ++s)
       for (int i = 0; i < 4; ++i) {
@@ -657,7 +657,7 @@ int impl_set_state_device(ctm_cell* cell, const double* dev, size_t n) {
   if (n != (size_t)L.total()) return afail(c, CTM_E_SHAPE, "wrong state size");
   const size_t cc = (size_t)c->chi * c->chi * 8, tt = (size_t)c->chi * c->Dl * c->chi * 8,
                nk = (size_t)c->Nf * c->k * 8;
-  const bool packed = elem_device_range(dev, n * 8);   // by one kernel, else a copy each
+  const bool packed = elem_device_range(dev, n * 8, c->mem);   // by one kernel, else a copy each
   PackList pack(c->st);
   auto load = [&](double* dst, const double* src, size_t bytes) -> int {
     if (packed)

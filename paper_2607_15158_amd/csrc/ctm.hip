@@ -2447,7 +2447,7 @@ int copy_state(ctm_ctx* c, double* dst, size_t n, bool device) {
   const size_t chi = c->chi, Dl = c->Dl, N = c->N, k = c->k;
   const size_t x = c->chi_env;
   const hipMemcpyKind kind = device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-  if (device && elem_device_range(dst, need * sizeof(double))) {
+  if (device && elem_device_range(dst, need * sizeof(double), c->C[0][0])) {
     // all tensors, and the zeros behind those of a growing environment, in one
     // launch; the counters go by a copy of their own
     const bool blocks = c->iso_pending || c->si_ready;

@@ -99,9 +99,11 @@ struct PackList {
     return rc;
   }
 };
-// Whether [p, p + bytes) is memory of the current device inside one allocation
-// (what a copy checks by itself).
-bool elem_device_range(const void* p, size_t bytes);
+// Whether [p, p + bytes) is memory inside one allocation (what a copy checks by
+// itself) of the current device, which is also the device of `own`, a buffer of the
+// context whose stream the kernel goes to: a kernel on that stream can then reach
+// p, where a copy reaches other devices too.
+bool elem_device_range(const void* p, size_t bytes, const void* own);
 int elem_permute4(const double* src, void* dst, DT t, int n, long s0, long s1, long s2, long s3,
                   hipStream_t s);
 int elem_init_env(const double* a, const double* e, int n, double* const* C, double* const* T,

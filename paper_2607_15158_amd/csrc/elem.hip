@@ -738,13 +738,14 @@ int elem_pack(const PackSeg* segs, int count, hipStream_t s) {
   return 0;
 }
 
-bool elem_device_range(const void* p, size_t bytes) {
-  hipPointerAttribute_t at{};
+bool elem_device_range(const void* p, size_t bytes, const void* own) {
+  hipPointerAttribute_t at{}, to{};
   int dev = -1;
   hipDeviceptr_t base = nullptr;
   size_t size = 0;
   if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice ||
-      hipGetDevice(&dev) != hipSuccess || at.device != dev ||
+      hipPointerGetAttributes(&to, own) != hipSuccess || to.type != hipMemoryTypeDevice ||
+      hipGetDevice(&dev) != hipSuccess || at.device != dev || to.device != dev ||
       hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
     (void)hipGetLastError();
     return false;
