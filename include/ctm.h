@@ -491,6 +491,12 @@ ctm_status ctm_gemm_f64_split(int count, const double* const* A, const double* c
  * step 1).  Zero columns get tau = 0 and no division by zero. */
 ctm_status ctm_qr_f64(int count, double* const* W, int N, int k, void* stream);
 
+/* ctm_qr_f64 and ctm_svd_f64 keep the workspaces of their last calls on a
+ * device, at most four of together 256 MiB.  They are given back when a context
+ * or a unit cell of that device is destroyed, when an allocation of one
+ * fails there, and by this call (those of the current device). */
+void ctm_release_workspaces(void);
+
 /* ctm_qr_f64 without any device allocation, for callers that cannot
  * allocate (code under HIP graph capture, serving loops, harnesses that
  * forbid hipMalloc).  The same kernels and result as ctm_qr_f64 (bit for

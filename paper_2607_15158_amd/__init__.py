@@ -126,6 +126,7 @@ _sigs = {
                                           _vp, ctypes.c_size_t, ctypes.c_int,
                                           ctypes.POINTER(ctypes.c_int), _vp]),
     "ctm_qr_f64": (ctypes.c_int, [ctypes.c_int, ctypes.POINTER(_vp), ctypes.c_int, ctypes.c_int, _vp]),
+    "ctm_release_workspaces": (None, []),
     "ctm_qr_f64_noalloc": (ctypes.c_int, [ctypes.c_int, ctypes.POINTER(_vp), ctypes.c_int,
                                           ctypes.c_int, _vp]),
     "ctm_qr_f64_noalloc_max_bytes": (ctypes.c_size_t, []),
@@ -790,6 +791,12 @@ def qr_f64_noalloc(W: Sequence, stream=None):
     no synchronisation)."""
     N, k = W[0].shape
     _check(_lib.ctm_qr_f64_noalloc(len(W), _ptr_array(W), N, k, _stream(stream)))
+
+
+def release_workspaces():
+    """Gives back the workspaces that qr_f64 and svd_f64 keep on the current
+    device (at most 256 MiB)."""
+    _lib.ctm_release_workspaces()
 
 
 def svd_f64(rho: Sequence, u: Sequence, s: Sequence, v: Sequence, stream=None):

@@ -36,6 +36,7 @@ struct ctm_cell {
   ctm_cell_config cfg;
   int Lx = 0, Ly = 0, ns = 0, Dl = 0, chi = 0, k = 0, Nf = 0, Lmax = 0;
   hipStream_t st = nullptr;
+  int dev = -1;   // the device that was current in ctm_cell_create
   rocblas_handle rb = nullptr;
   char* mem = nullptr;
   std::vector<std::pair<uintptr_t, uintptr_t>> bufs;

@@ -1005,6 +1005,7 @@ ctm_status ctm_cell_create(ctm_cell** out, const ctm_cell_config* cfg, const dou
     return (ctm_status)code;
   };
   const size_t bytes = carve_cell(c, nullptr);
+  c->dev = current_device();
   if (hipStreamCreateWithFlags(&c->st, hipStreamNonBlocking) != hipSuccess)
     return bail(cfail(nullptr, CTM_E_DEVICE, "hipStreamCreate failed"));
   if (device_malloc((void**)&c->mem, bytes) != hipSuccess)
@@ -1070,8 +1071,9 @@ void ctm_cell_destroy(ctm_cell* cell) {
   if (cell->rb) rocblas_destroy_handle(cell->rb);
   if (cell->mem) (void)hipFree(cell->mem);
   if (cell->st) (void)hipStreamDestroy(cell->st);
+  const int dev = cell->dev;
   delete cell;
-  release_kept_blocks();
+  release_kept_blocks(dev);
 }
 
 ctm_status ctm_cell_set_blocks(ctm_cell* cell, const double* X_dev, const double* Yt_dev) {

@@ -182,8 +182,9 @@ int launch_gemm_grouped(const GroupItem* dev_items, int n, long total, int kind,
 // hipMalloc on the current device; on failure the blocks that the standalone
 // factorisations keep there are freed and it is tried again.
 hipError_t device_malloc(void** p, size_t bytes);
-// Frees the kept blocks of the current device.
-void release_kept_blocks();
+// Frees the kept blocks of a device.
+int current_device();   // -1 where there is none
+void release_kept_blocks(int dev);
 
 // Householder QR (in place, Q returned with R_ii >= 0) of `count` N x k
 // row-major matrices.  ws must hold qr_workspace_bytes(count, N, k) bytes.

@@ -151,6 +151,7 @@ struct ctm_ctx {
   void* xi_qr = nullptr;
   int xi_m = 0;
   int sk_cus = kSplitMaxCus;  // CUs a balanced launch spreads over
+  int dev = -1;               // the device that was current in ctm_init
   double* obs_y;             // [d^2][x Dl x]
   double* obs_w;             // [d^2][x Dl x]
   double* obs_op;            // [d^4] device copy of an operator
@@ -2048,7 +2049,9 @@ int observable(ctm_ctx* c, int kind, const double* op_host, double* out_host) {
 // device keeps the last blocks: at most kKeptBlocks of together kKeptBytes.  A call
 // owns the block it has taken, and hands it back after its stream has been
 // synchronised, so blocks pass between threads and streams idle.  They are freed
-// when a context or cell is destroyed, when an allocation fails, and to make room.
+// when a context or cell of the device is destroyed, when the allocation of a
+// context, cell, tape or workspace fails there, by ctm_release_workspaces, and to
+// make room.
 // Inside a stream capture, where no allocation is allowed, none is used.
 // ---------------------------------------------------------------------------
 namespace sictm {
@@ -2069,11 +2072,6 @@ struct KeptSet {
 std::mutex g_kept_mu;
 KeptSet g_kept[kBatchMaxDevices];
 
-int kept_device() {
-  int dev = 0;
-  return hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kBatchMaxDevices ? dev : -1;
-}
-
 KeptBlock kept_remove(KeptSet& k, int i) {
   const KeptBlock b = k.b[i];
   for (int j = i + 1; j < k.n; ++j) k.b[j - 1] = k.b[j];
@@ -2093,7 +2091,7 @@ struct CallScratch {
   CallScratch(size_t need, hipStream_t s) : bytes(need), stream(s) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone)
-      dev = kept_device();
+      dev = current_device();
     if (dev >= 0) {
       std::lock_guard<std::mutex> lock(g_kept_mu);
       KeptSet& k = g_kept[dev];
@@ -2133,8 +2131,12 @@ struct CallScratch {
 
 }  // namespace
 
-void release_kept_blocks() {
-  const int dev = kept_device();
+int current_device() {
+  int dev = 0;
+  return hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kBatchMaxDevices ? dev : -1;
+}
+
+void release_kept_blocks(int dev) {
   if (dev < 0) return;
   KeptSet k;
   {
@@ -2149,7 +2151,7 @@ hipError_t device_malloc(void** p, size_t bytes) {
   hipError_t e = hipMalloc(p, bytes);
   if (e == hipSuccess) return e;
   (void)hipGetLastError();
-  release_kept_blocks();
+  release_kept_blocks(current_device());
   return hipMalloc(p, bytes);
 }
 
@@ -2201,6 +2203,7 @@ ctm_status ctm_init(ctm_ctx** out, const ctm_config* cfg, const double* site_dev
   ctm_ctx* c = new ctm_ctx();
   set_dims(c, cfg);
   c->st = (hipStream_t)stream;
+  c->dev = current_device();
   {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
@@ -2309,8 +2312,9 @@ void ctm_destroy(ctm_ctx* c) {
   if (c->hbuf) (void)hipHostFree(c->hbuf);
   if (c->rb) rocblas_destroy_handle(c->rb);
   if (c->own_ws && c->ws) (void)hipFree(c->ws);
+  const int dev = c->dev;
   delete c;
-  release_kept_blocks();
+  release_kept_blocks(dev);
 }
 
 ctm_status ctm_set_isometries(ctm_ctx* c, const double* X_dev, const double* Yt_dev) {
@@ -2693,6 +2697,8 @@ ctm_status ctm_gemm_f64_split(int count, const double* const* A, const double* c
                       : launch_gemm(g, DT::F64, DT::F64, DT::F64, (hipStream_t)stream);
   return r ? CTM_E_DEVICE : CTM_OK;
 }
+
+void ctm_release_workspaces(void) { release_kept_blocks(current_device()); }
 
 ctm_status ctm_qr_f64(int count, double* const* W, int N, int k, void* stream) {
   if (count < 0 || count > kMaxProb || !W || k < 1 || N < k)
