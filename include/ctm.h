@@ -493,7 +493,7 @@ ctm_status ctm_qr_f64(int count, double* const* W, int N, int k, void* stream);
 
 /* ctm_qr_f64 and ctm_svd_f64 keep the workspaces of their last calls on a
  * device, at most four of together 256 MiB.  They are given back when a context
- * or a unit cell of that device is destroyed, when an allocation of one
+ * or a unit cell of that device is destroyed, when an allocation of this library
  * fails there, and by this call (those of the current device). */
 void ctm_release_workspaces(void);
 

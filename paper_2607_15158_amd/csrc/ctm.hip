@@ -1601,7 +1601,7 @@ int enqueue_batch(ctm_ctx* const* ctxs, int n) {
     tb.host = nullptr;
     tb.cap = 0;
     const size_t cap = std::max<size_t>(2 * gs.size(), 256);
-    if (hipMalloc((void**)&tb.dev, cap * sizeof(GroupItem)) != hipSuccess ||
+    if (device_malloc((void**)&tb.dev, cap * sizeof(GroupItem)) != hipSuccess ||
         hipHostMalloc((void**)&tb.host, cap * sizeof(GroupItem), hipHostMallocDefault) != hipSuccess)
       return restore(fail(nullptr, CTM_E_NOMEM, "descriptor table of the batched move"));
     tb.cap = cap;
@@ -2049,9 +2049,8 @@ int observable(ctm_ctx* c, int kind, const double* op_host, double* out_host) {
 // device keeps the last blocks: at most kKeptBlocks of together kKeptBytes.  A call
 // owns the block it has taken, and hands it back after its stream has been
 // synchronised, so blocks pass between threads and streams idle.  They are freed
-// when a context or cell of the device is destroyed, when the allocation of a
-// context, cell, tape or workspace fails there, by ctm_release_workspaces, and to
-// make room.
+// when a context or cell of the device is destroyed, when an allocation of this
+// library fails there, by ctm_release_workspaces, and to make room.
 // Inside a stream capture, where no allocation is allowed, none is used.
 // ---------------------------------------------------------------------------
 namespace sictm {

@@ -28,6 +28,8 @@
 #include <string>
 #include <vector>
 
+#include "common.h"
+
 namespace {
 
 constexpr size_t kAlign = 256;
@@ -240,7 +242,7 @@ ctm_status ctm_server_create(ctm_server** out, size_t arena_bytes, int max_slots
   *out = nullptr;
   ctm_server* s = new ctm_server();
   s->arena_bytes = arena_bytes / kAlign * kAlign;
-  if (hipMalloc((void**)&s->arena, s->arena_bytes) != hipSuccess) {
+  if (sictm::device_malloc((void**)&s->arena, s->arena_bytes) != hipSuccess) {
     delete s;
     return CTM_E_NOMEM;
   }

@@ -1,6 +1,7 @@
 """The workspaces that ctm_qr_f64 and ctm_svd_f64 keep are given back: those of a
 context's device when it is destroyed, whatever device is current then; those of the
-current device by ctm_release_workspaces.  A small library that is loaded before the
+current device by ctm_release_workspaces and when an allocation of the library fails
+there, the serving arena's among them.  A small library that is loaded before the
 runtime plays it (two devices of 1 GiB, kernels that do nothing), so no GPU is needed."""
 import os
 import shutil
@@ -101,6 +102,7 @@ def context(dev):
 
 
 lib.ctm_destroy.argtypes = [V]
+lib.ctm_server_destroy.argtypes = [V]
 qr(0)
 qr(1)
 block = used()[0]
@@ -117,6 +119,17 @@ qr(0)
 play.play_device(1)
 lib.ctm_release_workspaces()
 assert used() == [block, 0], used()
+# an arena that fits only without the kept block
+play.play_device(0)
+s = V()
+lib.ctm_server_create.argtypes = [ctypes.POINTER(V), Z, I]
+assert lib.ctm_server_create(ctypes.byref(s), (1 << 30) - (16 << 20), 4) == 0
+assert used() == [(1 << 30) - (16 << 20), 0], used()
+lib.ctm_server_destroy(s)
+assert used() == [0, 0], used()
+# what no block makes room for is refused as before
+qr(0)
+assert lib.ctm_server_create(ctypes.byref(s), 2 << 30, 4) != 0
 """
 
 
