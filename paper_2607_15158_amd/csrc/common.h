@@ -193,6 +193,7 @@ size_t qr_workspace_bytes(int count, int N, int k);
 // k x k triangle): the shapes launch_qr accepts, also where it then runs on
 // leaves twice as tall.
 bool qr_plan_ok(int N, int k);
+void qr_plan_layout(int N, int k, int* leaves, int* wide, int* levels);
 int launch_qr(int count, double* const* W, int N, int k, void* ws, hipStream_t s);
 // The same factorisation with its sums in the order of qr_rows.hip.
 size_t qr_ordered_workspace_bytes(int count, int N, int k);

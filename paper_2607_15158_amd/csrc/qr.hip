@@ -762,6 +762,15 @@ bool qr_plan_ok(int N, int k) {
   return pl.wide || (N + pl.nb - 1) / pl.nb <= kLeafRows;
 }
 
+// The layout that N x k takes: its leaves, whether of eight wavefronts, and the
+// levels of the tree above them (tests hold shapes to the branch they are there for).
+void qr_plan_layout(int N, int k, int* leaves, int* wide, int* levels) {
+  const QrPlan pl = make_plan(N, k);
+  *leaves = pl.nb;
+  *wide = pl.wide;
+  *levels = pl.depth;
+}
+
 // Sized by the four-wavefront leaves, whose number grows with N: callers carve
 // the workspace for their full N and also run fewer rows, whose plan may have more
 // leaves than the full one's tall leaves (1152 rows 3, 1100 rows 8).
