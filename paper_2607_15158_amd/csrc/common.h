@@ -31,6 +31,12 @@ __device__ __forceinline__ double readlane_f64(double x, int l) {
   return __hiloint2double(hi, lo);
 }
 
+// A key for ranks by counting: a NaN ranks as infinity, so that ties by index make
+// the ranks a permutation whatever the values are (with NaN compared as it is, its
+// rank would be 0 beside another's, and a place that nothing is written to would be
+// read as an index).
+__device__ __forceinline__ double rank_key(double x) { return x == x ? x : __builtin_inf(); }
+
 // Sum over each aligned group of 16 lanes, in every lane of the group:
 // quad_perm(1,0,3,2), quad_perm(2,3,0,1), row_half_mirror, row_mirror.
 __device__ __forceinline__ double row_sum16(double x) {

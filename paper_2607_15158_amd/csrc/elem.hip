@@ -256,10 +256,10 @@ __global__ void k_proj_prep_full(const double* U, const double* Vt, const double
 __global__ __launch_bounds__(256) void k_rank_desc(const double* __restrict__ s, int n,
                                                    int* __restrict__ perm) {
   for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
-    const double v = s[i];
+    const double v = rank_key(s[i]);
     int r = 0;
     for (int j = 0; j < n; ++j) {
-      const double w = s[j];
+      const double w = rank_key(s[j]);
       r += (w > v || (w == v && j < i)) ? 1 : 0;
     }
     perm[r] = i;
@@ -620,10 +620,10 @@ __global__ void k_symmetrize_edge(double* T, int x, int Dl) {
 __global__ void k_c4v_order(const double* w, const double* V, int n, int keep, double* P) {
   extern __shared__ int order[];
   for (int j = threadIdx.x; j < n; j += blockDim.x) {
-    const double aj = fabs(w[j]);
+    const double aj = rank_key(fabs(w[j]));
     int rank = 0;
     for (int o = 0; o < n; ++o) {
-      const double ao = fabs(w[o]);
+      const double ao = rank_key(fabs(w[o]));
       rank += (ao > aj) || (ao == aj && o < j);
     }
     order[rank] = j;

@@ -116,7 +116,11 @@ __global__ __launch_bounds__(256) void svd_prep(SvdArgs a) {
   }
   for (int c = tid; c < n; c += 256) {
     int rank = 0;
-    for (int o = 0; o < n; ++o) rank += (nrm[o] > nrm[c]) || (nrm[o] == nrm[c] && o < c);
+    const double v = rank_key(nrm[c]);
+    for (int o = 0; o < n; ++o) {
+      const double w = rank_key(nrm[o]);
+      rank += (w > v) || (w == v && o < c);
+    }
     perm[rank] = c;
   }
   __syncthreads();
@@ -836,10 +840,10 @@ __global__ __launch_bounds__(1024) void svd_finalize(SvdArgs a) {
   __syncthreads();
   // descending order, ties by index
   for (int c = tid; c < n; c += 1024) {
-    const double sc = snorm[c];
+    const double sc = rank_key(snorm[c]);
     int rank = 0;
     for (int o = 0; o < n; ++o) {
-      const double so = snorm[o];
+      const double so = rank_key(snorm[o]);
       rank += (so > sc) || (so == sc && o < c);
     }
     order[rank] = c;
