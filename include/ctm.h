@@ -207,11 +207,13 @@ ctm_status ctm_move_poll(ctm_ctx* ctx, int* done, ctm_move_info* info);
  * lattice symmetry are recorded and launched together on the stream of the
  * first such context: at every step of the move the float64 GEMMs of all of
  * them (the enlarged corners, the SI applications, rho, the projectors and
- * the renormalisation) run as one persistent grouped launch over a device
- * table of (problem, tile) work items, and the other operations (QR, SVD,
- * signs, norms, spectra) follow one after another.  Each context's results
- * are bit for bit those of ctm_move (the tile kernels' sums do not depend on
- * the grid; the split SI product keeps its own launch).  Other moves
+ * the renormalisation) run as at most two persistent grouped launches over a
+ * device table of (problem, tile) work items, one of the small products and
+ * one of those on the tile kernels; products on the split kernel (cut or whole
+ * tiles) keep a launch of their own per context, and the other operations (QR,
+ * SVD, signs, norms, spectra) follow one after another.  Each context's results
+ * are bit for bit those of ctm_move (the sums of the grouped products do not
+ * depend on the grid).  Other moves
  * (growth, full SVD, C4v, float32/bfloat16) run as ctm_move_async on their
  * own streams.  Work queued earlier on a batched context's own stream is
  * waited for first.  infos (n entries) or NULL; returns the first error
@@ -475,10 +477,10 @@ ctm_status ctm_gemm_f64(int count, const double* const* A, const double* const* 
  * `count` flags (0 or 1) as in ctm_gemm_f64; C is row-major with leading
  * dimension ldc.  A tile has 128, 192 or 256 rows and as many columns as N
  * needs.  The split applies when scratch is non-NULL and 16-byte aligned,
- * N <= 160, K spans at
- * least 16 slices (K > 240), lda is even, the A bases are 16-byte aligned and
- * the B bases 16-byte aligned (even ldb) or 8-byte aligned (odd ldb);
- * otherwise the plain tile kernel runs.  If used_split is non-NULL it
+ * N <= 160, K spans at least 16 slices (K > 240), lda is even, the A bases are
+ * 16-byte aligned and the B bases 16-byte aligned (even ldb) or 8-byte aligned
+ * (odd ldb); otherwise the product runs as ctm_gemm_f64 runs it, on the kernel
+ * its shape selects (no tile of it is cut).  If used_split is non-NULL it
  * receives 1 when the split ran, else 0. */
 size_t ctm_gemm_f64_split_scratch_bytes(void);
 ctm_status ctm_gemm_f64_split(int count, const double* const* A, const double* const* B,

@@ -763,7 +763,7 @@ def gemm_f64_split(A: Sequence, B: Sequence, C: Sequence, M, N, K, trans_a: Sequ
                    ncu=256, lda=None, ldb=None, ldc=None, alpha=1.0, accumulate=0,
                    stream=None) -> bool:
     """The SI product split evenly over ncu CUs; returns whether the split
-    ran (else the plain tile kernel did)."""
+    ran (else the product ran as gemm_f64 runs it)."""
     tr = (ctypes.c_int * len(A))(*[int(t) for t in trans_a])
     if lda is None:
         if len(set(int(t) for t in trans_a)) > 1 and M != K:

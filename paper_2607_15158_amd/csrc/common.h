@@ -132,9 +132,9 @@ inline void gemm_set_rowmajor_c(GemmBatch& g, long ldc) {
 // Accumulation is float64 for F64 inputs and float32 otherwise.
 int launch_gemm(const GemmBatch& g, DT ta, DT tb, DT tc, hipStream_t s);
 // Whether a float64 product is small: its workgroups then split K over their
-// wavefronts; or else runs on whole tiles of the split kernel: at least 64 rows
-// (its tiles have 128 or more) and more than one slice of K.  launch_gemm sends
-// such products there.  Their bits do not depend on the grid, but differ from
+// wavefronts; or else runs on whole tiles of the split kernel: more than one slice
+// of K, and at least 97 rows (its tiles have 128 or more), 64 where K >= 256.
+// launch_gemm sends such products there.  Their bits do not depend on the grid, but differ from
 // the tile kernels'.
 bool gemm_short_applies(const GemmBatch& g);
 bool gemm_whole_applies(const GemmBatch& g);

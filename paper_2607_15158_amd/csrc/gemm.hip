@@ -36,10 +36,6 @@ template <>
 __device__ __forceinline__ __bf16 cvt<__bf16, double>(double x) { return (__bf16)(float)x; }
 template <>
 __device__ __forceinline__ __bf16 cvt<__bf16, float>(float x) { return (__bf16)x; }
-template <>
-__device__ __forceinline__ float cvt<float, __bf16>(__bf16 x) { return (float)x; }
-template <>
-__device__ __forceinline__ double cvt<double, __bf16>(__bf16 x) { return (double)(float)x; }
 
 __device__ __forceinline__ int xcd_remap(int bid, int nb) {
   const int xcd = bid & 7, idx = bid >> 3;
@@ -394,9 +390,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, 512 / (64 * WGM * WGN)) void gemm_s
 }
 
 // ---------------------------------------------------------------------------
-// Split products (stream-K style): C = op(A) B with long K.  A launch of one tile per workgroup leaves CUs idle or
-// half loaded when the tiles do not fill the chip evenly.  Here one workgroup
-// of 8 wavefronts per CU takes an equal, contiguous range of the (tile,
+// Split products (stream-K style): C = op(A) B with long K.  A launch of one
+// tile per workgroup leaves CUs idle or half loaded when the tiles do not fill
+// the chip evenly.  Here one workgroup of 8 wavefronts per CU takes an equal, contiguous range of the (tile,
 // 16-wide K slice) space.  A tile inside one range is written directly; a
 // tile cut by range boundaries leaves partial tiles in scratch (slot 2w for
 // the segment that starts range w, 2w+1 for the one that ends it), which a

@@ -13,9 +13,9 @@
 // reached delta < tol (at the full environment dimension) or their move
 // budget, and admits new ones.  SI moves replay a captured HIP graph per
 // request, or, for requests up to a size set by ctm_server_batching, move
-// together through ctm_move_batch_async (grouped launches over all of them).  Moves of different requests therefore overlap on the device,
-// and a result does not depend on what else runs:
-// each request executes exactly the kernels, launch shapes and reduction
+// together through ctm_move_batch_async (grouped launches over all of them).
+// Moves of different requests therefore overlap on the device, and a result does
+// not depend on what else runs: each request executes exactly the kernels, launch shapes and reduction
 // orders of a solo ctm_converge.
 
 #include "../../include/ctm.h"

@@ -222,28 +222,10 @@ __global__ __launch_bounds__(256) void k_copyltu(SmallArgs a) {
   }
 }
 
-// Inverse of an upper-triangular n x n matrix (n <= 256), one block per
-// matrix, thread j owns column j: back substitution row by row.  A zero
-// diagonal entry (a rank-deficient block) gives a zero row.
-__global__ __launch_bounds__(256) void k_tri_inv(SmallArgs a) {
-  const int b = blockIdx.x, n = a.n, j = threadIdx.x;
-  const double* R = a.in[b];
-  double* X = a.out[b];
-  if (j >= n) return;
-  for (int i = n - 1; i >= 0; --i) {
-    double v = 0.0;
-    if (j >= i) {
-      double acc = i == j ? 1.0 : 0.0;
-      for (int l = i + 1; l <= j; ++l) acc -= R[(long)i * n + l] * X[(long)l * n + j];
-      const double d = R[(long)i * n + i];
-      v = d != 0.0 ? acc / d : 0.0;
-    }
-    X[(long)i * n + j] = v;
-  }
-}
-
-// The inverse for n <= kTriLds with R's upper triangle in LDS, row-packed (row l
-// starts at l n - l (l - 1) / 2): a wavefront per column of X, its rows in the
+// Inverses of upper-triangular n x n matrices (n <= kTriLds, the widest block that
+// a context has), a zero diagonal entry (a rank-deficient block) giving a zero row.
+// R's upper triangle sits in LDS, row-packed (row l starts at l n - l (l - 1) / 2):
+// a wavefront per column of X, its rows in the
 // registers of the lanes (lane, lane + 64, lane + 128).  Step i divides entry i
 // and takes its multiple of R's column i from the entries above, so that a
 // column is n steps of one division and one multiply-add per lane; 16 columns
@@ -252,7 +234,7 @@ __global__ __launch_bounds__(256) void k_tri_inv(SmallArgs a) {
 // this takes 21.)
 constexpr int kTriLds = 192;
 
-__global__ __launch_bounds__(1024) void k_tri_inv_lds(SmallArgs a) {
+__global__ __launch_bounds__(1024) void k_tri_inv(SmallArgs a) {
   __shared__ double Rs[kTriLds * (kTriLds + 1) / 2];
   const int b = blockIdx.y, n = a.n, lane = threadIdx.x & 63;
   const double* R = a.in[b];
@@ -1389,10 +1371,8 @@ int backward(Run& r, const VjpView& v, const Dims& m, Bufs& b, const State& in,
         sa.in[j] = b.R[j];
         sa.out[j] = b.Rinv[j];
       }
-      if (k <= kTriLds)
-        k_tri_inv_lds<<<dim3((k + 15) / 16, 8), 1024, 0, r.st>>>(sa);
-      else
-        k_tri_inv<<<8, 256, 0, r.st>>>(sa);
+      if (k > kTriLds) return r.fail("adjoint QR wider than its triangular inverse; launch refused");
+      k_tri_inv<<<dim3((k + 15) / 16, 8), 1024, 0, r.st>>>(sa);
       CTM_HIP_TRY(hipGetLastError());
       ManyArgs qc{};
       for (int j = 0; j < 8; ++j) {
