@@ -131,8 +131,8 @@ int check_gemm(ctm_cell* c, const GemmBatch& g) {
 // run through all sweeps, 7e-9 up to k = 35, 2e-8 at k = 48, 4e-8 at k = 70 (of 8
 // states), 3e-7 at k = 105.  A state is then no longer, to the 4e-8 that states are
 // compared by, the one that the other order gives.  So wide cuts keep one order,
-// whatever is faster elsewhere: the rotations from kOrderedSvd = 33 on (k = 48: 12.2
-// ms an iteration, 9.5 with the one-workgroup kernel; D 4, chi 64: 22.8 and 18.8),
+// whatever is faster elsewhere: the rotations from kOrderedSvd = 33 on (k = 48: 11.3
+// ms an iteration, 9.5 with svd_small; D 4, chi 64: 22.8 and 18.8),
 // and from kOrderedSums = 97 on the products, the QRs and the absorptions (D 5, chi
 // 100: 87 ms, 52 without).
 bool ordered_svd(const ctm_cell* c) { return c->k >= kOrderedSvd; }

@@ -13,23 +13,23 @@
 // itself needs dozens: R^T = Ut S V'^T gives A = (Q V') S (P Ut)^T.
 //
 // Up to n = 96 (128 for the values alone) one workgroup holds the columns of
-// a matrix in LDS for all sweeps (svd_small).  Above that, block-pair parallel
-// ordering: the columns are cut into blocks of kBlk; an outer sweep pairs the
-// blocks in a round-robin tournament, one workgroup per block pair and matrix,
-// the rounds separated by grid barriers of one cooperative launch, or by
-// launches inside a stream capture.  The workgroup loads the columns of both
-// blocks into LDS and rotates the pairs across the two blocks in kBlk steps of
+// a matrix in LDS for all sweeps (svd_small).  Above that, and at every n where
+// the caller asks for this order, block-pair parallel ordering: the columns are
+// cut into blocks of kBlk; an outer sweep pairs the blocks in a round-robin
+// tournament, four wavefronts per block pair and matrix, the rounds separated by
+// the barriers of one workgroup (n <= 64), by grid barriers of one cooperative
+// launch, or by launches inside a stream capture.  The columns of both blocks are
+// loaded into LDS and the pairs across the two blocks rotated in kBlk steps of
 // kBlk disjoint pairs (in the sweep's first round, where every block is visited
 // once, the pairs within each block first, in kBlk - 1 more steps), so that
 // every column pair meets once per sweep; 16 lanes per pair (rows spread over
-// the lanes, dot products reduced by DPP row sums); the rotations of the visit are
-// accumulated in a 2 kBlk x 2 kBlk matrix W and applied to the right vectors
+// the lanes, dot products reduced by DPP row sums); the rotations of the visit
+// are accumulated in a 2 kBlk x 2 kBlk matrix W and applied to the right vectors
 // once at the end (V_cols <- V_cols W).  A per-matrix flag records whether a
 // sweep rotated anything, and the sweeps end after one without rotations.
-// Columns that end numerically zero
-// (rank-deficient input) are replaced by an orthonormal completion so that
-// u stays orthogonal.  Singular values are returned in descending order (ties by
-// index).
+// Columns that end numerically zero (rank-deficient input) are replaced by an
+// orthonormal completion so that u stays orthogonal.  Singular values are
+// returned in descending order (ties by index).
 
 #include "common.h"
 
@@ -401,7 +401,7 @@ __device__ __forceinline__ void block_round(const SvdArgs& a, int sweep, int rou
   int& rot = sh.rot;
   const int n = a.n, nblk = a.nblk;
   const int b0 = tour(bp, round, nblk), b1 = tour(nblk - 1 - bp, round, nblk);
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x & 255;   // of the block pair's four wavefronts
   double* Uc = a.work + (size_t)mat * 2 * n * n;
   double* Vc = Uc + (size_t)n * n;
   // local column j -> global column: j < kBlk from b0, else from b1
@@ -638,6 +638,26 @@ __global__ __launch_bounds__(256) void svd_sweeps(SvdArgs a, int count) {
   }
 }
 
+// All sweeps in one ordinary launch, where one workgroup holds all G block pairs of
+// a matrix (n <= 64): its barriers separate the rounds.  A cooperative launch goes
+// to a queue of its own, for which the stream waits both ways: a unit cell of one
+// site, D 2, k = 40, took 6.0 ms an iteration beside other contexts, 3.9 so.  Kernel times are alike (4 matrices, n = 48: 780 us with two
+// workgroups and both columns through LDS, 655 so; n = 64: 829 and 842); three pairs
+// on one CU take 1544 us at n = 70, where the cooperative launch takes 1288.
+template <int RPL, int G>
+__global__ __launch_bounds__(256 * G) void svd_sweeps_one(SvdArgs a) {
+  __shared__ RoundLds<RPL> sh[G];
+  const int mat = blockIdx.x, pair = threadIdx.x >> 8;
+  int* flags = a.flags + mat * kMaxSweeps;
+  for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
+    for (int round = 0; round < a.nblk - 1; ++round) {
+      block_round<RPL>(a, sweep, round, mat, pair, sh[pair]);
+      __syncthreads();
+    }
+    if (!__hip_atomic_load(&flags[sweep], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
+  }
+}
+
 // Singular values, normalisation, completion of zero columns, ordering.
 __global__ __launch_bounds__(1024) void svd_finalize(SvdArgs a) {
   const int mat = blockIdx.x;
@@ -861,17 +881,27 @@ __global__ __launch_bounds__(1024) void svd_finalize(SvdArgs a) {
   }
 }
 
-// The block-pair kernels: one cooperative launch, or inside a stream capture
-// (where none can be recorded) one launch per round.
+// The block-pair kernels: one workgroup per matrix up to n = 64, above that one
+// cooperative launch, or inside a stream capture (where none can be recorded) one
+// launch per round.
 int launch_block_svd(const SvdArgs& a, int count, hipStream_t s) {
   const int n = a.n, nblk = a.nblk;
+  if (nblk <= 4) {
+    if (nblk == 2)
+      svd_sweeps_one<2, 1><<<count, 256, 0, s>>>(a);
+    else if (n <= 48)
+      svd_sweeps_one<3, 2><<<count, 512, 0, s>>>(a);
+    else
+      svd_sweeps_one<4, 2><<<count, 512, 0, s>>>(a);
+    CTM_HIP_TRY(hipGetLastError());
+    return 0;
+  }
   const dim3 grid(nblk / 2, count);
   const int rpl = (n + kLanesPerPair - 1) / kLanesPerPair;
   SvdArgs arg = a;
   int cnt = count;
   void* args[] = {&arg, &cnt};
-  const void* fn = rpl <= 4    ? (const void*)svd_sweeps<4>
-                   : rpl <= 6  ? (const void*)svd_sweeps<6>
+  const void* fn = rpl <= 6    ? (const void*)svd_sweeps<6>
                    : rpl <= 8  ? (const void*)svd_sweeps<8>
                    : rpl <= 10 ? (const void*)svd_sweeps<10>
                                : (const void*)svd_sweeps<12>;
@@ -883,9 +913,7 @@ int launch_block_svd(const SvdArgs& a, int count, hipStream_t s) {
   (void)hipGetLastError();
   for (int sweep = 0; sweep < kMaxSweeps; ++sweep)
     for (int round = 0; round < nblk - 1; ++round) {
-      if (rpl <= 4)
-        svd_block_round<4><<<grid, 256, 0, s>>>(a, sweep, round);
-      else if (rpl <= 6)
+      if (rpl <= 6)
         svd_block_round<6><<<grid, 256, 0, s>>>(a, sweep, round);
       else if (rpl <= 8)
         svd_block_round<8><<<grid, 256, 0, s>>>(a, sweep, round);
